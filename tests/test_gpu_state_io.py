@@ -1,0 +1,52 @@
+"""Fields and canonical state read back from every storage form at both
+streaming parities, on lattices whose size is no multiple of a workgroup.
+
+Tolerance: both sides sum the same Q stored values (at most one each, FP64)
+in FP64, 19 roundings of 2^-53 of a sum of about one, then one division."""
+import numpy as np
+import pytest
+
+import workloads as W
+from helpers import _print_case, gpu_lattice
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2 * 20 * 2.0 ** -53
+BOXES = {"d2q9": (9, 67, 13, 1), "d3q19": (19, 9, 7, 13), "one_wave": (9, 3, 2, 1)}
+
+
+@pytest.mark.parametrize("steps", [0, 1, 2])
+@pytest.mark.parametrize("form", ["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("box", sorted(BOXES))
+def test_fields_are_the_moments_of_the_state(box, form, steps):
+    import torch
+    import paper_1901_09745_amd.psclbm as P
+    q, nx, ny, nz = BOXES[box]
+    F = (3e-4, -2e-4, 0.0 if q == 9 else 1e-4)
+    lat = W.LatticeSpec(q=q, nx=nx, ny=ny, nz=nz, tau=0.7, force=F,
+                        faces=("periodic",) * 2 + ("bounce_back",) * 2 + ("periodic",) * 2)
+    _print_case(test="fields", box=box, form=form, steps=steps)
+    G = gpu_lattice(lat, None, form)
+    G.set_f(torch.from_numpy(W.random_state(lat, 8)).cuda())
+    G.rasterize(None)
+    if steps:
+        G.step(steps)
+    f = G.get_f().cpu().numpy()
+    rho, u = (t.cpu().numpy() for t in G.macros())
+    E = {9: [(0, 0, 0), (1, 0, 0), (0, 1, 0), (-1, 0, 0), (0, -1, 0), (1, 1, 0), (-1, 1, 0),
+             (-1, -1, 0), (1, -1, 0)],
+         19: [(0, 0, 0), (1, 0, 0), (-1, 0, 0), (0, 1, 0), (0, -1, 0), (0, 0, 1), (0, 0, -1),
+              (1, 1, 0), (-1, -1, 0), (1, -1, 0), (-1, 1, 0), (1, 0, 1), (-1, 0, -1), (1, 0, -1),
+              (-1, 0, 1), (0, 1, 1), (0, -1, -1), (0, 1, -1), (0, -1, 1)]}[q]
+    ref = f.sum(0)
+    assert np.abs(rho - ref).max() <= TOL
+    for a in range(3):
+        ju = (np.tensordot(np.array([e[a] for e in E], float), f, (0, 0)) + 0.5 * F[a]) / ref
+        assert np.abs(u[..., a] - ju).max() <= TOL
+    # either output alone
+    only = torch.zeros_like(torch.from_numpy(rho)).cuda()
+    P.lbm_get_macros(G.ctx, only, None)
+    assert torch.equal(only.cpu(), torch.from_numpy(rho))
+    only = torch.zeros(u.shape, dtype=torch.float64, device="cuda")
+    P.lbm_get_macros(G.ctx, None, only)
+    assert torch.equal(only.cpu(), torch.from_numpy(u))
