@@ -413,17 +413,7 @@ int particle_forces(psclbm_ctx* ctx, double* d_force, double* d_torque) {
   if (!ctx) return PSCLBM_EINVAL;
   if (!ctx->rasterized) return PSCLBM_ESTATE;
   if (ctx->np == 0 || (!d_force && !d_torque)) return PSCLBM_OK;
-  const double* src = ctx->facc[ctx->force_buf];
-  const size_t pitch = 6 * sizeof(double);
-  int rc = PSCLBM_OK;
-  if (d_force)
-    rc = hip_ok(hipMemcpy2DAsync(d_force, 3 * sizeof(double), src, pitch, 3 * sizeof(double),
-                                 ctx->np, hipMemcpyDeviceToDevice, ctx->stream));
-  if (!rc && d_torque)
-    rc = hip_ok(hipMemcpy2DAsync(d_torque, 3 * sizeof(double), src + 3, pitch,
-                                 3 * sizeof(double), ctx->np, hipMemcpyDeviceToDevice,
-                                 ctx->stream));
-  return rc;
+  return launch_read_forces(ctx, d_force, d_torque);
 }
 
 // Material and friction parameters of a dynamic DEM step.

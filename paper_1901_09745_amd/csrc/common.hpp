@@ -381,6 +381,7 @@ int launch_init_equilibrium(psclbm_ctx* c, const double* rho, const double* u);
 int launch_set_f(psclbm_ctx* c, const double* f);
 int launch_get_f(psclbm_ctx* c, double* f);
 int launch_get_macros(psclbm_ctx* c, double* rho, double* u);
+int launch_read_forces(psclbm_ctx* c, double* force, double* torque);
 int launch_rasterize(psclbm_ctx* c, const psclbm_particles* p, bool dem_bins);
 // The step with the contact workgroups of dem (the DEM contact forces of the
 // step's start into fcontact); dem null: the plain step.
