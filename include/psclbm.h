@@ -237,14 +237,15 @@ int dem_step(psclbm_ctx* ctx, const psclbm_dem_params* prm, double* d_x, double*
  * and advances the particles by one dem_step driven by that step's force and
  * torque, in place in d_x, d_u, d_omega (n particles, d_radius[n]).  The
  * result is that of those three calls in turn, up to the order of the FP64
- * sums of contact forces.  With n_sub == 1 the work of consecutive steps is
- * fused: the DEM wave of a particle, having integrated it, writes its
- * snapshot and enters it in the tile lists and DEM bins of the next step, so
- * a step is two kernels (plus one at the start of the call).  Without
- * friction and with adhesion the contacts are gathered by workgroups of the
- * step kernel; with friction (mu_f > 0 or theta_r > 0) or the Hertz contact
- * (gamma == 0) by the DEM kernel, which also records the spins the next
- * step's contacts read.  Afterwards the context holds the last step's
+ * sums of contact forces.  The work of consecutive (sub-)steps is fused: the
+ * DEM wave of a particle, having integrated it, enters it in the DEM bins of
+ * the next sub-step, and after the last one writes its snapshot and enters it
+ * in the tile lists and DEM bins of the next step, so a step is 1 + n_sub
+ * kernels (plus one at the start of the call).  Without friction and with
+ * adhesion the contacts of the first sub-step are gathered by workgroups of
+ * the step kernel; otherwise, and in the sub-steps after it, by the DEM
+ * kernel, which with friction also records the spins the next (sub-)step's
+ * contacts read.  Afterwards the context holds the last step's
  * rasterisation and force / torque accumulators, as after the three calls.
  * Errors: those of psc_rasterize, lbm_step and dem_step (EINVAL, EHIP;
  * sticky ESLOTS, ECONTACTS). */

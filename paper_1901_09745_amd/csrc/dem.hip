@@ -4,23 +4,23 @@
 // and twisting friction of Eqs. 22, 28, 29, sub-cycled n_sub times per
 // coupling step with the hydrodynamic force and torque held fixed.
 //
-// Per sub-step, two kernels: (1) bin the particles into a uniform grid whose
-// bins are at least 2 r_max + 1 wide, each bin entry a record of the
-// particle's position, velocity, radius and id; (2) one wave per particle
-// gathers its contacts from the records of the neighbouring bins and the
-// walls (so that no particle sees another's update), records the new contact
-// list, sums the forces over the wave and integrates the particle with
-// semi-implicit Euler.  The bin counts and records are triple buffered: each
-// binning fills one set and clears the set the binning after it fills.  With
-// friction the binning also copies the spins, which the contacts read, and
-// each contact's springs travel with the contact lists.
+// Per sub-step, one kernel after a first binning of the particles into a
+// uniform grid whose bins are at least 2 r_max + 1 wide, each bin entry a
+// record of the particle's position, velocity, radius and id: one wave per
+// particle gathers its contacts from the records of the neighbouring bins and
+// the walls (so that no particle sees another's update), records the new
+// contact list, sums the forces over the wave, integrates the particle with
+// semi-implicit Euler and enters it in the bins of the next sub-step.  The bin
+// counts and records are triple buffered: each binning fills one set and
+// clears the set the binning after it fills.  With friction the binning also
+// copies the spins (double buffered), which the contacts read, and each
+// contact's springs travel with the contact lists.
 //
-// The coupled step (n_sub = 1) gathers the contacts in leading workgroups of
-// the step kernel instead, which run beside the tiles (contacts need only
-// the binning of the step's start); its DEM kernel reads their forces,
-// integrates, and rasterises and bins the particles for the next step.  With
-// friction or the Hertz contact the DEM kernel gathers the contacts itself
-// from that binning, and records the spins for the next step's contacts.
+// The coupled step's first sub-step has its contacts gathered in leading
+// workgroups of the step kernel, which run beside the tiles (contacts need
+// only the binning of the step's start); with friction or the Hertz contact
+// the DEM kernel gathers them itself.  The DEM kernel of the last sub-step
+// also rasterises and bins the particles for the next step.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -93,9 +93,11 @@ __device__ inline void integrate_state(const IntArgs& p, double ri, const double
   }
 }
 
-// Rasterisation of the next coupled step by the DEM wave of this one: the
-// tile set to fill (all zero on entry) and the one to clear, the snapshot and
-// the DEM binning of the updated particle.
+// What the DEM wave of a sub-step leaves for the next one: the DEM binning
+// (when db.count is given) and spins (wnext) of the updated particle, and, when
+// the next sub-step is that of a new coupled step (build), its rasterisation:
+// the tile set to fill (all zero on entry) and the one to clear, and the
+// snapshot.
 struct NextOut {
   int build;
   Geom g;
@@ -115,8 +117,10 @@ struct NextOut {
 // coupled step kernel gathered), the contacts are gathered here
 // (dem_contact_wave, with friction when FRIC and Hertz's normal force when
 // HERTZ).  Every lane then integrates the particle (the same values), lane 0
-// stores it, and with nx.build the wave rasterises it for the next coupled
-// step.  Kinematic particles skip the contacts.
+// stores it, and the wave bins and rasterises it for the next sub-step or
+// coupled step (NextOut): a launch of its own for the binning cost 4.3 us a
+// sub-step (500 spheres, four sub-steps), as long as a third of the contacts.
+// Kinematic particles skip the contacts.
 template <bool FRIC, bool HERTZ>
 __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, IntArgs ia,
                                                       NextOut nx, double* x, double* u,
@@ -124,13 +128,12 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
                                                       const double* Ff, const double* Tf,
                                                       const double* fc_in) {
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (nx.build) {
+  if (nx.build)
     for (long long k = gid; k < nx.ntiles; k += (long long)gridDim.x * blockDim.x)
       nx.tstale[k] = 0;
-    if (nx.db.count)
-      for (long long k = gid; k < nx.db.nbins; k += (long long)gridDim.x * blockDim.x)
-        nx.db.stale[k] = 0;
-  }
+  if (nx.db.count)
+    for (long long k = gid; k < nx.db.nbins; k += (long long)gridDim.x * blockDim.x)
+      nx.db.stale[k] = 0;
   const int i = (int)(gid >> 6);
   const int lane = (int)(threadIdx.x & 63);
   if (i >= d.n) return;  // uniform over the wave
@@ -169,17 +172,19 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
       w[3 * i + a] = ws[a];
     }
   }
+  if (lane == 0) {
+    if (nx.db.count) dem_bin_insert(nx.db, d.three_d, nx.g, i, xs, us, ri, nx.err);
+    if constexpr (FRIC) {
+      if (nx.wnext)
+        for (int a = 0; a < 3; ++a) nx.wnext[3 * i + a] = ws[a];
+    }
+  }
   if (!nx.build) return;
   PSnap P;
   const bool ok = make_snap(d.three_d, xs, us, ws, ri, P, r_prev, cs_prev);
   if (lane == 0) {
     nx.snap[i] = P;
     if (!ok) atomicOr(nx.err, ERR_RADIUS);
-    if (nx.db.count) dem_bin_insert(nx.db, d.three_d, nx.g, i, xs, us, ri, nx.err);
-    if constexpr (FRIC) {
-      if (nx.wnext)
-        for (int a = 0; a < 3; ++a) nx.wnext[3 * i + a] = ws[a];
-    }
   }
   if (ok) bin_tiles(nx.g, d.three_d, nx.h, P, i, lane, nx.tcount, nx.tile_list, nx.cap, nx.err);
 }
@@ -308,6 +313,26 @@ static int launch_contacts(psclbm_ctx* c, bool fric, bool hertz, int n, const De
   return hip_ok(hipGetLastError());
 }
 
+// What a sub-step's DEM kernel leaves for the next one: its rasterisation
+// (build), DEM bins and spin snapshot (null: none).
+static NextOut next_out(psclbm_ctx* c, bool build, bool bins, double* wnext) {
+  NextOut nx;
+  std::memset(&nx, 0, sizeof(nx));
+  nx.build = build ? 1 : 0;
+  nx.g = c->geom;
+  nx.h = c->cfg.shell_h;
+  nx.snap = c->snap;
+  nx.tcount = c->tile_count_buf[c->tile_cur ^ 1];
+  nx.tstale = c->tile_count_buf[c->tile_cur];
+  nx.ntiles = c->ntiles;
+  nx.tile_list = c->tile_list;
+  nx.cap = c->cfg.max_tile_particles;
+  nx.db = dem_bin_out(c, bins);
+  nx.wnext = wnext;
+  nx.err = c->err;
+  return nx;
+}
+
 int launch_dem_step(psclbm_ctx* c, const psclbm_dem_params* prm, double* x, double* u, double* w,
                     const double* r, int n, const double* F, const double* T) {
   IntArgs ia = int_args(c, prm, n, F, T);
@@ -323,22 +348,27 @@ int launch_dem_step(psclbm_ctx* c, const psclbm_dem_params* prm, double* x, doub
   }
   const double E = dem_modulus(c, prm);
   if (!(E > 0.0)) return PSCLBM_EINVAL;
-  NextOut nx;
-  std::memset(&nx, 0, sizeof(nx));
   const bool fric = dem_friction(prm), hertz = prm->gamma == 0.0;
+  const DemBinOut b = dem_bin_out(c, true);
+  const long long bth = b.nbins > n ? b.nbins : n;
+  k_dem_bin<<<(unsigned)((bth + 127) / 128), 128, 0, c->stream>>>(
+      b, c->geom, n, c->geom.q == 19, x, u, r, c->err, w, fric ? c->wsnap[0] : nullptr);
+  int rc = hip_ok(hipGetLastError());
+  if (rc) return rc;
+  dem_bins_advance(c);
+  int wcur = 0;  // the spin snapshot of the current sub-step's start
   for (int s = 0; s < prm->n_sub; ++s) {
-    ia.wrap = s == prm->n_sub - 1;  // positions wrap once, after the last sub-step
-    const DemBinOut b = dem_bin_out(c, true);
-    const long long bth = b.nbins > n ? b.nbins : n;
-    k_dem_bin<<<(unsigned)((bth + 127) / 128), 128, 0, c->stream>>>(
-        b, c->geom, n, c->geom.q == 19, x, u, r, c->err, w, fric ? c->wsnap[0] : nullptr);
-    dem_bins_advance(c);
+    const bool last = s == prm->n_sub - 1;
+    ia.wrap = last;  // positions wrap once, after the last sub-step
     const DemArgs d = dem_args(c, prm, n, E);
-    const FricArgs fr = fric_args(c, prm, c->wsnap[0]);
-    const int rc = launch_contacts(c, fric, hertz, n, d, fr, ia, nx, x, u, w, r, F, T, nullptr);
+    const FricArgs fr = fric_args(c, prm, c->wsnap[wcur]);
+    const NextOut nx = next_out(c, false, !last, !last && fric ? c->wsnap[wcur ^ 1] : nullptr);
+    rc = launch_contacts(c, fric, hertz, n, d, fr, ia, nx, x, u, w, r, F, T, nullptr);
     if (rc) return rc;
     c->contact_cur ^= 1;
     c->springs_valid = fric ? 1 : 0;
+    if (!last) dem_bins_advance(c);
+    wcur ^= 1;
   }
   return PSCLBM_OK;
 }
@@ -357,67 +387,57 @@ int launch_coupled(psclbm_ctx* c, const psclbm_dem_params* prm, double* x, doubl
     E = dem_modulus(c, prm);
     if (!(E > 0.0)) return PSCLBM_EINVAL;
   }
-  if (prm->n_sub != 1 || n == 0) {
-    // sub-cycled DEM: the three calls in turn
+  if (n == 0) {
     for (int t = 0; t < nsteps; ++t) {
       int rc = launch_rasterize(c, p, false);
       if (!rc) c->np = n;
       if (!rc) rc = launch_step(c);
-      if (!rc && n > 0)
-        rc = launch_dem_step(c, prm, x, u, w, r, n, nullptr, nullptr);
       if (rc) return rc;
     }
     return PSCLBM_OK;
   }
   // with friction or the Hertz contact the DEM kernel gathers the contacts
-  const bool fric = !prm->kinematic && dem_friction(prm);
-  const bool hertz = !prm->kinematic && prm->gamma == 0.0;
-  const bool own_contacts = prm->kinematic || fric || hertz;
+  const bool dynamic = !prm->kinematic;
+  const bool fric = dynamic && dem_friction(prm);
+  const bool hertz = dynamic && prm->gamma == 0.0;
+  const bool own_contacts = !dynamic || fric || hertz;
   // first step's rasterisation, with its DEM binning (and spins)
-  int rc = launch_rasterize(c, p, !prm->kinematic);
+  int rc = launch_rasterize(c, p, dynamic);
   if (!rc && fric)
     rc = hip_ok(hipMemcpyAsync(c->wsnap[0], w, sizeof(double) * 3 * (size_t)n,
                                hipMemcpyDeviceToDevice, c->stream));
   if (rc) return rc;
   c->np = n;
-  const size_t ntiles = (size_t)c->ntiles;
-  int wcur = 0;  // the spin snapshot of the current step's start
+  int wcur = 0;  // the spin snapshot of the current sub-step's start
   for (int t = 0; t < nsteps; ++t) {
     // the step, with the contact workgroups on the binning of its start
-    const DemArgs d = dem_args(c, prm, n, E);
-    rc = own_contacts ? launch_step(c) : launch_step_contacts(c, &d, x, u, r);
+    const DemArgs d0 = dem_args(c, prm, n, E);
+    rc = own_contacts ? launch_step(c) : launch_step_contacts(c, &d0, x, u, r);
     if (rc) return rc;
-    const bool build = t + 1 < nsteps;
     const double* F = nullptr;
     const double* T = nullptr;
-    const IntArgs ia = int_args(c, prm, n, F, T);
-    NextOut nx;
-    std::memset(&nx, 0, sizeof(nx));
-    nx.build = build ? 1 : 0;
-    nx.g = c->geom;
-    nx.h = c->cfg.shell_h;
-    nx.snap = c->snap;
-    nx.tcount = c->tile_count_buf[c->tile_cur ^ 1];
-    nx.tstale = c->tile_count_buf[c->tile_cur];
-    nx.ntiles = (long long)ntiles;
-    nx.tile_list = c->tile_list;
-    nx.cap = c->cfg.max_tile_particles;
-    nx.db = dem_bin_out(c, build && !prm->kinematic);
-    nx.wnext = build && fric ? c->wsnap[wcur ^ 1] : nullptr;
-    nx.err = c->err;
-    const FricArgs fr = fric_args(c, prm, c->wsnap[wcur]);
-    rc = launch_contacts(c, fric, hertz, n, d, fr, ia, nx, x, u, w, r, F, T,
-                         own_contacts ? nullptr : c->fcontact);
-    if (rc) return rc;
-    if (!prm->kinematic) {
-      c->contact_cur ^= 1;
-      c->springs_valid = fric ? 1 : 0;
-    }
-    wcur ^= 1;
-    if (build) {
-      c->tile_cur ^= 1;
-      c->tile_count = c->tile_count_buf[c->tile_cur];
-      if (nx.db.count) dem_bins_advance(c);
+    IntArgs ia = int_args(c, prm, n, F, T);
+    for (int s = 0; s < prm->n_sub; ++s) {
+      const bool last = s == prm->n_sub - 1;
+      ia.wrap = last;  // positions wrap once, after the last sub-step
+      const bool build = last && t + 1 < nsteps;
+      const bool bins = dynamic && (build || !last);
+      const DemArgs d = dem_args(c, prm, n, E);
+      const FricArgs fr = fric_args(c, prm, c->wsnap[wcur]);
+      const NextOut nx = next_out(c, build, bins, bins && fric ? c->wsnap[wcur ^ 1] : nullptr);
+      rc = launch_contacts(c, fric, hertz, n, d, fr, ia, nx, x, u, w, r, F, T,
+                           own_contacts || s > 0 ? nullptr : c->fcontact);
+      if (rc) return rc;
+      if (dynamic) {
+        c->contact_cur ^= 1;
+        c->springs_valid = fric ? 1 : 0;
+      }
+      wcur ^= 1;
+      if (build) {
+        c->tile_cur ^= 1;
+        c->tile_count = c->tile_count_buf[c->tile_cur];
+      }
+      if (bins) dem_bins_advance(c);
     }
   }
   return PSCLBM_OK;
