@@ -137,7 +137,8 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
   const int i = (int)(gid >> 6);
   const int lane = (int)(threadIdx.x & 63);
   if (i >= d.n) return;  // uniform over the wave
-  const int D = d.three_d ? 3 : 2;
+  __shared__ int cand_lds[4 * CONTACT_LDS];
+  int* cand = cand_lds + CONTACT_LDS * (int)(threadIdx.x >> 6);
   const double ri = r[i];
   // the particle's previous snapshot: its c_s is reused while r is unchanged
   double r_prev = -1.0, cs_prev = 0.0;
@@ -155,12 +156,12 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
   double fsum[3] = {0.0, 0.0, 0.0};
   double tsum[3] = {0.0, 0.0, 0.0};
   if constexpr (FRIC || HERTZ) {
-    dem_contact_wave<FRIC, HERTZ>(d, i, lane, xs, us, ri, fsum, &fr, ws, tsum);
+    dem_contact_wave<FRIC, HERTZ>(d, i, lane, xs, us, ri, fsum, cand, &fr, ws, tsum);
   } else if (fc_in) {  // contacts gathered by the step kernel's contact workgroups
 #pragma unroll
     for (int a = 0; a < 3; ++a) fsum[a] = fc_in[3 * i + a];
   } else if (!ia.kinematic) {
-    dem_contact_wave(d, i, lane, xs, us, ri, fsum);
+    dem_contact_wave(d, i, lane, xs, us, ri, fsum, cand);
   }
   integrate_state(ia, ri, Ff + (size_t)ia.fstride * i, Tf + (size_t)ia.tstride * i, fsum,
                   FRIC ? tsum : nullptr, xs, us, ws);

@@ -28,7 +28,10 @@ __device__ inline double min_img(double d, int periodic, int L) {
 // F_C = 3 pi gamma R, a0^3 = 9 pi gamma R^2 / E, delta_C = a0^2/(2 6^{1/3} R).
 // Solved for s = x^{1/2} by Newton from above (g(s) = 2 s^4 - 4/3 s is convex
 // and increasing on the branch s >= 6^{-1/3}, so the iterates decrease
-// monotonically to the root).  Returns the repulsive-positive force, and the
+// monotonically to the root).  The iteration is one serial chain whose FP64
+// division is most of it, so it starts from a few FP32 steps: the first FP64
+// step then lands on or above the root from either side, and one or two more
+// reach it, against eight or so from the bound max(1, (1.5 t)^{1/4}).  Returns the repulsive-positive force, and the
 // contact radius a = x a0 and x in *a_out and *x_out when those are given.
 __device__ inline double jkr_force(double R, double E, double gamma, double delta, double* dC,
                                    double* a_out = nullptr, double* x_out = nullptr) {
@@ -43,13 +46,26 @@ __device__ inline double jkr_force(double R, double E, double gamma, double delt
   if (target <= 2.0 * sC * sC * sC * sC - (4.0 / 3.0) * sC) {
     s = sC;
   } else {
-    s = fmax(1.0, sqrt(sqrt(1.5 * fmax(target, 0.0))));
+    auto newton = [&](double v) {
+      const double v3 = v * v * v;
+      const double sn = v - (2.0 * v3 * v - (4.0 / 3.0) * v - target) / (8.0 * v3 - 4.0 / 3.0);
+      return sn < sC ? sC : sn;
+    };
+    if (target < 1e12) {
+      const float t = (float)target;
+      float v = fmaxf(1.0f, __builtin_amdgcn_sqrtf(__builtin_amdgcn_sqrtf(1.5f * fmaxf(t, 0.0f))));
+#pragma unroll 1
+      for (int it = 0; it < 5; ++it) {
+        const float v3 = v * v * v;
+        v -= (2.0f * v3 * v - (4.0f / 3.0f) * v - t) * __builtin_amdgcn_rcpf(8.0f * v3 - 4.0f / 3.0f);
+        v = fmaxf(v, 0.5509f);  // (the slope vanishes at s = 0.5503)
+      }
+      s = newton((double)v);
+    } else {  // beyond FP32's range, or NaN
+      s = fmax(1.0, sqrt(sqrt(1.5 * fmax(target, 0.0))));
+    }
     for (int it = 0; it < 200; ++it) {
-      const double s3 = s * s * s;
-      const double gs = 2.0 * s3 * s - (4.0 / 3.0) * s - target;
-      const double dg = 8.0 * s3 - 4.0 / 3.0;
-      double sn = s - gs / dg;
-      if (sn < sC) sn = sC;
+      const double sn = newton(s);
       if (!(sn < s)) break;  // monotone from above: stop when it no longer decreases
       s = sn;
     }
@@ -205,21 +221,30 @@ __device__ inline AxisNb wave_uniform(AxisNb a) {
   return a;
 }
 
+// Ints of LDS that one wave's contact gather needs (CONTACT_LDS per wave).
+constexpr int CONTACT_LDS = 128;
+
 // Contact force on particle i (position xs, velocity us, radius ri at the
-// start of the sub-step), gathered by the 64 lanes of one wave: the lanes
-// stride over the walls of the non-periodic axes and the (neighbour bin,
-// slot) candidates, whose positions and velocities are the binning's records
-// (so no particle sees another's update).  Contacts are compacted into the
-// new contact list (d.next_id / d.next_n) with a ballot, and every lane
-// returns the force summed over the wave in fsum.  With HERTZ the normal
-// force is Hertz's (no adhesion, gamma == 0).  With FRIC, each contact also
-// carries the friction of contact_friction (walls at rest; the spins are ws
-// for i and fr->w for the partners, a 2D disk spinning about z only): its
-// springs go beside its id into fr->next_h and the torque summed over the
-// wave is returned in tsum.  Every lane of the wave must be active.
+// start of the sub-step), gathered by the 64 lanes of one wave in two phases.
+// First the candidates: the walls of the non-periodic axes, then the records
+// of the neighbouring bins in bin order (the positions and velocities are the
+// binning's, so no particle sees another's update), 64 at a time; those that
+// overlap, or were in contact before, go into the wave's list `cand` in LDS.
+// Then the contacts, one per lane: the normal force, compacted with a ballot
+// into the new contact list (d.next_id / d.next_n); every lane returns the
+// force summed over the wave in fsum.  The work is one serial chain (FP64
+// square root, cube root, JKR's root, friction), so it is walked once for all
+// contacts rather than once per 64 candidates and once for the walls, and the
+// bin counts are read once by a lane each rather than before every batch of
+// records.  With HERTZ the normal force is Hertz's (no adhesion, gamma == 0).
+// With FRIC, each contact also carries the friction of contact_friction
+// (walls at rest; the spins are ws for i and fr->w for the partners, a 2D disk
+// spinning about z only): its springs go beside its id into fr->next_h and the
+// torque summed over the wave is returned in tsum.  Every lane of the wave
+// must be active.
 template <bool FRIC = false, bool HERTZ = false>
 __device__ inline void dem_contact_wave(const DemArgs& d, int i, int lane, const double* xs,
-                                        const double* us, double r_i, double* fsum,
+                                        const double* us, double r_i, double* fsum, int* cand,
                                         const FricArgs* fr = nullptr, const double* ws = nullptr,
                                         double* tsum = nullptr) {
   const int D = d.three_d ? 3 : 2;
@@ -240,44 +265,167 @@ __device__ inline void dem_contact_wave(const DemArgs& d, int i, int lane, const
   // the previous contact list, one entry per lane (max_contacts <= 64)
   const int pn = __builtin_amdgcn_readfirstlane(d.prev_n[i]);
   const int pid = lane < d.max_contacts ? d.prev_id[(size_t)i * d.max_contacts + lane] : 0;
-  auto was_in_contact = [&](int id) {
-    bool hit = false;
-    for (int k = 0; k < pn; ++k) hit |= __builtin_amdgcn_readlane(pid, k) == id;
-    return hit;
-  };
-  // with friction: the position of id in the previous list, or -1
+  // the position of id in the previous list, or -1
   auto prev_slot = [&](int id) {
     int at = -1;
     for (int k = 0; k < pn; ++k)
       if (__builtin_amdgcn_readlane(pid, k) == id) at = k;
     return at;
   };
-  // the springs of previous-list entry k (zero for a new contact)
-  auto load_springs = [&](int k, double h[SPRINGS]) {
-    if (k >= 0 && fr->prev_h) {
-      const double* hp = fr->prev_h + ((size_t)i * d.max_contacts + k) * SPRINGS;
-      for (int b = 0; b < SPRINGS; ++b) h[b] = hp[b];
-    } else {
-      for (int b = 0; b < SPRINGS; ++b) h[b] = 0.0;
-    }
+  // wall `face`: its distance from the centre (flat bodies at -1/2 and L-1/2)
+  auto wall_dist = [&](int face) {
+    const int a = face / 2;
+    const double xa = a == 0 ? xi0 : (a == 1 ? xi1 : xi2);
+    return (face % 2 == 0) ? xa + 0.5 : (d.L[a] - 0.5) - xa;
   };
-  // elastic normal force and delta_C, with the contact radius and x = a / a0
-  // when friction needs them
-  auto normal_force = [&](double R, double delta, double* dC, double* acon, double* xcon) {
-    if constexpr (HERTZ) {
-      *dC = 0.0;
-      *xcon = 0.0;
-      return hertz_force(R, d.E, delta, acon);
-    } else {
-      return jkr_force(R, d.E, d.gamma, delta, dC, FRIC ? acon : nullptr,
-                       FRIC ? xcon : nullptr);
-    }
+  auto separation = [&](const double* rc, double& dv0, double& dv1, double& dv2) {
+    dv0 = min_img(rc[0] - xi0, d.periodic[0], d.L[0]);
+    dv1 = min_img(rc[1] - xi1, d.periodic[1], d.L[1]);
+    dv2 = d.three_d ? min_img(rc[2] - xi2, d.periodic[2], d.L[2]) : 0.0;
+    return sqrt(dv0 * dv0 + dv1 * dv1 + dv2 * dv2);
   };
+  int ncand = 0;  // entries of cand: record indices, or -1 - face (uniform over the wave)
+  auto push = [&](bool touch, int entry) {
+    const unsigned long long m = __ballot(touch);
+    if (touch) cand[ncand + lanes_below(m)] = entry;
+    ncand += __popcll(m);
+  };
+
+  // walls
+  {
+    bool touch = false;
+    if (lane < 2 * D && !d.periodic[lane / 2])
+      touch = ri - wall_dist(lane) >= 0.0 || prev_slot(-1 - lane) >= 0;
+    push(touch, -1 - lane);
+  }
+  // the neighbour bins, one per lane (at most 27): where their candidates
+  // start in the run of all candidates, laid out bin by bin
+  const AxisNb ax = wave_uniform(axis_nb(bin_coord(xi0, 0, d), 0, d));
+  const AxisNb ay = wave_uniform(axis_nb(bin_coord(xi1, 1, d), 1, d));
+  AxisNb az;
+  az.first = 0;
+  az.cnt = 1;
+  az.nb = 1;
+  az.periodic = 0;
+  if (d.three_d) az = wave_uniform(axis_nb(bin_coord(xi2, 2, d), 2, d));
+  const int nb = ax.cnt * ay.cnt * az.cnt;
+  int bin = 0, held = 0;
+  if (lane < nb) {
+    const int kx = lane % ax.cnt, ky = (lane / ax.cnt) % ay.cnt, kz = lane / (ax.cnt * ay.cnt);
+    bin = ax.at(kx) + d.nbin[0] * (ay.at(ky) + d.nbin[1] * az.at(kz));
+    held = d.bin_count[bin];
+    if (held > d.bin_cap) held = d.bin_cap;
+  }
+  const int upto = wave_scan_incl(held);
+  const int total = __builtin_amdgcn_readlane(upto, 63);
+  const int rec0 = bin * d.bin_cap - (upto - held);  // record of candidate c of this bin: rec0 + c
+
   int* next = d.next_id + (size_t)i * d.max_contacts;
   double fs0 = 0.0, fs1 = 0.0, fs2 = 0.0;
   double tq[3] = {0.0, 0.0, 0.0};
-  double h[SPRINGS] = {};
-  auto store = [&](bool have, int id, unsigned long long m, int cnt) {
+  int cnt = 0;  // contacts found (uniform over the wave)
+  for (int base = 0;;) {
+    // phase 1: fill the list (at most 63 + 64 entries)
+    for (; base < total && ncand < 64; base += 64) {
+      const int c = base + lane;
+      // its bin: the first whose run ends past c (an inclusive scan, so the
+      // lanes' values ascend; the lanes past the last bin hold the total)
+      int lo = 0;
+#pragma unroll
+      for (int w = 16; w > 0; w >>= 1)
+        if (__shfl(upto, lo + w - 1, 64) <= c) lo += w;
+      const int at = __shfl(rec0, lo, 64) + c;
+      bool touch = false;
+      if (c < total) {
+        const double* rc = d.bin_rec + (size_t)at * 8;
+        double dv0, dv1, dv2;
+        const int j = (int)rc[7];
+        const double delta = ri + rc[6] - separation(rc, dv0, dv1, dv2);
+        touch = j != i && (delta >= 0.0 || prev_slot(j) >= 0);
+      }
+      push(touch, at);
+    }
+    if (ncand == 0) break;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // phase 2: one contact per lane
+    bool have = false;
+    int id = 0;
+    double h[SPRINGS] = {};
+    if (lane < ncand) {
+      const int at = cand[lane];
+      const bool wall = at < 0;
+      double n0, n1, n2, dist, R, rj, vrn;
+      double uj0 = 0.0, uj1 = 0.0, uj2 = 0.0;
+      if (wall) {  // 1/R = 1/r; at rest
+        id = at;
+        const int face = -1 - at, a = face / 2;
+        const double sgn = (face % 2 == 0) ? -1.0 : 1.0;  // normal towards the wall
+        n0 = a == 0 ? sgn : 0.0;
+        n1 = a == 1 ? sgn : 0.0;
+        n2 = a == 2 ? sgn : 0.0;
+        dist = wall_dist(face);
+        rj = 0.0;
+        R = ri;
+        vrn = -(ui0 * n0 + ui1 * n1 + ui2 * n2);
+      } else {
+        const double* rc = d.bin_rec + (size_t)at * 8;
+        id = (int)rc[7];
+        rj = rc[6];
+        uj0 = rc[3];
+        uj1 = rc[4];
+        uj2 = d.three_d ? rc[5] : 0.0;
+        double dv0, dv1, dv2;
+        dist = separation(rc, dv0, dv1, dv2);
+        const double inv = 1.0 / dist;
+        n0 = dv0 * inv;
+        n1 = dv1 * inv;
+        n2 = dv2 * inv;
+        R = 1.0 / (1.0 / ri + 1.0 / rj);
+        vrn = (uj0 - ui0) * n0 + (uj1 - ui1) * n1;
+        if (d.three_d) vrn += (uj2 - ui2) * n2;
+      }
+      const double delta = ri + rj - dist;
+      double dC = 0.0, acon = 0.0, xcon = 0.0, F;
+      if constexpr (HERTZ) F = hertz_force(R, d.E, delta, &acon);
+      else F = jkr_force(R, d.E, d.gamma, delta, &dC, FRIC ? &acon : nullptr, FRIC ? &xcon : nullptr);
+      if (delta >= 0.0 || delta > -dC) {
+        have = true;
+        const double fm = -F + d.eta_n * vrn;
+        fs0 += fm * n0;
+        fs1 += fm * n1;
+        fs2 += fm * n2;
+        if constexpr (FRIC) {
+          double wj0 = 0.0, wj1 = 0.0, wj2 = 0.0;
+          if (!wall) {
+            wj2 = fr->w[3 * id + 2];
+            if (d.three_d) {
+              wj0 = fr->w[3 * id];
+              wj1 = fr->w[3 * id + 1];
+            }
+          }
+          // (u_j + omega_j x (-r_j n)) - (u_i + omega_i x (r_i n))
+          const double vr0 = (uj0 - ui0) - rj * (wj1 * n2 - wj2 * n1) -
+                             ri * (wi1 * n2 - wi2 * n1);
+          const double vr1 = (uj1 - ui1) - rj * (wj2 * n0 - wj0 * n2) -
+                             ri * (wi2 * n0 - wi0 * n2);
+          const double vr2 = (uj2 - ui2) - rj * (wj0 * n1 - wj1 * n0) -
+                             ri * (wi0 * n1 - wi1 * n0);
+          const int kp = prev_slot(id);
+          if (kp >= 0 && fr->prev_h) {
+            const double* hp = fr->prev_h + ((size_t)i * d.max_contacts + kp) * SPRINGS;
+            for (int b = 0; b < SPRINGS; ++b) h[b] = hp[b];
+          }
+          double f[3] = {0.0, 0.0, 0.0};
+          contact_friction(*fr, n0, n1, n2, ri, R, vr0, vr1, vr2, wi0 - wj0, wi1 - wj1,
+                           wi2 - wj2, F, 3.0 * M_PI * d.gamma * R, acon, xcon, h, f, tq);
+          fs0 += f[0];
+          fs1 += f[1];
+          fs2 += f[2];
+        }
+      }
+    }
+    const unsigned long long m = __ballot(have);
     if (have) {
       const int pos = cnt + lanes_below(m);
       if (pos < d.max_contacts) {
@@ -288,149 +436,14 @@ __device__ inline void dem_contact_wave(const DemArgs& d, int i, int lane, const
         }
       }
     }
-  };
-  int cnt = 0;  // uniform over the wave
-
-  // walls of non-periodic axes: flat bodies at -1/2 and L-1/2 (1/R = 1/r)
-  {
-    bool have = false;
-    int id = 0;
-    if (lane < 2 * D) {
-      const int face = lane, a = face / 2;
-      if (!d.periodic[a]) {
-        const double xa = a == 0 ? xi0 : (a == 1 ? xi1 : xi2);
-        const double ua = a == 0 ? ui0 : (a == 1 ? ui1 : ui2);
-        const double dist = (face % 2 == 0) ? xa + 0.5 : (d.L[a] - 0.5) - xa;
-        const double delta = ri - dist;
-        id = -1 - face;
-        int kp = -1;
-        bool touch;
-        if constexpr (FRIC) {
-          kp = prev_slot(id);
-          touch = delta >= 0.0 || kp >= 0;
-        } else {
-          touch = delta >= 0.0 || was_in_contact(id);
-        }
-        if (touch) {
-          const double sgn = (face % 2 == 0) ? -1.0 : 1.0;  // normal towards the wall
-          const double damp = d.eta_n * (-ua * sgn);
-          double dC, acon, xcon;
-          const double F = normal_force(ri, delta, &dC, &acon, &xcon);
-          if (delta >= 0.0 || delta > -dC) {
-            const double fm = (-F + damp) * sgn;
-            if (a == 0) fs0 += fm;
-            else if (a == 1) fs1 += fm;
-            else fs2 += fm;
-            have = true;
-            if constexpr (FRIC) {
-              const double n0 = a == 0 ? sgn : 0.0, n1 = a == 1 ? sgn : 0.0,
-                           n2 = a == 2 ? sgn : 0.0;
-              // the wall is at rest: vr = -(u_i + omega_i x (r_i n))
-              const double vr0 = -(ui0 + ri * (wi1 * n2 - wi2 * n1));
-              const double vr1 = -(ui1 + ri * (wi2 * n0 - wi0 * n2));
-              const double vr2 = -(ui2 + ri * (wi0 * n1 - wi1 * n0));
-              double f[3] = {0.0, 0.0, 0.0};
-              load_springs(kp, h);
-              contact_friction(*fr, n0, n1, n2, ri, ri, vr0, vr1, vr2, wi0, wi1, wi2, F,
-                               3.0 * M_PI * d.gamma * ri, acon, xcon, h, f, tq);
-              fs0 += f[0];
-              fs1 += f[1];
-              fs2 += f[2];
-            }
-          }
-        }
-      }
-    }
-    const unsigned long long m = __ballot(have);
-    store(have, id, m, cnt);
     cnt += __popcll(m);
-  }
-
-  // particle pairs from the neighbouring bins: the lanes take the
-  // (neighbour bin, slot) candidates 64 at a time
-  const AxisNb ax = wave_uniform(axis_nb(bin_coord(xi0, 0, d), 0, d));
-  const AxisNb ay = wave_uniform(axis_nb(bin_coord(xi1, 1, d), 1, d));
-  AxisNb az;
-  az.first = 0;
-  az.cnt = 1;
-  az.nb = 1;
-  az.periodic = 0;
-  if (d.three_d) az = wave_uniform(axis_nb(bin_coord(xi2, 2, d), 2, d));
-  const int nb = ax.cnt * ay.cnt * az.cnt;
-  for (int base = 0;; base += 64) {
-    const int c = base + lane;
-    const int k = c % nb, slot = c / nb;
-    const int kx = k % ax.cnt, ky = (k / ax.cnt) % ay.cnt, kz = k / (ax.cnt * ay.cnt);
-    const int b = ax.at(kx) + d.nbin[0] * (ay.at(ky) + d.nbin[1] * az.at(kz));
-    int mcount = d.bin_count[b];
-    if (mcount > d.bin_cap) mcount = d.bin_cap;
-    const bool valid = slot < mcount;
-    if (!__any(valid)) break;
-    bool have = false;
-    int id = 0;
-    if (valid) {
-      const double* rc = d.bin_rec + ((size_t)b * d.bin_cap + slot) * 8;
-      const int j = (int)rc[7];
-      if (j != i) {
-        const double dv0 = min_img(rc[0] - xi0, d.periodic[0], d.L[0]);
-        const double dv1 = min_img(rc[1] - xi1, d.periodic[1], d.L[1]);
-        const double dv2 = d.three_d ? min_img(rc[2] - xi2, d.periodic[2], d.L[2]) : 0.0;
-        const double dist = sqrt(dv0 * dv0 + dv1 * dv1 + dv2 * dv2);
-        const double rj = rc[6];
-        const double delta = ri + rj - dist;
-        int kp = -1;
-        bool touch;
-        if constexpr (FRIC) {
-          kp = prev_slot(j);
-          touch = delta >= 0.0 || kp >= 0;
-        } else {
-          touch = delta >= 0.0 || was_in_contact(j);
-        }
-        if (touch) {
-          // normal and normal relative velocity first: only they (and the
-          // force sums) stay live across the JKR solve
-          const double inv = 1.0 / dist;
-          const double n0 = dv0 * inv, n1 = dv1 * inv, n2 = dv2 * inv;
-          double vrn = (rc[3] - ui0) * n0 + (rc[4] - ui1) * n1;
-          if (d.three_d) vrn += (rc[5] - ui2) * n2;
-          const double damp = d.eta_n * vrn;
-          const double Reff = 1.0 / (1.0 / ri + 1.0 / rj);
-          double dC, acon, xcon;
-          const double F = normal_force(Reff, delta, &dC, &acon, &xcon);
-          if (delta >= 0.0 || delta > -dC) {
-            const double fm = -F + damp;
-            fs0 += fm * n0;
-            fs1 += fm * n1;
-            fs2 += fm * n2;
-            have = true;
-            id = j;
-            if constexpr (FRIC) {
-              const double uj2 = d.three_d ? rc[5] : 0.0;
-              const double wj2 = fr->w[3 * j + 2];
-              const double wj0 = d.three_d ? fr->w[3 * j] : 0.0;
-              const double wj1 = d.three_d ? fr->w[3 * j + 1] : 0.0;
-              // (u_j + omega_j x (-r_j n)) - (u_i + omega_i x (r_i n))
-              const double vr0 = (rc[3] - ui0) - rj * (wj1 * n2 - wj2 * n1) -
-                                 ri * (wi1 * n2 - wi2 * n1);
-              const double vr1 = (rc[4] - ui1) - rj * (wj2 * n0 - wj0 * n2) -
-                                 ri * (wi2 * n0 - wi0 * n2);
-              const double vr2 = (uj2 - ui2) - rj * (wj0 * n1 - wj1 * n0) -
-                                 ri * (wi0 * n1 - wi1 * n0);
-              double f[3] = {0.0, 0.0, 0.0};
-              load_springs(kp, h);
-              contact_friction(*fr, n0, n1, n2, ri, Reff, vr0, vr1, vr2, wi0 - wj0, wi1 - wj1,
-                               wi2 - wj2, F, 3.0 * M_PI * d.gamma * Reff, acon, xcon, h, f, tq);
-              fs0 += f[0];
-              fs1 += f[1];
-              fs2 += f[2];
-            }
-          }
-        }
-      }
-    }
-    const unsigned long long m = __ballot(have);
-    store(have, id, m, cnt);
-    cnt += __popcll(m);
+    // the entries past the 64 just taken
+    const int left = ncand > 64 ? ncand - 64 : 0;
+    const int moved = lane < left ? cand[64 + lane] : 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (lane < left) cand[lane] = moved;
+    ncand = left;
   }
   fsum[0] = wave_sum(fs0);
   fsum[1] = wave_sum(fs1);

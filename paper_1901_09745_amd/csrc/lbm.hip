@@ -310,7 +310,10 @@ __global__ void __launch_bounds__(BLOCK)
         xs[k] = a.px[3 * i + k];
         us[k] = a.pu[3 * i + k];
       }
-      dem_contact_wave(a.dem, i, lane, xs, us, a.pr[i], fs);
+      // (the slot search's LDS is free here)
+      static_assert(sizeof(slot_lds) >= BLOCK / 64 * CONTACT_LDS * sizeof(int), "contact lists");
+      dem_contact_wave(a.dem, i, lane, xs, us, a.pr[i], fs,
+                       reinterpret_cast<int*>(&slot_lds) + CONTACT_LDS * (int)(threadIdx.x / 64));
       if (lane == 0)
 #pragma unroll
         for (int k = 0; k < 3; ++k) a.fc[3 * i + k] = fs[k];
