@@ -342,20 +342,6 @@ __global__ void __launch_bounds__(BLOCK)
   const unsigned N = (unsigned)a.g.N;
   const double rho0 = a.g.rho0;
   double mass_dev = 0.0;
-  // the wave's cells and all their neighbours inside the lattice (no face
-  // within one cell of the segment): every link is the plain offset, with no
-  // wrap and no wall (uniform over the wave).  Taken by the odd steps of the
-  // FP32 form and of the walled FP16 one, whose pulled loads and pushed
-  // stores otherwise resolve 2 x 18 links (the walled 384x192x192 odd step
-  // 503 -> 449 us in FP32, 496 -> 436 us in FP16); in the other forms the
-  // second copy of the loops measured neutral to 2 % slower.
-  constexpr bool INNER_PATH =
-      PAR == 1 && (PREC == PSCLBM_FP32 || (PREC == PSCLBM_FP32_FP16STORE && WALLS));
-  const bool inner = INNER_PATH &&
-                     __builtin_amdgcn_readfirstlane(
-                         (int)(x0 >= 1 && x0 + SEG <= d.nx - 1 && y >= 1 && y <= d.ny - 2 &&
-                               (D == 2 || (z >= 1 && z <= d.nz - 2)))) != 0;
-
   // ---- solid fractions of the covering particles (Table 1), whole wave; in
   // 3D after the loads of f are issued, so that their latency overlaps the
   // slot search (in 2D the registers this holds cost more than it saves) ----
@@ -381,30 +367,22 @@ __global__ void __launch_bounds__(BLOCK)
   E bscale = 1;  // B_s / eps_{n,s} of the cell (Eq. 13), formed with the weights
   if (active) {
     // ---- load f as deviations g_i = f_i - w_i rho0 ----
-    bool loaded = false;
-    if constexpr (INNER_PATH) {
-      if (inner) {  // plain offsets
+    if constexpr (PAR == 1) {
+      const CellLinks<Q, WALLS> lk(d, x, y, z);
+      if (lk.inner) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i)
-          g[i] = ST::ld(A + (size_t)L::opp(i) * N, n - link_offset<L>(d, i), i, rho0);
-        loaded = true;
-      }
-    }
-    if (!loaded) {
-#pragma unroll
-      for (int i = 0; i < Q; ++i) {
-        if constexpr (PAR == 2) {
-          g[i] = ST::ld(dir_ptr(const_cast<S*>(static_cast<const S*>(a.src)), i, N), n, i, rho0);
-        } else if constexpr (PAR == 0) {
-          g[i] = ST::template ld<NT>(dir_ptr(A, i, N), n, i, rho0);
-        } else {
-          unsigned m = n;
-          if (!link<WALLS>(d, x, y, z, -L::ex(i), -L::ey(i), -L::ez(i), n, m))
-            g[i] = ST::ld(A + (size_t)L::opp(i) * N, m, i, rho0);
-          else  // reflected at a wall during the previous (even) step
-            g[i] = ST::ld(A + (size_t)i * N, n, i, rho0);
+        for (int i = 0; i < Q; ++i) {
+          const int o = L::opp(i);  // arrives along e_i: leaves along e_o seen from here
+          g[i] = ST::ld(A + (size_t)o * N + (ptrdiff_t)lk.row_part(o), lk.lane_part(o), i, rho0);
         }
+      } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) g[i] = ST::ld(lk.at(A, N, L::opp(i)), 0u, i, rho0);
       }
+    } else {
+      S* from = PAR == 2 ? const_cast<S*>(static_cast<const S*>(a.src)) : A;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) g[i] = ST::template ld<NT>(dir_ptr(from, i, N), n, i, rho0);
     }
   }
   if constexpr (Q == 19) {
@@ -820,54 +798,48 @@ __global__ void __launch_bounds__(BLOCK)
 
   if (active) {
     // ---- stream (Eq. 1) with halfway bounce-back (Eq. 6) ----
-    // the cell index formed again from x (an empty asm keeps the compiler from
-    // reusing, and so holding or spilling, the one the loads used)
-    unsigned xo = (unsigned)x;
+    // the cell's index and links formed again from x (an empty asm keeps the
+    // compiler from reusing, and so holding or spilling, those of the loads)
+    int xo = x;
     asm volatile("" : "+v"(xo));
-    const unsigned no = xo + d.sy * (unsigned)y + d.sz * (unsigned)z;
-    double cell_dev = 0.0;  // FP64 sum of the stored deviations, in every form
-    bool stored = false;
-    if constexpr (INNER_PATH) {
-      if (inner) {  // plain offsets: every population to its neighbour
+    if constexpr (WALLS) {
+      if (a.moving_mask) {  // moving walls: -2 w_i rho (e_i . u_w) / c_s^2
+        const CellLinks<Q, true> lk(d, xo, y, z);
 #pragma unroll
-        for (int i = 0; i < Q; ++i)
-          cell_dev += ST::st(A + (size_t)i * N, no + link_offset<L>(d, i), i, g[i], rho0);
-        stored = true;
-      }
-    }
-    if (!stored) {
+        for (int i = 1; i < Q; ++i) {
+          const unsigned mw = lk.out(i) & a.moving_mask;
+          if (mw) {
+            double uw0 = 0.0, uw1 = 0.0, uw2 = 0.0;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      unsigned m = no;
-      // the even step stores into the own cell: its links matter only for a
-      // moving wall's term
-      const unsigned out =
-          (i == 0 || (PAR == 0 && !a.moving_mask))
-              ? 0u
-              : link<WALLS>(d, x, y, z, L::ex(i), L::ey(i), L::ez(i), no, m);
-      C v = g[i];
-      if (out) {
-        const unsigned mw = out & a.moving_mask;
-        if (mw) {  // moving wall: -2 w_i rho (e_i . u_w) / c_s^2
-          double uw0 = 0.0, uw1 = 0.0, uw2 = 0.0;
-#pragma unroll
-          for (int f = 0; f < 6; ++f)
-            if ((mw >> f) & 1u) {
-              uw0 += a.g.face_u[f][0];
-              uw1 += a.g.face_u[f][1];
-              uw2 += a.g.face_u[f][2];
-            }
-          const double eu = edot(L::ex(i), L::ey(i), L::ez(i), uw0, uw1, uw2);
-          v -= (C)(6.0 * (SC ? 1.0 : L::w(i)) * eu) * rho;
+            for (int f = 0; f < 6; ++f)
+              if ((mw >> f) & 1u) {
+                uw0 += a.g.face_u[f][0];
+                uw1 += a.g.face_u[f][1];
+                uw2 += a.g.face_u[f][2];
+              }
+            const double eu = edot(L::ex(i), L::ey(i), L::ez(i), uw0, uw1, uw2);
+            g[i] -= (C)(6.0 * (SC ? 1.0 : L::w(i)) * eu) * rho;
+          }
         }
       }
-      if (PAR == 0)  // own cell, opposite slot
-        cell_dev += ST::template st<NT>(dir_ptr(A, L::opp(i), N), no, i, v, rho0);
-      else if (out)  // reflected into the own cell's opposite slot
-        cell_dev += ST::st(A + (size_t)L::opp(i) * N, no, i, v, rho0);
-      else                  // neighbour cell, same slot
-        cell_dev += ST::st(A + (size_t)i * N, m, i, v, rho0);
     }
+    double cell_dev = 0.0;  // FP64 sum of the stored deviations, in every form
+    if constexpr (PAR == 0) {  // own cell, opposite slot
+      const unsigned no = (unsigned)xo + d.sy * (unsigned)y + d.sz * (unsigned)z;
+#pragma unroll
+      for (int i = 0; i < Q; ++i)
+        cell_dev += ST::template st<NT>(dir_ptr(A, L::opp(i), N), no, i, g[i], rho0);
+    } else {
+      const CellLinks<Q, WALLS> lk(d, xo, y, z);
+      if (lk.inner) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+          cell_dev += ST::st(A + (size_t)i * N + (ptrdiff_t)lk.row_part(i), lk.lane_part(i), i,
+                             g[i], rho0);
+      } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) cell_dev += ST::st(lk.at(A, N, i), 0u, i, g[i], rho0);
+      }
     }
     mass_dev = cell_dev;
   }

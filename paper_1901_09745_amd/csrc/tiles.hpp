@@ -365,16 +365,76 @@ __device__ __forceinline__ Dims dims_of(const Geom& g) {
   return d;
 }
 
+// The links of one cell: its neighbours through the periodic wrap, and the
+// non-periodic faces it lies at.  y and z are uniform over the wave, so a
+// link's y and z part is a scalar that goes into the base pointer, and its x
+// part is one of three lane offsets: no arithmetic per link.  Only in a wave
+// with a cell at a wall do the lanes choose an address each (`at`); that path
+// is taken by the waves along the faces alone.  Resolving each link through
+// the faces by itself, with a branch around each load, cost the odd steps
+// 100-260 VALU and 50-510 SALU instructions a wave (384x192x192 with walls,
+// FP64: 890 us against 822 for the even step; the 10x51x51 FP32 duct 10.8
+// against 6.2 us).
+template <int Q, bool WALLS>
+struct CellLinks {
+  using L = Lattice<Q>;
+  unsigned n, xm, xp;  // the cell and its x neighbours
+  int ym, yp, zm, zp;  // offsets to its y and z neighbours (uniform)
+  unsigned wall;       // bit f: the cell lies at the non-periodic face f
+  bool inner;          // no cell of the wave lies at one (uniform)
+
+  __device__ __forceinline__ CellLinks(const Dims& d, int x, int y, int z) {
+    n = (unsigned)x + d.sy * (unsigned)y + d.sz * (unsigned)z;
+    xm = x == 0 ? n + (unsigned)(d.nx - 1) : n - 1u;
+    xp = x == d.nx - 1 ? n - (unsigned)(d.nx - 1) : n + 1u;
+    ym = y == 0 ? (d.ny - 1) * (int)d.sy : -(int)d.sy;
+    yp = y == d.ny - 1 ? -(d.ny - 1) * (int)d.sy : (int)d.sy;
+    zm = zp = 0;
+    if constexpr (L::D == 3) {
+      zm = z == 0 ? (int)(d.sz * (unsigned)(d.nz - 1)) : -(int)d.sz;
+      zp = z == d.nz - 1 ? -(int)(d.sz * (unsigned)(d.nz - 1)) : (int)d.sz;
+    }
+    wall = 0;
+    inner = true;
+    if constexpr (WALLS) {
+      if (!d.px) wall |= (x == 0 ? 1u : 0u) | (x == d.nx - 1 ? 2u : 0u);
+      if (!d.py) wall |= (y == 0 ? 4u : 0u) | (y == d.ny - 1 ? 8u : 0u);
+      if (L::D == 3 && !d.pz) wall |= (z == 0 ? 16u : 0u) | (z == d.nz - 1 ? 32u : 0u);
+      inner = __ballot(wall != 0) == 0;
+    }
+  }
+  // the faces a link along e_i crosses when it leaves the lattice
+  __device__ static constexpr unsigned faces(int i) {
+    return (L::ex(i) < 0 ? 1u : 0u) | (L::ex(i) > 0 ? 2u : 0u) | (L::ey(i) < 0 ? 4u : 0u) |
+           (L::ey(i) > 0 ? 8u : 0u) | (L::ez(i) < 0 ? 16u : 0u) | (L::ez(i) > 0 ? 32u : 0u);
+  }
+  // the non-periodic faces the cell's link along e_i leaves through
+  __device__ __forceinline__ unsigned out(int i) const { return wall & faces(i); }
+  __device__ __forceinline__ unsigned lane_part(int i) const {
+    return L::ex(i) > 0 ? xp : (L::ex(i) < 0 ? xm : n);
+  }
+  __device__ __forceinline__ int row_part(int i) const {
+    return (L::ey(i) > 0 ? yp : (L::ey(i) < 0 ? ym : 0)) +
+           (L::ez(i) > 0 ? zp : (L::ez(i) < 0 ? zm : 0));
+  }
+  // Where the population that leaves along e_i goes (N cells per direction
+  // array): array i of the neighbour, or, when the link leaves through a
+  // non-periodic face, the cell's own slot of the opposite direction.  The
+  // odd step reads what arrives along e_o from the same place, i = opp(o).
+  template <typename S>
+  __device__ __forceinline__ S* at(S* A, unsigned N, int i) const {
+    S* in = A + (size_t)i * N + (ptrdiff_t)row_part(i) + lane_part(i);
+    if constexpr (WALLS) {
+      if (out(i)) in = A + (size_t)L::opp(i) * N + n;
+    }
+    return in;
+  }
+};
+
 // The link from cell (x, y, z) along (dx, dy, dz): sets the neighbour's cell
 // offset m (periodic wrap applied) and returns the mask of non-periodic faces
 // the link leaves through (bit f for face f; 0 when the neighbour exists).
 // WALLS == false: every axis is periodic and no link ever leaves.
-// Offset of the neighbour e_i of a cell far from every face (no wrap, no wall).
-template <typename L>
-__device__ __forceinline__ unsigned link_offset(const Dims& d, int i) {
-  return (unsigned)(L::ex(i) + L::ey(i) * (int)d.sy + L::ez(i) * (int)d.sz);
-}
-
 template <bool WALLS>
 __device__ __forceinline__ unsigned link(const Dims& d, int x, int y, int z, int dx, int dy,
                                          int dz, unsigned n, unsigned& m) {
@@ -551,7 +611,7 @@ __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSn
 // DEM bin of a position along axis a (uniform bins of width bin_size).
 __device__ inline int dem_bin_coord(double x, int L, int periodic, int nbin, double bin_size) {
   double v = x;
-  if (periodic) {
+  if (periodic && !(x >= 0.0 && x < (double)L)) {  // (fmod is a long loop: only when it acts)
     v = fmod(v, (double)L);
     if (v < 0) v += L;
   }
