@@ -97,37 +97,91 @@ int tile_width(int nx, int nz) {
   return best;
 }
 
+double distribution_bytes(const psclbm_config* c) {
+  return (double)c->nx * c->ny * c->nz * c->lattice * storage_bytes(c->precision);
+}
+
 // Even steps read and write every cell's own slots, each line by one wave
 // only, and stream them with non-temporal hints when the distributions are
 // larger than the 256 MB last-level cache (which they would otherwise sweep
-// out).  PSCLBM_NT=0/1 overrides, for measurements.
-int nt_even(const psclbm_config* c) {
+// out).  Not in the FP16 form's flat tiles, where a wave's 128 bytes straddle
+// lines it shares with its neighbours (250x200x200: 169 us without the hints,
+// 187 with; FP32 300 / 298, FP64 592 / 563).  PSCLBM_NT=0/1 overrides, for
+// measurements.
+int nt_even(const psclbm_config* c, bool flat) {
   if (const char* e = std::getenv("PSCLBM_NT")) return std::atoi(e) ? 1 : 0;
-  const double bytes = (double)c->nx * c->ny * c->nz * c->lattice * storage_bytes(c->precision);
-  return bytes > 256.0 * 1024 * 1024 ? 1 : 0;
+  if (flat && c->precision == PSCLBM_FP32_FP16STORE) return 0;
+  return distribution_bytes(c) > 256.0 * 1024 * 1024 ? 1 : 0;
+}
+
+// Flat tiles (256 consecutive cells of a plane) instead of row tiles, which
+// leave lanes of each row's last 64-cell segment without a cell (a wave that
+// costs as many instructions and as much latency as a full one) and, in rows
+// that are no multiple of a cache line, split the lines between neighbouring
+// workgroups at every segment.
+//   3D: wherever nx is no multiple of 64.  A step takes, row -> flat tiles
+//   (with particles): 80^3 FP64 44 -> 35 us; 300x180x190 FP32 404-466 -> 315;
+//   300x180x190 FP16 288-355 -> 251; 250x200x200 FP64 659 -> 560; rows of 120
+//   (94 % full) FP32 23.8 -> 22.2.  Full rows are the better ones as row tiles
+//   (the flat kernel's y varies over the wave, 5 % of the instructions).
+//   2D: only rows of 64 or more that are less than 85 % full (70: 1.06-1.12
+//   times faster, 200: 1.02-1.09); fuller ones gain nothing, and with particles
+//   rows of 40-50 lose 10 % (each row of a wave is searched by itself).
+//   Not with an outlet on an x face unless other outlet faces need their
+//   velocities read before the step anyway: a flat wave cannot take them from
+//   its own lanes, and that launch costs 5 us.
+//   Not with lists longer than 160: a flat tile's is half as long again, in LDS.
+bool flat_tiles(const psclbm_config* c) {
+  if (c->nx % SEG == 0) return false;
+  if (c->max_particles > 0 && c->max_tile_particles > 160) return false;
+  if (c->lattice == 9 && (c->nx < SEG || c->nx >= 0.85 * ((c->nx + SEG - 1) / SEG * SEG)))
+    return false;
+  bool x_outlet = false, other = false;
+  for (int f = 0; f < (c->lattice == 9 ? 4 : 6); ++f)
+    if (c->face_bc[f] == PSCLBM_OUTLET_EQ) (f < 2 ? x_outlet : other) = true;
+  return !x_outlet || other;
+}
+
+// Tiles dealt to the XCDs in contiguous runs, so that the lines neighbouring
+// tiles share stay in one L2: for the 64-wide row tiles, whose x neighbours
+// share them, and wherever the distributions fit the 256 MB last-level cache
+// (128x64x64 FP32 17.9 -> 15.2 us, FP64 30.8 -> 26.4; 150^3 FP32 flat 95 -> 87);
+// larger lattices stream faster as dispatched (256^3 FP32 467 against 496 us,
+// 384x192x192 FP32 399 against 422, 200x160x160 FP64 flat 280 against 300).
+int xcd_runs(const psclbm_config* c, bool flat, int twx) {
+  if (!flat && twx == SEG) return 1;
+  return distribution_bytes(c) <= 256.0 * 1024 * 1024 ? 1 : 0;
 }
 
 struct Layout {
   size_t f, err, scalar, tile_count, tile_list, snap, facc0, facc1, mass_part, outlet_u, outlet_g;
   size_t bin_count, bin_rec, cn0, cn1, cid0, cid1, fcont, spr0, spr1, ws0, ws1, total;
-  int ntx, nty, ntz, ntiles, twx, twy;
+  int ntx, nty, ntz, ntiles, twx, twy, flat, list_cap;
   long long face_stride;
   int nbin[3];
   double bin_size[3];
   int bin_cap;
 };
 
-Layout plan(const psclbm_config* c) {
+Layout plan(const psclbm_config* c, bool may_be_flat = true) {
   Layout l;
   const long long N = (long long)c->nx * c->ny * c->nz;
   l.twx = tile_width(c->nx, c->nz);
   l.twy = BLOCK / l.twx;
+  l.flat = may_be_flat && flat_tiles(c) ? 1 : 0;
   l.ntx = (c->nx + l.twx - 1) / l.twx;
   l.nty = (c->ny + l.twy - 1) / l.twy;
+  if (l.flat) {
+    l.ntx = (int)(((long long)c->nx * c->ny + BLOCK - 1) / BLOCK);
+    l.nty = 1;
+  }
   l.ntz = c->nz;
   l.ntiles = l.ntx * l.nty * l.ntz;
   const int np = c->max_particles;
-  const int cap = np > 0 ? c->max_tile_particles : 1;
+  // (a flat tile's cells lie in two or three of the row tiles: its list is
+  // given half as much again)
+  l.list_cap = l.flat ? c->max_tile_particles + c->max_tile_particles / 2 : c->max_tile_particles;
+  const int cap = np > 0 ? l.list_cap : 1;
   bool outlet = false;
   for (int f = 0; f < 6; ++f) outlet |= c->face_bc[f] == PSCLBM_OUTLET_EQ;
   long long fs = (long long)c->ny * c->nz;
@@ -200,10 +254,11 @@ void fill_geom(const psclbm_config* cfg, const Layout& l, Geom& g) {
   g.ntx = l.ntx;
   g.nty = l.nty;
   g.ntz = l.ntz;
+  g.flat = l.flat;
   g.twx = l.twx;
   g.twy = l.twy;
-  g.remap = l.twx == SEG ? 1 : 0;
-  g.nt_even = nt_even(cfg);
+  g.remap = xcd_runs(cfg, l.flat != 0, l.twx);
+  g.nt_even = nt_even(cfg, l.flat != 0);
   g.rho0 = cfg->rho0;
 }
 
@@ -298,6 +353,7 @@ int lbm_init(const psclbm_config* cfg, void* d_workspace, size_t bytes, void* hi
   c->tile_count = c->tile_count_buf[0];
   c->tile_list = reinterpret_cast<int*>(base + l.tile_list);
   c->ntiles = l.ntiles;
+  c->list_cap = l.list_cap;
   c->snap = reinterpret_cast<PSnap*>(base + l.snap);
   c->facc[0] = reinterpret_cast<double*>(base + l.facc0);
   c->facc[1] = reinterpret_cast<double*>(base + l.facc1);
@@ -566,14 +622,14 @@ int psc_solid_fraction_noalloc(const psclbm_config* cfg, const psclbm_particles*
   if (cfg->max_particles < 1 || p->n < 0 || p->n > cfg->max_particles) return PSCLBM_EINVAL;
   if (p->n > 0 && (!p->x || !p->u || !p->omega || !p->radius)) return PSCLBM_EINVAL;
   if (kslots > 0 && (!d_slot_id || !d_slot_eps)) return PSCLBM_EINVAL;
-  const Layout l = plan(cfg);
+  const Layout l = plan(cfg, false);
   const int np = p->n > 0 ? p->n : 1;
   // the scratch layout: error word, two sets of tile counts, tile lists,
   // snapshot, one block of force rows (cleared by the rasterisation)
   const size_t o_err = 0;
   const size_t o_cnt = align_up(sizeof(unsigned));
   const size_t o_list = o_cnt + align_up(sizeof(int) * 2 * (size_t)l.ntiles);
-  const size_t o_snap = o_list + align_up(sizeof(int) * (size_t)l.ntiles * cfg->max_tile_particles);
+  const size_t o_snap = o_list + align_up(sizeof(int) * (size_t)l.ntiles * l.list_cap);
   const size_t o_facc = o_snap + align_up(sizeof(PSnap) * (size_t)np);
   const size_t need = o_facc + align_up(sizeof(double) * 6 * (size_t)np);
   if (need > NOALLOC_BYTES) return PSCLBM_EINVAL;
@@ -593,6 +649,7 @@ int psc_solid_fraction_noalloc(const psclbm_config* cfg, const psclbm_particles*
   c.tile_count = c.tile_count_buf[0];
   c.tile_list = reinterpret_cast<int*>(base + o_list);
   c.ntiles = l.ntiles;
+  c.list_cap = l.list_cap;
   c.snap = reinterpret_cast<PSnap*>(base + o_snap);
   c.facc[0] = c.facc[1] = reinterpret_cast<double*>(base + o_facc);
   // the array keeps the last call's contents: clear the error word and the

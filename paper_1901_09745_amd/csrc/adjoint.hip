@@ -73,7 +73,7 @@ __device__ __forceinline__ double feq_i(int i, double rho, double ux, double uy,
   return rho * L::w(i) * (1.0 + 3.0 * eu + 4.5 * eu * eu - 1.5 * uu);
 }
 
-template <int Q, bool WALLS>
+template <int Q, bool WALLS, bool FLAT>
 __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
   using L = Lattice<Q>;
   constexpr int D = L::D;
@@ -89,16 +89,16 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
     for (int k = threadIdx.x; k < 9 * cnt; k += BLOCK) acc[k] = 0.0;
     __syncthreads();
   }
-  // the wave's 64-cell row segment; y and z are uniform over the wave (scalar)
-  int x0, y, z;
-  wave_segment(G, tile, x0, y, z);
-  const int x = x0 + (int)(threadIdx.x & 63);
-  const bool active = x < G.nx && y < G.ny && z < G.nz;
+  // the wave's cells; z, and y unless FLAT, are uniform over the wave (scalar)
+  const WaveCells<FLAT> wc = wave_cells<FLAT>(G, tile);
+  const LaneCell cell = lane_cell<FLAT>(G, wc);
+  const int x = cell.x, y = cell.y, z = wc.z;
+  const bool active = (int)(threadIdx.x & 63) <= wc.last;
   const unsigned N = (unsigned)G.N;
   const unsigned n = (unsigned)x + (unsigned)G.nx * ((unsigned)y + (unsigned)G.ny * (unsigned)z);
   Slots s;
   s.n = 0;
-  if (cnt > 0) collect_slots<D>(G, x0, y, z, active, lds, cnt, a.h, s, nullptr, slot_lds);
+  if (cnt > 0) collect_slots<D, FLAT>(G, wc, active, lds, cnt, a.h, s, nullptr, slot_lds);
 
   if (active) {
     Dims d;
@@ -565,7 +565,7 @@ __global__ void k_outlet_adjoint(Geom g, int face, const double* f, const double
 
 // Table 1 chain alone: dJ/dX_s += sum_n dJ/deps_{n,s} r/|r| on the linear band,
 // for sensitivities given per recorded slot (the order of psc_get_solid_fraction).
-template <int D>
+template <int D, bool FLAT>
 __global__ void __launch_bounds__(BLOCK) k_rasterize_adjoint(Geom g, double h, int np, int cap,
                                                            const int* tile_count,
                                                            const int* tile_list,
@@ -576,14 +576,13 @@ __global__ void __launch_bounds__(BLOCK) k_rasterize_adjoint(Geom g, double h, i
   LdsEntry* lds = reinterpret_cast<LdsEntry*>(smem_d);
   const int tile = blockIdx.x;
   const int cnt = load_tile_list(tile_count, tile_list, cap, snap, tile, lds, nullptr, np);
-  // the wave's 64-cell row segment; y and z are uniform over the wave (scalar)
-  int x0, y, z;
-  wave_segment(g, tile, x0, y, z);
-  const int x = x0 + (int)(threadIdx.x & 63);
-  const bool active = x < g.nx && y < g.ny && z < g.nz;
+  const WaveCells<FLAT> wc = wave_cells<FLAT>(g, tile);
+  const LaneCell cell = lane_cell<FLAT>(g, wc);
+  const int x = cell.x, y = cell.y, z = wc.z;
+  const bool active = (int)(threadIdx.x & 63) <= wc.last;
   Slots s;
   s.n = 0;
-  if (cnt > 0) collect_slots<D>(g, x0, y, z, active, lds, cnt, h, s, nullptr, slot_lds);
+  if (cnt > 0) collect_slots<D, FLAT>(g, wc, active, lds, cnt, h, s, nullptr, slot_lds);
   if (!active) return;
   const long long n = x + (long long)g.nx * (y + (long long)g.ny * z);
 #pragma unroll
@@ -605,6 +604,17 @@ __global__ void __launch_bounds__(BLOCK) k_rasterize_adjoint(Geom g, double h, i
   }
 }
 
+template <int Q>
+static void launch_step_adjoint(psclbm_ctx* c, const AdjArgs& a, bool walls, size_t lds) {
+  if (c->geom.flat) {
+    if (walls) k_adjoint<Q, true, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+    else k_adjoint<Q, false, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+  } else {
+    if (walls) k_adjoint<Q, true, false><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+    else k_adjoint<Q, false, false><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+  }
+}
+
 int launch_adjoint(psclbm_ctx* c, const double* f, const double* lam_in, double* lam_out,
                    const double* gF, const double* gT, double* gX, double* gU, double* gW,
                    double* gface) {
@@ -615,7 +625,7 @@ int launch_adjoint(psclbm_ctx* c, const double* f, const double* lam_in, double*
   for (int k = 0; k < 3; ++k) a.force[k] = c->cfg.body_force[k];
   a.h = c->cfg.shell_h;
   a.np = c->np;
-  a.cap = c->cfg.max_tile_particles;
+  a.cap = c->list_cap;
   a.tile_count = c->tile_count;
   a.tile_list = c->tile_list;
   a.snap = c->snap;
@@ -647,16 +657,11 @@ int launch_adjoint(psclbm_ctx* c, const double* f, const double* lam_in, double*
                                                           c->outlet_u, c->face_stride);
   }
   const size_t lds = c->np > 0 ? (sizeof(LdsEntry) + 9 * sizeof(double)) *
-                                     (size_t)c->cfg.max_tile_particles
+                                     (size_t)c->list_cap
                                : 0;
   const bool walls = !(c->geom.periodic[0] && c->geom.periodic[1] && c->geom.periodic[2]);
-  if (c->geom.q == 9) {
-    if (walls) k_adjoint<9, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
-    else k_adjoint<9, false><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
-  } else {
-    if (walls) k_adjoint<19, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
-    else k_adjoint<19, false><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
-  }
+  if (c->geom.q == 9) launch_step_adjoint<9>(c, a, walls, lds);
+  else launch_step_adjoint<19>(c, a, walls, lds);
   int rc = hip_ok(hipGetLastError());
   if (rc) return rc;
   for (int fc = 0; fc < 6; ++fc) {
@@ -671,17 +676,21 @@ int launch_adjoint(psclbm_ctx* c, const double* f, const double* lam_in, double*
   return hip_ok(hipGetLastError());
 }
 
-int launch_rasterize_adjoint(psclbm_ctx* c, const double* gs, int kslots, double* gX) {
-  const size_t lds = (sizeof(LdsEntry) + sizeof(double)) * (size_t)c->cfg.max_tile_particles;
-  if (c->geom.q == 9)
-    k_rasterize_adjoint<2><<<c->ntiles, BLOCK, lds, c->stream>>>(
-        c->geom, c->cfg.shell_h, c->np, c->cfg.max_tile_particles, c->tile_count, c->tile_list,
-        c->snap, gs, kslots, gX);
-  else
-    k_rasterize_adjoint<3><<<c->ntiles, BLOCK, lds, c->stream>>>(
-        c->geom, c->cfg.shell_h, c->np, c->cfg.max_tile_particles, c->tile_count, c->tile_list,
-        c->snap, gs, kslots, gX);
+template <int D, bool FLAT>
+static int rasterize_adjoint(psclbm_ctx* c, const double* gs, int kslots, double* gX) {
+  const size_t lds = (sizeof(LdsEntry) + sizeof(double)) * (size_t)c->list_cap;
+  k_rasterize_adjoint<D, FLAT><<<c->ntiles, BLOCK, lds, c->stream>>>(
+      c->geom, c->cfg.shell_h, c->np, c->list_cap, c->tile_count, c->tile_list, c->snap, gs,
+      kslots, gX);
   return hip_ok(hipGetLastError());
+}
+
+int launch_rasterize_adjoint(psclbm_ctx* c, const double* gs, int kslots, double* gX) {
+  if (c->geom.q == 9)
+    return c->geom.flat ? rasterize_adjoint<2, true>(c, gs, kslots, gX)
+                        : rasterize_adjoint<2, false>(c, gs, kslots, gX);
+  return c->geom.flat ? rasterize_adjoint<3, true>(c, gs, kslots, gX)
+                      : rasterize_adjoint<3, false>(c, gs, kslots, gX);
 }
 
 }  // namespace psclbm

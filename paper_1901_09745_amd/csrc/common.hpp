@@ -79,9 +79,12 @@ struct Form<PSCLBM_FP32_FP16STORE> {
   using C = float;
 };
 
-// Workgroup tile: 256 cells, twx along x by twy = 256 / twx rows along y (twx
-// 64, 128 or 256, chosen per lattice), worked by four waves; each wave takes
-// one 64-cell segment of one row.
+// Workgroup tile: 256 cells of one z-plane, worked by four waves.  Row tiles are
+// twx cells along x by twy = 256 / twx rows along y (twx 64, 128 or 256, chosen
+// per lattice), each wave taking one 64-cell segment of one row.  Flat tiles are
+// 256 consecutive cells of the plane (x fastest), each wave taking 64 of them,
+// which may lie in several rows: for lattices whose rows would leave many
+// lanes of their last segment without a cell.
 constexpr int SEG = 64;
 constexpr int BLOCK = 256;
 constexpr int KSLOTS = 4;  // particles a single cell can be covered by
@@ -109,7 +112,8 @@ struct Geom {
   int face[6];
   int periodic[3];
   int ntx, nty, ntz;
-  int twx, twy;  // tile extent along x and y (twx * twy == BLOCK)
+  int flat;      // flat tiles: ntx of them a plane, nty == 1
+  int twx, twy;  // row tiles: tile extent along x and y (twx * twy == BLOCK)
   int remap;     // deal the tiles to the XCDs in contiguous runs
   int nt_even;   // even steps stream the lattice with non-temporal loads and stores
   double face_u[6][3];
@@ -188,6 +192,7 @@ struct StepArgs {
 // the first lane of a segment.
 inline unsigned outlet_wave_mask(const Geom& g, unsigned outlet_mask) {
   unsigned m = 0;
+  if (g.flat) return 0;  // a flat wave may start at x = nx-1 or end at x = 0
   if ((outlet_mask & 1u) && g.nx >= 2) m |= 1u;
   if ((outlet_mask & 2u) && g.nx >= 2 && (g.nx - 1) % SEG != 0) m |= 2u;
   return m;
@@ -206,6 +211,7 @@ struct psclbm_ctx {
   int* tile_count_buf[2];    // double-buffered: each rasterisation clears the other
   int tile_cur;
   int* tile_list;
+  int list_cap;  // entries each tile's list can hold
   int ntiles;
   psclbm::PSnap* snap;
   double* facc[2];

@@ -327,7 +327,7 @@ static NextOut next_out(psclbm_ctx* c, bool build, bool bins, double* wnext) {
   nx.tstale = c->tile_count_buf[c->tile_cur];
   nx.ntiles = c->ntiles;
   nx.tile_list = c->tile_list;
-  nx.cap = c->cfg.max_tile_particles;
+  nx.cap = c->list_cap;
   nx.db = dem_bin_out(c, bins);
   nx.wnext = wnext;
   nx.err = c->err;

@@ -181,29 +181,6 @@ __device__ __forceinline__ S* dir_ptr(S* A, int i, unsigned N) {
   asm("" : "+s"(p));
   return p;
 }
-// Element `e` of a per-direction array through a 32-bit byte offset, in the
-// global address space, so the access is the scalar base plus one 32-bit
-// vector offset.
-template <typename S>
-using GlobalT = __attribute__((address_space(1))) S;
-template <typename S>
-__device__ __forceinline__ GlobalT<S>& elem(S* base, unsigned e) {
-  auto* gb = (__attribute__((address_space(1))) char*)base;
-  return *(GlobalT<S>*)(gb + (e * (unsigned)sizeof(S)));
-}
-// The same element read or written with a non-temporal hint when NT: the
-// line is streamed through the caches rather than kept in them.
-template <bool NT, typename S>
-__device__ __forceinline__ S elem_ld(S* base, unsigned e) {
-  if constexpr (NT) return __builtin_nontemporal_load(&elem(base, e));
-  else return elem(base, e);
-}
-template <bool NT, typename S>
-__device__ __forceinline__ void elem_st(S* base, unsigned e, S v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, &elem(base, e));
-  else elem(base, e) = v;
-}
-
 template <int PREC, int Q>
 struct Store {
   using S = typename Form<PREC>::S;
@@ -283,7 +260,7 @@ constexpr int step_waves() {
 
 // NT (even steps only): the lattice is streamed with non-temporal loads and
 // stores, each line being read and written by one wave.
-template <int Q, int PREC, int PAR, bool WALLS, bool NT = false>
+template <int Q, int PREC, int PAR, bool WALLS, bool FLAT, bool NT = false>
 __global__ void __launch_bounds__(BLOCK)
     __attribute__((amdgpu_waves_per_eu(step_waves<Q, PREC, WALLS>())))
     k_step(const StepArgs a) {
@@ -328,16 +305,17 @@ __global__ void __launch_bounds__(BLOCK)
   const int tile = tile_of(a.g, bid, nb);
 
   // particle list of the tile (LDS) and its force accumulators
-  LdsEntry* lds = reinterpret_cast<LdsEntry*>(smem_d);
+  using Entry = LdsEntryT<E>;
+  Entry* lds = reinterpret_cast<Entry*>(smem_d);
   double* acc = reinterpret_cast<double*>(lds + a.cap);
   const int cnt = load_tile_list(a.tile_count, a.tile_list, a.cap, a.snap, tile, lds, acc, a.np);
 
   const Dims d = dims_of(a.g);
-  // the wave's 64-cell row segment; y and z are uniform over the wave (scalar)
-  int x0, y, z;
-  wave_segment(a.g, tile, x0, y, z);
-  const int x = x0 + (int)(threadIdx.x & 63);
-  const bool active = x < d.nx && y < d.ny && z < d.nz;
+  // the wave's cells; z, and y unless FLAT, are uniform over the wave (scalar)
+  const WaveCells<FLAT> wc = wave_cells<FLAT>(a.g, tile);
+  const LaneCell cell = lane_cell<FLAT>(a.g, wc);
+  const int x = cell.x, y = cell.y, z = wc.z;
+  const bool active = (int)(threadIdx.x & 63) <= wc.last;
   const unsigned n = (unsigned)x + d.sy * (unsigned)y + d.sz * (unsigned)z;
   const unsigned N = (unsigned)a.g.N;
   const double rho0 = a.g.rho0;
@@ -348,7 +326,7 @@ __global__ void __launch_bounds__(BLOCK)
   SlotsT<E> s;
   s.n = 0;
   if constexpr (Q == 9) {
-    if (cnt > 0) collect_slots<D>(a.g, x0, y, z, active, lds, cnt, a.h, s, a.err, slot_lds);
+    if (cnt > 0) collect_slots<D, FLAT>(a.g, wc, active, lds, cnt, a.h, s, a.err, slot_lds);
   }
 
   C g[Q];
@@ -368,7 +346,7 @@ __global__ void __launch_bounds__(BLOCK)
   if (active) {
     // ---- load f as deviations g_i = f_i - w_i rho0 ----
     if constexpr (PAR == 1) {
-      const CellLinks<Q, WALLS> lk(d, x, y, z);
+      const CellLinks<Q, WALLS, FLAT> lk(d, x, y, z);
       if (lk.inner) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
@@ -386,7 +364,7 @@ __global__ void __launch_bounds__(BLOCK)
     }
   }
   if constexpr (Q == 19) {
-    if (cnt > 0) collect_slots<D>(a.g, x0, y, z, active, lds, cnt, a.h, s, a.err, slot_lds);
+    if (cnt > 0) collect_slots<D, FLAT>(a.g, wc, active, lds, cnt, a.h, s, a.err, slot_lds);
   }
   // the slots' list entries, two to a register (entries < 2^16; the list
   // capacity is at most 512): registers held through the collision
@@ -402,7 +380,7 @@ __global__ void __launch_bounds__(BLOCK)
   // use: an empty asm makes each use opaque, so the compiler does not hold
   // (or spill) one converted copy across the slots
   auto row_coord = [](int v) {
-    asm volatile("" : "+s"(v));
+    if constexpr (!FLAT) asm volatile("" : "+s"(v));
     return (double)v;
   };
   constexpr int NV = D == 3 ? 6 : 3;
@@ -417,7 +395,7 @@ __global__ void __launch_bounds__(BLOCK)
     SlotKin t;
     t.Bs = a.original ? (C)(s.eps[k] * tm / ((1.0 - s.eps[k]) + tm)) : (C)(s.eps[k] * bscale);
     t.Bm = a.original ? Bn_cell : t.Bs;
-    const LdsEntry& P = lds[slot_e(k)];
+    const Entry& P = lds[slot_e(k)];
     // u_s = U + Omega x r in the arithmetic precision: the arm from its FP64
     // nearest image, or in the FP32 forms from the centre's FP32 pair
     C cx, cy, cz;
@@ -801,10 +779,10 @@ __global__ void __launch_bounds__(BLOCK)
     // the cell's index and links formed again from x (an empty asm keeps the
     // compiler from reusing, and so holding or spilling, those of the loads)
     int xo = x;
-    asm volatile("" : "+v"(xo));
+    asm volatile("" : "+v"(xo));  // (FLAT: y stays held)
     if constexpr (WALLS) {
       if (a.moving_mask) {  // moving walls: -2 w_i rho (e_i . u_w) / c_s^2
-        const CellLinks<Q, true> lk(d, xo, y, z);
+        const CellLinks<Q, true, FLAT> lk(d, xo, y, z);
 #pragma unroll
         for (int i = 1; i < Q; ++i) {
           const unsigned mw = lk.out(i) & a.moving_mask;
@@ -830,7 +808,7 @@ __global__ void __launch_bounds__(BLOCK)
       for (int i = 0; i < Q; ++i)
         cell_dev += ST::template st<NT>(dir_ptr(A, L::opp(i), N), no, i, g[i], rho0);
     } else {
-      const CellLinks<Q, WALLS> lk(d, xo, y, z);
+      const CellLinks<Q, WALLS, FLAT> lk(d, xo, y, z);
       if (lk.inner) {
 #pragma unroll
         for (int i = 0; i < Q; ++i)
@@ -1116,7 +1094,7 @@ __global__ void __launch_bounds__(256) k_rasterize(Geom g, int n, int three_d, d
   bin_tiles(g, three_d, h, P, s, lane, count, tile_list, cap, err);
 }
 
-template <int D>
+template <int D, bool FLAT>
 __global__ void __launch_bounds__(BLOCK) k_solid_fraction(Geom g, double h, int np, int cap,
                                                         const int* tile_count, const int* tile_list,
                                                         const PSnap* snap, double* eps_total,
@@ -1127,14 +1105,13 @@ __global__ void __launch_bounds__(BLOCK) k_solid_fraction(Geom g, double h, int 
   LdsEntry* lds = reinterpret_cast<LdsEntry*>(smem_d);
   const int tile = blockIdx.x;
   const int cnt = load_tile_list(tile_count, tile_list, cap, snap, tile, lds, nullptr, np);
-  int x0, y0, z0;
-  wave_segment(g, tile, x0, y0, z0);
-  const int x = x0 + (int)(threadIdx.x & 63);
-  const bool active = x < g.nx && y0 < g.ny && z0 < g.nz;
-  const long long n = x + (long long)g.nx * (y0 + (long long)g.ny * z0);
+  const WaveCells<FLAT> wc = wave_cells<FLAT>(g, tile);
+  const LaneCell cell = lane_cell<FLAT>(g, wc);
+  const bool active = (int)(threadIdx.x & 63) <= wc.last;
+  const long long n = cell.x + (long long)g.nx * (cell.y + (long long)g.ny * wc.z);
   Slots s;
   s.n = 0;
-  if (cnt > 0) collect_slots<D>(g, x0, y0, z0, active, lds, cnt, h, s, err, slot_lds);
+  if (cnt > 0) collect_slots<D, FLAT>(g, wc, active, lds, cnt, h, s, err, slot_lds);
   if (!active) return;
   double S_ = 0.0;
 #pragma unroll
@@ -1164,37 +1141,32 @@ static int grid_for(long long n, int block = 256) {
   return (int)b;
 }
 
-template <int Q, int PREC>
+template <int Q, int PREC, bool WALLS, bool FLAT>
 static int dispatch_step(psclbm_ctx* c, const StepArgs& a, int par, size_t lds_bytes) {
   const int nb = c->ntiles + a.dem_blocks;
-  const bool walls = !(c->geom.periodic[0] && c->geom.periodic[1] && c->geom.periodic[2]);
   if (par == 2) {  // ring step: canonical FP64 in and out
-    if constexpr (PREC == PSCLBM_FP64) {
-      if (walls)
-        k_step<Q, PREC, 2, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
-      else
-        k_step<Q, PREC, 2, false><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
-      return hip_ok(hipGetLastError());
-    }
-    return PSCLBM_EINVAL;
-  }
-  const bool nt = c->geom.nt_even != 0;
-  if (walls) {
-    if (par == 0 && nt)
-      k_step<Q, PREC, 0, true, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
-    else if (par == 0)
-      k_step<Q, PREC, 0, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+    if constexpr (PREC == PSCLBM_FP64)
+      k_step<Q, PREC, 2, WALLS, FLAT><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
     else
-      k_step<Q, PREC, 1, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+      return PSCLBM_EINVAL;
+  } else if (par == 1) {
+    k_step<Q, PREC, 1, WALLS, FLAT><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+  } else if (c->geom.nt_even) {
+    k_step<Q, PREC, 0, WALLS, FLAT, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
   } else {
-    if (par == 0 && nt)
-      k_step<Q, PREC, 0, false, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
-    else if (par == 0)
-      k_step<Q, PREC, 0, false><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
-    else
-      k_step<Q, PREC, 1, false><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+    k_step<Q, PREC, 0, WALLS, FLAT><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
   }
   return hip_ok(hipGetLastError());
+}
+
+template <int Q, int PREC>
+static int dispatch_step(psclbm_ctx* c, const StepArgs& a, int par, size_t lds) {
+  const bool walls = !(c->geom.periodic[0] && c->geom.periodic[1] && c->geom.periodic[2]);
+  if (c->geom.flat)
+    return walls ? dispatch_step<Q, PREC, true, true>(c, a, par, lds)
+                 : dispatch_step<Q, PREC, false, true>(c, a, par, lds);
+  return walls ? dispatch_step<Q, PREC, true, false>(c, a, par, lds)
+               : dispatch_step<Q, PREC, false, false>(c, a, par, lds);
 }
 
 template <int PREC>
@@ -1274,7 +1246,7 @@ int launch_rasterize(psclbm_ctx* c, const psclbm_particles* p, bool dem_bins) {
   k_rasterize<<<(unsigned)blocks, 256, 0, c->stream>>>(
       c->geom, p->n, three_d, c->cfg.shell_h, p->x, p->u, p->omega, p->radius, c->snap,
       c->tile_count_buf[next], c->tile_count_buf[c->tile_cur], c->tile_list,
-      c->cfg.max_tile_particles, c->facc[0], c->facc[1], c->err, db);
+      c->list_cap, c->facc[0], c->facc[1], c->err, db);
   const int rc = hip_ok(hipGetLastError());
   if (rc) return rc;
   c->tile_cur = next;
@@ -1283,17 +1255,21 @@ int launch_rasterize(psclbm_ctx* c, const psclbm_particles* p, bool dem_bins) {
   return PSCLBM_OK;
 }
 
-int launch_solid_fraction(psclbm_ctx* c, double* eps, int* ids, double* seps, int k) {
-  const size_t lds = (sizeof(LdsEntry) + sizeof(double)) * (size_t)c->cfg.max_tile_particles;
-  if (c->geom.q == 9)
-    k_solid_fraction<2><<<c->ntiles, BLOCK, lds, c->stream>>>(
-        c->geom, c->cfg.shell_h, c->np, c->cfg.max_tile_particles, c->tile_count, c->tile_list,
-        c->snap, eps, ids, seps, k, c->err);
-  else
-    k_solid_fraction<3><<<c->ntiles, BLOCK, lds, c->stream>>>(
-        c->geom, c->cfg.shell_h, c->np, c->cfg.max_tile_particles, c->tile_count, c->tile_list,
-        c->snap, eps, ids, seps, k, c->err);
+template <int D, bool FLAT>
+static int solid_fraction(psclbm_ctx* c, double* eps, int* ids, double* seps, int k) {
+  const size_t lds = (sizeof(LdsEntry) + sizeof(double)) * (size_t)c->list_cap;
+  k_solid_fraction<D, FLAT><<<c->ntiles, BLOCK, lds, c->stream>>>(
+      c->geom, c->cfg.shell_h, c->np, c->list_cap, c->tile_count, c->tile_list, c->snap, eps, ids,
+      seps, k, c->err);
   return hip_ok(hipGetLastError());
+}
+
+int launch_solid_fraction(psclbm_ctx* c, double* eps, int* ids, double* seps, int k) {
+  if (c->geom.q == 9)
+    return c->geom.flat ? solid_fraction<2, true>(c, eps, ids, seps, k)
+                        : solid_fraction<2, false>(c, eps, ids, seps, k);
+  return c->geom.flat ? solid_fraction<3, true>(c, eps, ids, seps, k)
+                      : solid_fraction<3, false>(c, eps, ids, seps, k);
 }
 
 // Arguments of one step from the context (state, forces and mass in place).
@@ -1306,7 +1282,7 @@ static StepArgs step_args(psclbm_ctx* c) {
   for (int k = 0; k < 3; ++k) a.force[k] = c->cfg.body_force[k];
   a.h = c->cfg.shell_h;
   a.np = c->np;
-  a.cap = c->cfg.max_tile_particles;
+  a.cap = c->list_cap;
   a.tile_count = c->tile_count;
   a.tile_list = c->tile_list;
   a.snap = c->snap;
@@ -1357,7 +1333,7 @@ static int outlet_velocity(psclbm_ctx* c, const void* f, int prec, int par, unsi
 }
 
 static size_t step_lds(const psclbm_ctx* c) {
-  return c->np > 0 ? (sizeof(LdsEntry) + 6 * sizeof(double)) * (size_t)c->cfg.max_tile_particles
+  return c->np > 0 ? (sizeof(LdsEntry) + 6 * sizeof(double)) * (size_t)c->list_cap
                    : 0;
 }
 

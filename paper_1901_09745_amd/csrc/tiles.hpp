@@ -57,11 +57,21 @@ __device__ __forceinline__ double sqrt_nr(double v) {
   return s > 0.0f ? s0 + res * (double)(0.5f * __builtin_amdgcn_rcpf(s)) : 0.0;
 }
 
-// LDS image of a tile's particle list.
-struct LdsEntry {
+// LDS image of a tile's particle list: 96 bytes an entry in either form.
+template <typename E>
+struct LdsEntryT;
+template <>
+struct LdsEntryT<double> {
   double x, y, z;
   double r, cs;
   double u[3], w[3];
+  int id;
+  int pad;
+};
+template <>
+struct LdsEntryT<float> {
+  double x, y, z;
+  double r, cs;
   // the centre as an FP32 pair, x = xh + xl to FP64 accuracy, and U and
   // Omega rounded to FP32: the FP32 arithmetic forms take u_s = U + Omega x r
   // from these
@@ -70,6 +80,7 @@ struct LdsEntry {
   int id;
   int pad;
 };
+using LdsEntry = LdsEntryT<double>;
 
 // Slots of one cell: up to KSLOTS particles with eps > 0, ascending particle
 // id (lds[e[k]].id).  The fractions are evaluated in FP64 and held as E (FP64,
@@ -105,44 +116,64 @@ __device__ __forceinline__ int wave_scan_incl(int v) {
   return v;
 }
 
-// The cells of one wave form one x-row of the tile (TX == 64), so a list
-// entry's y and z separations are the same for the whole wave.  Phase 1: each
-// lane takes one list entry and, when its shell r + h reaches the row, the
-// chord of the row the shell can cover (the lanes whose cell centres lie
-// within sqrt((r + h)^2 - dy^2 - dz^2) of the centre's nearest image, bounded
-// in FP32 and widened by 1e-3 lanes, since it only limits the cells examined;
-// on periodic x narrower than 64 + 2 (r + h) + 2 the whole row).  Phase 2: the
-// (entry, cell) pairs of all chords, laid out entry by entry by a prefix scan,
-// are taken 64 at a time, one per lane: Table 1 for the pair in FP64, and a
-// slot of its cell in LDS when the fraction is positive.  Phase 3: each cell reads its
-// slots and orders them by particle id.  At most KSLOTS slots are kept per
-// cell (more set ERR_SLOTS).  All 64 lanes must call this.
-static_assert(SEG == 64, "one wave per 64-cell row segment");
+// The cells of one wave: 64 of a row (row tiles), or 64 consecutive cells of a
+// plane in one or more rows (FLAT).  All values are uniform over the wave.
+template <bool FLAT>
+struct WaveCells {
+  int x0, y0, z;  // the first cell
+  int rows;       // rows the wave's cells lie in (1 for row tiles)
+  int last;       // last lane with a cell, negative when there is none
+};
 
-template <int D, typename E>
-__device__ inline void collect_slots(const Geom& g, int x0, int y, int z, bool active,
-                                     const LdsEntry* lds, int cnt, double h, SlotsT<E>& s,
+// A list entry's y and z separations are the same for all of a row's cells.
+// Phase 1: each lane takes one (list entry, row of the wave) item and, when
+// the entry's shell r + h reaches the row, the chord of the row the shell can
+// cover (the lanes whose cell centres lie within sqrt((r + h)^2 - dy^2 -
+// dz^2) of the centre's nearest image, bounded in FP32 and widened by 1e-3
+// lanes, since it only limits the cells examined; on periodic x narrower than
+// 64 + 2 (r + h) + 2 the whole row).  Phase 2: the (entry, cell) pairs of all
+// chords, laid out item by item by a prefix scan, are taken 64 at a time, one
+// per lane: Table 1 for the pair in FP64, and a slot of its cell in LDS when
+// the fraction is positive.  Phase 3: each cell reads its slots and orders
+// them by particle id.  At most KSLOTS slots are kept per cell (more set
+// ERR_SLOTS).  All 64 lanes must call this.
+static_assert(SEG == 64, "64 cells a wave");
+
+template <int D, bool FLAT, typename E>
+__device__ inline void collect_slots(const Geom& g, const WaveCells<FLAT>& wc, bool active,
+                                     const LdsEntryT<E>* lds, int cnt, double h, SlotsT<E>& s,
                                      unsigned* err, SlotLdsT<E>& sl) {
   const int px = g.periodic[0], py = g.periodic[1], pz = g.periodic[2];
   const int nx = g.nx, ny = g.ny, nz = g.nz;
+  const int z = wc.z;
   const int tid = (int)threadIdx.x;
   const int lane = tid & 63;
   const int wbase = tid - lane;
-  const bool row = y < ny && z < nz;  // uniform over the wave
-  const int xlim = (nx - 1 - x0) < 63 ? (nx - 1 - x0) : 63;
+  const int last = wc.last;  // uniform over the wave
   const double Lx = (double)nx;
-  const double xc = (double)x0 + 31.5;
+  // item t: entry t / rows, row t % rows (the quotient is exact: t < 2^15 and
+  // rows <= 64, so (t + 1/2) / rows stays 2^-7 from a whole number)
+  const int rows = FLAT ? wc.rows : 1;
+  const float per_row = FLAT ? __builtin_amdgcn_rcpf((float)rows) : 1.0f;
+  auto entry_of = [&](int t) { return FLAT ? (int)(((float)t + 0.5f) * per_row) : t; };
+  const int items = cnt * rows;
   sl.n[tid] = 0;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  for (int base = 0; row && base < cnt; base += 64) {
+  for (int base = 0; last >= 0 && base < items; base += 64) {
     // phase 1: chords
-    const int ec = base + lane;
-    int chord = 0, lo = 0, wrap = 0, shc = 0;
+    const int it = base + lane;
+    int chord = 0, lo = 0, wrap = 0, shc = 0, row = 0;
     double dyz2 = 0.0;
-    if (ec < cnt) {
-      const LdsEntry& P = lds[ec];
-      const double dy = min_image((double)y - P.y, py, ny);
+    if (it < items) {
+      const int ec = entry_of(it);
+      row = FLAT ? it - ec * rows : 0;
+      // the row's lanes la .. lb; lane l is its cell x = xr + l
+      const int xr = wc.x0 - row * nx;
+      const int la = FLAT && xr < 0 ? -xr : 0;
+      const int lb = FLAT && nx - 1 - xr < last ? nx - 1 - xr : last;
+      const LdsEntryT<E>& P = lds[ec];
+      const double dy = min_image((double)(wc.y0 + row) - P.y, py, ny);
       dyz2 = dy * dy;
       if constexpr (D == 3) {
         const double dz = min_image((double)z - P.z, pz, nz);
@@ -151,22 +182,22 @@ __device__ inline void collect_slots(const Geom& g, int x0, int y, int z, bool a
       const double rh = P.r + h;
       if (dyz2 < rh * rh) {
         // x-image of the centre nearest the row's middle: shc 1 is -Lx, 2 is +Lx
-        const double ddx = xc - P.x;
+        const double ddx = (FLAT ? (double)xr + 0.5 * (double)(la + lb) : (double)xr + 31.5) - P.x;
         if (px) shc = ddx > 0.5 * Lx ? 1 : (ddx < -0.5 * Lx ? 2 : 0);
         wrap = px && Lx < 66.0 + 2.0 * rh;
         int hi;
         if (wrap) {
-          lo = 0;
-          hi = xlim;
+          lo = la;
+          hi = lb;
         } else {
           // the chord only bounds the cells examined (their membership is
           // decided in phase 2), so FP32 with a margin of 1e-3 lanes will do
           const double sh = shc == 1 ? -Lx : (shc == 2 ? Lx : 0.0);
           const float half = __builtin_amdgcn_sqrtf((float)(rh * rh - dyz2));
-          const float c0 = (float)((P.x - sh) - (double)x0);  // centre's image, in lanes
+          const float c0 = (float)((P.x - sh) - (double)xr);  // centre's image, in lanes
           const float l = ceilf(c0 - half - 1e-3f), u = floorf(c0 + half + 1e-3f);
-          lo = l < 0.0f ? 0 : (int)l;
-          hi = u > (float)xlim ? xlim : (int)u;
+          lo = l < (float)la ? la : (int)l;
+          hi = u > (float)lb ? lb : (int)u;
         }
         chord = hi >= lo ? hi - lo + 1 : 0;
       }
@@ -175,8 +206,9 @@ __device__ inline void collect_slots(const Geom& g, int x0, int y, int z, bool a
     const int off = incl - chord;
     const int total = __builtin_amdgcn_readlane(incl, 63);
     const unsigned long long cmask = __ballot(chord > 0);
-    // lo (6 bits), wrap, shc (2 bits) and off in one word for the broadcast
-    const int pk = lo | (wrap << 6) | (shc << 7) | (off << 9);
+    // lo (6 bits), wrap, shc (2 bits), off (at most 64 x 63) and the row in one
+    // word for the broadcast (lo past the last lane only where the chord is empty)
+    const int pk = (lo & 63) | (wrap << 6) | (shc << 7) | (off << 9) | (row << 22);
     // phase 2: one (entry, cell) pair per lane
     for (int jb = 0; jb < total; jb += 64) {
       const int j = jb + lane;
@@ -187,13 +219,14 @@ __device__ inline void collect_slots(const Geom& g, int x0, int y, int z, bool a
       }
       const int pkb = __shfl(pk, b, 64);
       const double dyz2b = __shfl(dyz2, b, 64);
-      const int lob = pkb & 63, wrapb = (pkb >> 6) & 1, offb = pkb >> 9;
+      const int lob = pkb & 63, wrapb = (pkb >> 6) & 1, offb = (pkb >> 9) & 0x1fff;
       const double shb = ((pkb >> 7) & 3) == 1 ? -Lx : (((pkb >> 7) & 3) == 2 ? Lx : 0.0);
       const int cl = lob + (j - offb);  // cell lane of the pair
       const bool valid = j < total && (unsigned)cl < 64u;
-      const int e = base + b;
-      const LdsEntry& P = lds[valid ? e : 0];
-      double dx = (double)(x0 + cl) - P.x;
+      const int e = entry_of(base + b);
+      const LdsEntryT<E>& P = lds[valid ? e : 0];
+      const int xr = FLAT ? wc.x0 - (pkb >> 22) * nx : wc.x0;
+      double dx = (double)(xr + cl) - P.x;
       dx = wrapb ? min_image(dx, px, nx) : dx + shb;
       const double d2 = dx * dx + dyz2b;
       // the Table 1 rule on d = sqrt(d2)
@@ -272,62 +305,112 @@ __device__ inline void collect_slots(const Geom& g, int x0, int y, int z, bool a
 }
 
 
+template <typename E>
+__device__ __forceinline__ void fill_entry(LdsEntryT<E>& L, const PSnap& P, int id) {
+  L.x = P.x[0];
+  L.y = P.x[1];
+  L.z = P.x[2];
+  L.r = P.r;
+  L.cs = P.cs;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if constexpr (std::is_same<E, float>::value) {
+      L.xh[a] = (float)P.x[a];
+      L.xl[a] = (float)(P.x[a] - (double)L.xh[a]);
+      L.uf[a] = (float)P.u[a];
+      L.wf[a] = (float)P.w[a];
+    } else {
+      L.u[a] = P.u[a];
+      L.w[a] = P.w[a];
+    }
+  }
+  L.id = id;
+}
+
 // Loads the tile's particle list into LDS (in list order: the slot search
 // orders each cell's slots by particle id) and clears its force accumulators.
 // Returns the list length (uniform over the block); when it is positive the
 // block has passed a barrier after the fill.  Must be called by the whole
 // block.
+// `issue` is called once the loads of the count and the first ids are under
+// way: loads a kernel starts there travel beside the list's own chain (count
+// and ids, snapshots, LDS).
+template <typename E, typename Issue>
 __device__ inline int load_tile_list(const int* tile_count, const int* tile_list, int cap,
-                                     const PSnap* snap, int tile, LdsEntry* lds, double* acc,
-                                     int np) {
+                                     const PSnap* snap, int tile, LdsEntryT<E>* lds, double* acc,
+                                     int np, Issue issue) {
   // each thread's first list entry is read alongside the count (entries past
   // the count are stale ids or zeros inside the list buffer, never used)
   const int* lst = tile_list + (size_t)tile * cap;
   const int e0 = (int)threadIdx.x;
   const int pre = np > 0 && e0 < cap ? lst[e0] : 0;
   int cnt = np > 0 ? tile_count[tile] : 0;
+  issue();
   if (cnt > cap) cnt = cap;
   if (cnt == 0) return 0;
-  for (int e = e0; e < cnt; e += BLOCK) {
-    const int id = e == e0 ? pre : lst[e];
-    const PSnap& P = snap[id];
-    LdsEntry& L = lds[e];
-    L.x = P.x[0];
-    L.y = P.x[1];
-    L.z = P.x[2];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      L.xh[a] = (float)P.x[a];
-      L.xl[a] = (float)(P.x[a] - (double)L.xh[a]);
-      L.uf[a] = (float)P.u[a];
-      L.wf[a] = (float)P.w[a];
-    }
-    L.r = P.r;
-    L.cs = P.cs;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      L.u[a] = P.u[a];
-      L.w[a] = P.w[a];
-    }
-    L.id = id;
-  }
+  // (the first entry apart from the loop: its id is waited for by itself, not
+  // with every load issued after it)
+  if (e0 < cnt) fill_entry(lds[e0], snap[pre], pre);
+  for (int e = e0 + BLOCK; e < cnt; e += BLOCK) fill_entry(lds[e], snap[lst[e]], lst[e]);
   if (acc)
     for (int k = threadIdx.x; k < 6 * cnt; k += BLOCK) acc[k] = 0.0;
   __syncthreads();
   return cnt;
 }
+template <typename E>
+__device__ inline int load_tile_list(const int* tile_count, const int* tile_list, int cap,
+                                     const PSnap* snap, int tile, LdsEntryT<E>* lds, double* acc,
+                                     int np) {
+  return load_tile_list(tile_count, tile_list, cap, snap, tile, lds, acc, np, [] {});
+}
 
-// The calling wave's cells in a tile: the 64-cell row segment starting at x
-// = xw in row (y, z).  The results are uniform over the wave (scalar).
-__device__ inline void wave_segment(const Geom& g, int tile, int& xw, int& y, int& z) {
+// The calling wave's cells in a tile.
+template <bool FLAT>
+__device__ inline WaveCells<FLAT> wave_cells(const Geom& g, int tile) {
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int tx = tile % g.ntx;
   const int r = tile / g.ntx;
-  const int ty = r % g.nty;
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int segs = g.twx >> 6;  // segments per tile row
-  xw = __builtin_amdgcn_readfirstlane(tx * g.twx + SEG * (w % segs));
-  y = __builtin_amdgcn_readfirstlane(ty * g.twy + w / segs);
-  z = __builtin_amdgcn_readfirstlane(r / g.nty);
+  WaveCells<FLAT> c;
+  if constexpr (FLAT) {
+    const int p0 = BLOCK * tx + SEG * w;  // the wave's first cell in the plane
+    const int left = g.nx * g.ny - p0;
+    c.y0 = __builtin_amdgcn_readfirstlane(p0 / g.nx);
+    c.x0 = __builtin_amdgcn_readfirstlane(p0 - c.y0 * g.nx);
+    c.z = __builtin_amdgcn_readfirstlane(r);
+    c.last = __builtin_amdgcn_readfirstlane((left < SEG ? left : SEG) - 1);
+    c.rows = __builtin_amdgcn_readfirstlane((c.x0 + c.last) / g.nx + 1);
+  } else {
+    const int ty = r % g.nty;
+    const int segs = g.twx >> 6;  // segments per tile row
+    c.x0 = __builtin_amdgcn_readfirstlane(tx * g.twx + SEG * (w % segs));
+    c.y0 = __builtin_amdgcn_readfirstlane(ty * g.twy + w / segs);
+    c.z = __builtin_amdgcn_readfirstlane(r / g.nty);
+    c.rows = 1;
+    const int left = g.nx - c.x0;
+    c.last = c.y0 < g.ny && c.z < g.nz ? (left < SEG ? left : SEG) - 1 : -1;
+  }
+  return c;
+}
+
+// The calling lane's cell (when lane <= c.last).
+struct LaneCell {
+  int x, y;
+};
+template <bool FLAT>
+__device__ __forceinline__ LaneCell lane_cell(const Geom& g, const WaveCells<FLAT>& c) {
+  const int t = c.x0 + (int)(threadIdx.x & 63);
+  LaneCell l;
+  l.x = t;
+  l.y = c.y0;
+  if constexpr (FLAT) {
+    // t < nx + 63: t / nx is 0 or 1 in rows of 64 or more, and in shorter
+    // ones the product with 2^16 / nx rounded up is exact (t nx < 2^16)
+    const unsigned k = g.nx >= SEG ? (t >= g.nx ? 1u : 0u)
+                                   : ((unsigned)t * (65536u / (unsigned)g.nx + 1u)) >> 16;
+    l.x = t - (int)k * g.nx;
+    l.y = c.y0 + (int)k;
+  }
+  return l;
 }
 
 
@@ -340,8 +423,6 @@ __device__ inline int xcd_tile(int b, int nb) {
   const int xcd = b % NX, k = b / NX;
   return xcd * per + (xcd < rem ? xcd : rem) + k;
 }
-// The remap pays for 64-wide tiles, whose x-neighbours share the halo lines;
-// wider tiles keep those lines inside the workgroup and run as dispatched.
 __device__ inline int tile_of(const Geom& g, int b, int nb) { return g.remap ? xcd_tile(b, nb) : b; }
 
 // Lattice extents and periodicity as plain scalars (no arrays: every access
@@ -365,21 +446,46 @@ __device__ __forceinline__ Dims dims_of(const Geom& g) {
   return d;
 }
 
+// Element `e` of a per-direction array through a 32-bit byte offset, in the
+// global address space, so the access is the scalar base plus one 32-bit
+// vector offset.
+template <typename S>
+using GlobalT = __attribute__((address_space(1))) S;
+template <typename S>
+__device__ __forceinline__ GlobalT<S>& elem(S* base, unsigned e) {
+  auto* gb = (__attribute__((address_space(1))) char*)base;
+  return *(GlobalT<S>*)(gb + (e * (unsigned)sizeof(S)));
+}
+
+// The same element read or written with a non-temporal hint when NT: the
+// line is streamed through the caches rather than kept in them.
+template <bool NT, typename S>
+__device__ __forceinline__ S elem_ld(S* base, unsigned e) {
+  if constexpr (NT) return __builtin_nontemporal_load(&elem(base, e));
+  else return elem(base, e);
+}
+template <bool NT, typename S>
+__device__ __forceinline__ void elem_st(S* base, unsigned e, S v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, &elem(base, e));
+  else elem(base, e) = v;
+}
+
 // The links of one cell: its neighbours through the periodic wrap, and the
 // non-periodic faces it lies at.  y and z are uniform over the wave, so a
 // link's y and z part is a scalar that goes into the base pointer, and its x
-// part is one of three lane offsets: no arithmetic per link.  Only in a wave
+// part is one of three lane offsets: no arithmetic per link.  (In a FLAT wave
+// y varies and joins the lane part, one addition a link.)  Only in a wave
 // with a cell at a wall do the lanes choose an address each (`at`); that path
 // is taken by the waves along the faces alone.  Resolving each link through
 // the faces by itself, with a branch around each load, cost the odd steps
 // 100-260 VALU and 50-510 SALU instructions a wave (384x192x192 with walls,
 // FP64: 890 us against 822 for the even step; the 10x51x51 FP32 duct 10.8
 // against 6.2 us).
-template <int Q, bool WALLS>
+template <int Q, bool WALLS, bool FLAT>
 struct CellLinks {
   using L = Lattice<Q>;
   unsigned n, xm, xp;  // the cell and its x neighbours
-  int ym, yp, zm, zp;  // offsets to its y and z neighbours (uniform)
+  int ym, yp, zm, zp;  // offsets to its y and z neighbours (uniform but for y in a FLAT wave)
   unsigned wall;       // bit f: the cell lies at the non-periodic face f
   bool inner;          // no cell of the wave lies at one (uniform)
 
@@ -411,11 +517,14 @@ struct CellLinks {
   // the non-periodic faces the cell's link along e_i leaves through
   __device__ __forceinline__ unsigned out(int i) const { return wall & faces(i); }
   __device__ __forceinline__ unsigned lane_part(int i) const {
-    return L::ex(i) > 0 ? xp : (L::ex(i) < 0 ? xm : n);
+    const unsigned v = L::ex(i) > 0 ? xp : (L::ex(i) < 0 ? xm : n);
+    return FLAT ? v + (unsigned)y_part(i) : v;
+  }
+  __device__ __forceinline__ int y_part(int i) const {
+    return L::ey(i) > 0 ? yp : (L::ey(i) < 0 ? ym : 0);
   }
   __device__ __forceinline__ int row_part(int i) const {
-    return (L::ey(i) > 0 ? yp : (L::ey(i) < 0 ? ym : 0)) +
-           (L::ez(i) > 0 ? zp : (L::ez(i) < 0 ? zm : 0));
+    return (FLAT ? 0 : y_part(i)) + (L::ez(i) > 0 ? zp : (L::ez(i) < 0 ? zm : 0));
   }
   // Where the population that leaves along e_i goes (N cells per direction
   // array): array i of the neighbour, or, when the link leaves through a
@@ -575,7 +684,8 @@ __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSn
                                  int lane, int* count, int* tile_list, int cap, unsigned* err) {
   const double R = P.r + h;
   const int L[3] = {g.nx, g.ny, g.nz};
-  const int T[3] = {g.twx, g.twy, 1};
+  // (flat tiles: runs of x cells and of rows)
+  const int T[3] = {g.flat ? 1 : g.twx, g.flat ? 1 : g.twy, 1};
   AxisRuns runs[3];
   int la[3], lt[3];
 #pragma unroll
@@ -591,6 +701,44 @@ __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSn
     la[a] = runs[a].a1 >= runs[a].a0 ? runs[a].a1 - runs[a].a0 + 1 : 0;
     lt[a] = la[a] + (runs[a].b1 >= runs[a].b0 ? runs[a].b1 - runs[a].b0 + 1 : 0);
   }
+  auto enter = [&](int t) {
+    const int slot = atomicAdd(&count[t], 1);
+    if (slot < cap)
+      tile_list[(size_t)t * cap + slot] = s;
+    else
+      atomicOr(err, ERR_SLOTS);
+  };
+  if (g.flat) {
+    // per plane, the tiles from the first row of the box to its last (both
+    // runs of a wrapped box, the tile they may share counted once), each entered
+    // if one of its rows within the box holds one of the box's cells
+    if (la[0] <= 0 || la[1] <= 0 || la[2] <= 0) return;
+    const bool two = runs[1].b1 >= runs[1].b0;
+    auto first = [&](int y) { return (int)((unsigned)y * (unsigned)g.nx / BLOCK); };
+    auto final = [&](int y) { return (int)(((unsigned)(y + 1) * (unsigned)g.nx - 1u) / BLOCK); };
+    const int a0 = first(runs[1].a0), a1 = final(runs[1].a1);
+    int b0 = two ? first(runs[1].b0) : 1;
+    int b1 = two ? final(runs[1].b1) : 0;
+    if (two && b1 >= a0) b1 = a0 - 1;  // run b (from row 0) ends below run a
+    const int na = a1 - a0 + 1, per = na + (b1 >= b0 ? b1 - b0 + 1 : 0);
+    const int total = per * lt[2];
+    for (int k = lane; k < total; k += 64) {
+      const int iz = k / per, kt = k - iz * per;
+      const int tx = kt < na ? a0 + kt : b0 + (kt - na);
+      const int tz = iz < la[2] ? runs[2].a0 + iz : runs[2].b0 + (iz - la[2]);
+      const int p0 = BLOCK * tx, p1 = p0 + BLOCK - 1;
+      bool hit = false;
+      const int y1 = p1 / g.nx < g.ny - 1 ? p1 / g.nx : g.ny - 1;
+      for (int y = p0 / g.nx; y <= y1; ++y) {
+        if (!((y >= runs[1].a0 && y <= runs[1].a1) || (y >= runs[1].b0 && y <= runs[1].b1))) continue;
+        const int c0 = p0 - y * g.nx, c1 = p1 - y * g.nx;  // the tile's x range in row y
+        hit |= runs[0].a0 <= c1 && runs[0].a1 >= c0;
+        hit |= runs[0].b1 >= runs[0].b0 && runs[0].b0 <= c1 && runs[0].b1 >= c0;
+      }
+      if (hit) enter(tx + g.ntx * tz);
+    }
+    return;
+  }
   const int total = lt[0] * lt[1] * lt[2];
   for (int k = lane; k < total; k += 64) {
     const int ix = k % lt[0];
@@ -599,12 +747,7 @@ __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSn
     const int tx = ix < la[0] ? runs[0].a0 + ix : runs[0].b0 + (ix - la[0]);
     const int ty = iy < la[1] ? runs[1].a0 + iy : runs[1].b0 + (iy - la[1]);
     const int tz = iz < la[2] ? runs[2].a0 + iz : runs[2].b0 + (iz - la[2]);
-    const int t = tx + g.ntx * (ty + g.nty * tz);
-    const int slot = atomicAdd(&count[t], 1);
-    if (slot < cap)
-      tile_list[(size_t)t * cap + slot] = s;
-    else
-      atomicOr(err, ERR_SLOTS);
+    enter(tx + g.ntx * (ty + g.nty * tz));
   }
 }
 
