@@ -73,56 +73,82 @@ __device__ __forceinline__ double feq_i(int i, double rho, double ux, double uy,
   return rho * L::w(i) * (1.0 + 3.0 * eu + 4.5 * eu * eu - 1.5 * uu);
 }
 
-template <int Q, bool WALLS, bool FLAT>
-__global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
+// Bytes: the state and the sensitivity read, the sensitivity written.  Bound
+// by them in 3D with non-temporal hints (NT: the two aligned streams, when
+// they are larger than the last-level cache), else by the latency of its chain
+// at two or three waves per SIMD.  192x96x96 with 2000 spheres between walls:
+// 195 us as one wave's list, search, loads and arithmetic in turn; 186 with the
+// loads started first, 180 with the slots' gradients summed over lanes before
+// the LDS atomics, 162 with the hints (5.0 TB/s).  1024^2 with 1600 disks 60
+// -> 52 us (open faces compiled out, three waves); the 512x256 channel 17.0 ->
+// 13.1 (the inlet's gradient summed per tile).
+template <int Q, bool WALLS, bool FLAT, bool NT>
+__global__ void __launch_bounds__(BLOCK)
+    __attribute__((amdgpu_waves_per_eu(Q == 9 && !WALLS ? 3 : 2))) k_adjoint(const AdjArgs a) {
   using L = Lattice<Q>;
   constexpr int D = L::D;
   extern __shared__ double smem_d[];
   __shared__ SlotLds slot_lds;
   const Geom& G = a.g;
-  const int tile = blockIdx.x;
-  LdsEntry* lds = reinterpret_cast<LdsEntry*>(smem_d);
-  double* acc = reinterpret_cast<double*>(lds + a.cap);  // [cap][9]
-  const int cnt = load_tile_list(a.tile_count, a.tile_list, a.cap, a.snap, tile, lds, nullptr,
-                                 a.np);
-  if (cnt > 0) {
-    for (int k = threadIdx.x; k < 9 * cnt; k += BLOCK) acc[k] = 0.0;
-    __syncthreads();
-  }
+  const int tile = tile_of(G, (int)blockIdx.x, (int)gridDim.x);
   // the wave's cells; z, and y unless FLAT, are uniform over the wave (scalar)
   const WaveCells<FLAT> wc = wave_cells<FLAT>(G, tile);
   const LaneCell cell = lane_cell<FLAT>(G, wc);
   const int x = cell.x, y = cell.y, z = wc.z;
   const bool active = (int)(threadIdx.x & 63) <= wc.last;
   const unsigned N = (unsigned)G.N;
-  const unsigned n = (unsigned)x + (unsigned)G.nx * ((unsigned)y + (unsigned)G.ny * (unsigned)z);
+  const Dims d = dims_of(G);
+  const bool any = wc.last >= 0;
+  const CellLinks<Q, WALLS, FLAT> lk(d, active ? x : any ? wc.x0 : 0,
+                                     active ? y : any ? wc.y0 : 0, any ? z : 0);
+  const unsigned n = lk.n;
+
+  // The sensitivity of each post-collision population, read where it streams
+  // to, and the state entering the step: all 2 Q loads of a cell are started
+  // before the tile's list is waited for and used after the slot search.
+  double ls[Q], fv[Q];
+  auto issue = [&] {
+    // (lanes without a cell read the wave's first: no branch, so that the
+    // number of loads under way is known when the list's ids are waited for)
+    if (lk.inner) {
+#pragma unroll
+      for (int i = 0; i < Q; ++i)
+        ls[i] = elem(a.lam_in + (size_t)i * N + (ptrdiff_t)lk.row_part(i), lk.lane_part(i));
+    } else {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) ls[i] = *lk.at(a.lam_in, N, i);
+    }
+#pragma unroll
+    for (int i = 0; i < Q; ++i) fv[i] = elem_ld<NT>(a.f + (size_t)i * N, n);
+  };
+  LdsEntry* lds = reinterpret_cast<LdsEntry*>(smem_d);
+  double* acc = reinterpret_cast<double*>(lds + a.cap);  // [cap][9]
+  // dJ/d(face velocity) of the tile: every cell of an inlet adds to the same
+  // three numbers, and atomics of one address are taken in turn
+  __shared__ double face_acc[18];
+  const bool faces = WALLS && a.gface;  // (a periodic lattice has no such face)
+  if (faces && threadIdx.x < 18) face_acc[threadIdx.x] = 0.0;
+  const int cnt = load_tile_list(a.tile_count, a.tile_list, a.cap, a.snap, tile, lds, nullptr,
+                                 a.np, issue);
+  for (int k = threadIdx.x; k < 9 * cnt; k += BLOCK) acc[k] = 0.0;
+  if (cnt > 0 || faces) __syncthreads();
   Slots s;
   s.n = 0;
   if (cnt > 0) collect_slots<D, FLAT>(G, wc, active, lds, cnt, a.h, s, nullptr, slot_lds);
 
-  if (active) {
-    Dims d;
-    d.nx = G.nx; d.ny = G.ny; d.nz = G.nz;
-    d.px = G.periodic[0]; d.py = G.periodic[1]; d.pz = G.periodic[2];
-    d.sy = (unsigned)G.nx;
-    d.sz = (unsigned)G.nx * (unsigned)G.ny;
+  // from here on every lane computes (those without a cell the wave's first
+  // one, without slots and without output), so that lanes can exchange values
+  {
     const double rho0 = G.rho0;
     const double F0 = a.force[0], F1 = a.force[1], F2 = a.force[2];
     const int lane = (int)(threadIdx.x & 63);
 
-    // sensitivity of each post-collision population: where it streams to;
     // kappa is the moving-wall term -6 w_i rho (e_i . u_w): d/df_j = -6 w_i (e_i . u_w)
-    double ls[Q];
     double kappa = 0.0;
+    if (WALLS && a.moving_mask) {
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      unsigned m = n;
-      const unsigned out = i == 0 ? 0u : link<WALLS>(d, x, y, z, L::ex(i), L::ey(i), L::ez(i), n, m);
-      if (!out) {
-        ls[i] = a.lam_in[(size_t)i * N + m];
-      } else {
-        ls[i] = a.lam_in[(size_t)L::opp(i) * N + n];
-        const unsigned mw = out & a.moving_mask;
+      for (int i = 1; i < Q; ++i) {
+        const unsigned mw = lk.out(i) & a.moving_mask;
         if (mw) {
           double uw0 = 0.0, uw1 = 0.0, uw2 = 0.0;
 #pragma unroll
@@ -137,15 +163,14 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
       }
     }
 
-    // the state entering the step, consumed as it loads: its moments and
-    // the two sums through which it enters the adjoint, Sf = sum_i lam*_i f_i
-    // and So = sum_i lam*_{-i} f_i (= sum_i lam*_i f_{-i}); an x-face outlet
-    // whose interior neighbour is in this wave takes that neighbour's
-    // velocity from its lane
+    // the state entering the step: its moments and the two sums through which
+    // it enters the adjoint, Sf = sum_i lam*_i f_i and So = sum_i lam*_{-i} f_i
+    // (= sum_i lam*_i f_{-i}); an x-face outlet whose interior neighbour is in
+    // this wave takes that neighbour's velocity from its lane
     double rho_in = 0.0, j0 = 0.0, j1 = 0.0, j2 = 0.0, Sf = 0.0, So = 0.0;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      const double fi = a.f[(size_t)i * N + n];
+      const double fi = fv[i];
       rho_in += fi;
       eacc(L::ex(i), j0, fi);
       eacc(L::ey(i), j1, fi);
@@ -155,7 +180,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
     }
     double uin0 = 0.0, uin1 = 0.0, uin2 = 0.0;
     double wu0 = 0.0, wu1 = 0.0, wu2 = 0.0;
-    if (a.outlet_wave) {
+    if (WALLS && a.outlet_wave) {
       uin0 = (j0 + 0.5 * F0) / rho_in;
       uin1 = (j1 + 0.5 * F1) / rho_in;
       uin2 = (j2 + 0.5 * F2) / rho_in;
@@ -171,7 +196,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
     int reset = 0, rface = 0;
     double ub0 = 0.0, ub1 = 0.0, ub2 = 0.0;
     double rho = rho_in, jx = j0, jy = j1, jz = j2;
-    if (a.inlet_mask | a.outlet_mask) {
+    if (WALLS && active && (a.inlet_mask | a.outlet_mask)) {
 #pragma unroll
       for (int fc = 0; fc < 6; ++fc) {
         const bool on = fc == 0 ? x == 0 : fc == 1 ? x == d.nx - 1 : fc == 2 ? y == 0
@@ -217,20 +242,18 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
     }
 
     // moving walls: d/du_w of -6 w_i rho (e_i . u_w)
-    if (a.gface && a.moving_mask) {
+    if (active && faces && a.moving_mask) {
 #pragma unroll
       for (int i = 1; i < Q; ++i) {
-        unsigned m = n;
-        const unsigned mw =
-            link<WALLS>(d, x, y, z, L::ex(i), L::ey(i), L::ez(i), n, m) & a.moving_mask;
+        const unsigned mw = lk.out(i) & a.moving_mask;
         if (!mw) continue;
         const double cw = -6.0 * L::w(i) * rho * ls[i];
 #pragma unroll
         for (int fc = 0; fc < 6; ++fc)
           if ((mw >> fc) & 1u) {
-            if (L::ex(i)) atomicAdd(a.gface + 3 * fc, cw * L::ex(i));
-            if (L::ey(i)) atomicAdd(a.gface + 3 * fc + 1, cw * L::ey(i));
-            if (L::ez(i)) atomicAdd(a.gface + 3 * fc + 2, cw * L::ez(i));
+            if (L::ex(i)) atomicAdd(face_acc + 3 * fc, cw * L::ex(i));
+            if (L::ey(i)) atomicAdd(face_acc + 3 * fc + 1, cw * L::ey(i));
+            if (L::ez(i)) atomicAdd(face_acc + 3 * fc + 2, cw * L::ez(i));
           }
       }
     }
@@ -322,80 +345,105 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
     // clamped)
     double SG = 0.0;
     const double BLP = Bnp * LP;
+    const bool several = s.n > 1;
+    // the gradient of one slot (9 values: X, U, Omega) into the entry's LDS
+    // accumulators: summed first over aligned blocks of up to 8 lanes whose
+    // slot holds the same entry, so that the LDS unit, which takes lanes of one
+    // address in turn, sees a block's leader only
+    auto accumulate = [&](int e, bool has, auto& v) {
+      constexpr int NV = sizeof(v) / sizeof(v[0]);
+      bool lead;
+      const unsigned mf = merge_flags(has ? e : -1, lane, lead);
+      double* ac = acc + 9 * e;
+#pragma unroll
+      for (int j = 0; j < NV; ++j) {
+        if (D == 2 && (j == 2 || (j > 4 && j < 8))) continue;  // out of the plane
+        const double t = merge_sum(v[j], mf);
+        if (lead) atomicAdd(ac + j, t);
+      }
+    };
 #pragma unroll
     for (int k = 0; k < KSLOTS; ++k) {
-      if (k >= s.n) continue;
-      const int e = s.e[k];
-      const double epsk = s.eps[k];
-      const LdsEntry& P = lds[e];
-      const double rx = min_image((double)x - P.x, d.px, d.nx);
-      const double ry = min_image((double)y - P.y, d.py, d.ny);
-      const double rz = D == 3 ? min_image((double)z - P.z, d.pz, d.nz) : 0.0;
-      const double usx = P.u[0] + P.w[1] * rz - P.w[2] * ry;
-      const double usy = P.u[1] + P.w[2] * rx - P.w[0] * rz;
-      const double usz = P.u[2] + P.w[0] * ry - P.w[1] * rx;
-      const double us2 = usx * usx + usy * usy + usz * usz;
-      const double Bs = epsk * c;
-      // q = dJ/dm = -dJ/dF - dJ/dT x r
-      double qx = 0.0, qy = 0.0, qz = 0.0;
-      const int id = P.id;
-      if (a.gF) {
-        qx -= a.gF[3 * id];
-        qy -= a.gF[3 * id + 1];
-        qz -= a.gF[3 * id + 2];
+      const bool has = k < s.n;
+      if (!__any(has)) break;  // uniform over the wave
+      double v[9];
+#pragma unroll
+      for (int j = 0; j < 9; ++j) v[j] = 0.0;
+      const int e = has ? s.e[k] : 0;
+      if (has) {
+        const double epsk = s.eps[k];
+        const LdsEntry& P = lds[e];
+        const double rx = min_image((double)x - P.x, d.px, d.nx);
+        const double ry = min_image((double)y - P.y, d.py, d.ny);
+        const double rz = D == 3 ? min_image((double)z - P.z, d.pz, d.nz) : 0.0;
+        const double usx = P.u[0] + P.w[1] * rz - P.w[2] * ry;
+        const double usy = P.u[1] + P.w[2] * rx - P.w[0] * rz;
+        const double usz = P.u[2] + P.w[0] * ry - P.w[1] * rx;
+        const double us2 = usx * usx + usy * usy + usz * usz;
+        const double Bs = epsk * c;
+        // q = dJ/dm = -dJ/dF - dJ/dT x r
+        double qx = 0.0, qy = 0.0, qz = 0.0;
+        const int id = P.id;
+        if (a.gF) {
+          qx -= a.gF[3 * id];
+          qy -= a.gF[3 * id + 1];
+          qz -= a.gF[3 * id + 2];
+        }
+        double tx = 0.0, ty = 0.0, tz = 0.0;
+        if (a.gT) {
+          tx = a.gT[3 * id];
+          ty = a.gT[3 * id + 1];
+          tz = a.gT[3 * id + 2];
+          qx -= ty * rz - tz * ry;
+          qy -= tz * rx - tx * rz;
+          qz -= tx * ry - ty * rx;
+        }
+        const double Mx = rho * (usx - ux) + F0, My = rho * (usy - uy) + F1, Mz = rho * (usz - uz) + F2;
+        const double M2x = mxx * usx + mxy * usy + mxz * usz;
+        const double M2y = mxy * usx + myy * usy + myz * usz;
+        const double M2z = mxz * usx + myz * usy + mzz * usz;
+        // (sum_i lam*_i f^eq_i(u_s)) / rho
+        const double Lfr = m0 * (1.0 - 1.5 * us2) + 3.0 * (usx * m1x + usy * m1y + usz * m1z) +
+                           4.5 * (usx * M2x + usy * M2y + usz * M2z);
+        const double dsx = rho * (3.0 * m1x + 9.0 * M2x - 3.0 * usx * m0);
+        const double dsy = rho * (3.0 * m1y + 9.0 * M2y - 3.0 * usy * m0);
+        const double dsz = rho * (3.0 * m1z + 9.0 * M2z - 3.0 * usz * m0);
+        const double Gs = L0 + rho * Lfr + qx * Mx + qy * My + qz * Mz;
+        SG += epsk * Gs;
+        ar += Bs * Lfr + Bs * (qx * (usx - ux) + qy * (usy - uy) + qz * (usz - uz));
+        aux -= Bs * rho * qx;
+        auy -= Bs * rho * qy;
+        auz -= Bs * rho * qz;
+        // dJ/du_s, and through u_s = U + Omega x r and m = B_s M: the parts of
+        // dJ/dr that are dJ/du_s x Omega and dJ/dT x m
+        const double ax = Bs * (dsx + rho * qx), ay = Bs * (dsy + rho * qy), az = Bs * (dsz + rho * qz);
+        const double mx = Bs * Mx, my = Bs * My, mz = Bs * Mz;
+        const double dist = sqrt(rx * rx + ry * ry + rz * rz);
+        const double lin = P.cs - dist;
+        const bool band = dist < P.r + a.h && dist > P.r - a.h && lin > 0.0 && lin < 1.0;
+        // (the c' sum_t eps_t G_t part here when this is the cell's only particle)
+        const double own = several ? 0.0 : cp * epsk * Gs;
+        const double gd = band ? (BLP + c * Gs + own) / dist : 0.0;
+        v[0] = gd * rx - ((ay * P.w[2] - az * P.w[1]) + (ty * mz - tz * my));
+        v[1] = gd * ry - ((az * P.w[0] - ax * P.w[2]) + (tz * mx - tx * mz));
+        v[2] = gd * rz - ((ax * P.w[1] - ay * P.w[0]) + (tx * my - ty * mx));
+        v[3] = ax;
+        v[4] = ay;
+        v[5] = az;
+        v[6] = ry * az - rz * ay;
+        v[7] = rz * ax - rx * az;
+        v[8] = rx * ay - ry * ax;
       }
-      double tx = 0.0, ty = 0.0, tz = 0.0;
-      if (a.gT) {
-        tx = a.gT[3 * id];
-        ty = a.gT[3 * id + 1];
-        tz = a.gT[3 * id + 2];
-        qx -= ty * rz - tz * ry;
-        qy -= tz * rx - tx * rz;
-        qz -= tx * ry - ty * rx;
-      }
-      const double Mx = rho * (usx - ux) + F0, My = rho * (usy - uy) + F1, Mz = rho * (usz - uz) + F2;
-      const double M2x = mxx * usx + mxy * usy + mxz * usz;
-      const double M2y = mxy * usx + myy * usy + myz * usz;
-      const double M2z = mxz * usx + myz * usy + mzz * usz;
-      const double Lfs = rho * (m0 * (1.0 - 1.5 * us2) + 3.0 * (usx * m1x + usy * m1y + usz * m1z) +
-                                4.5 * (usx * M2x + usy * M2y + usz * M2z));
-      const double dsx = rho * (3.0 * m1x + 9.0 * M2x - 3.0 * usx * m0);
-      const double dsy = rho * (3.0 * m1y + 9.0 * M2y - 3.0 * usy * m0);
-      const double dsz = rho * (3.0 * m1z + 9.0 * M2z - 3.0 * usz * m0);
-      const double Gs = L0 + Lfs + qx * Mx + qy * My + qz * Mz;
-      SG += epsk * Gs;
-      ar += Bs * Lfs / rho + Bs * (qx * (usx - ux) + qy * (usy - uy) + qz * (usz - uz));
-      aux -= Bs * rho * qx;
-      auy -= Bs * rho * qy;
-      auz -= Bs * rho * qz;
-      // dJ/du_s, and through u_s = U + Omega x r and m = B_s M: the parts of
-      // dJ/dr that are dJ/du_s x Omega and dJ/dT x m
-      const double ax = Bs * (dsx + rho * qx), ay = Bs * (dsy + rho * qy), az = Bs * (dsz + rho * qz);
-      const double mx = Bs * Mx, my = Bs * My, mz = Bs * Mz;
-      const double dist = sqrt(rx * rx + ry * ry + rz * rz);
-      const double lin = P.cs - dist;
-      const bool band = dist < P.r + a.h && dist > P.r - a.h && lin > 0.0 && lin < 1.0;
-      const double gd = band ? (BLP + c * Gs) / dist : 0.0;
-      double* ac = acc + 9 * e;
-      atomicAdd(ac + 0, gd * rx - ((ay * P.w[2] - az * P.w[1]) + (ty * mz - tz * my)));
-      atomicAdd(ac + 1, gd * ry - ((az * P.w[0] - ax * P.w[2]) + (tz * mx - tx * mz)));
-      atomicAdd(ac + 3, ax);
-      atomicAdd(ac + 4, ay);
-      if constexpr (D == 3) {
-        atomicAdd(ac + 2, gd * rz - ((ax * P.w[1] - ay * P.w[0]) + (tx * my - ty * mx)));
-        atomicAdd(ac + 5, az);
-        atomicAdd(ac + 6, ry * az - rz * ay);
-        atomicAdd(ac + 7, rz * ax - rx * az);
-      }
-      atomicAdd(ac + 8, rx * ay - ry * ax);
+      accumulate(e, has, v);
     }
 
-    // second pass: the c' sum_t eps_t G_t part of dJ/deps_s
-    if (s.n > 0) {
+    // second pass, for cells that several particles share: the c' sum_t eps_t
+    // G_t part of dJ/deps_s
+    if (__any(several)) {
       const double cSG = cp * SG;
 #pragma unroll
       for (int k = 0; k < KSLOTS; ++k) {
-        if (k >= s.n) continue;
+        if (!several || k >= s.n) continue;
         const int e = s.e[k];
         const LdsEntry& P = lds[e];
         const double rx = min_image((double)x - P.x, d.px, d.nx);
@@ -432,10 +480,10 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
         g2 += rw * (3.0 * ez + 9.0 * eu * ez - 3.0 * ub2);
       }
       if (reset == 1) {
-        if (a.gface) {
-          atomicAdd(a.gface + 3 * rface, g0);
-          atomicAdd(a.gface + 3 * rface + 1, g1);
-          atomicAdd(a.gface + 3 * rface + 2, g2);
+        if (faces) {
+          atomicAdd(face_acc + 3 * rface, g0);
+          atomicAdd(face_acc + 3 * rface + 1, g1);
+          atomicAdd(face_acc + 3 * rface + 2, g2);
         }
       } else if (!((a.outlet_wave >> rface) & 1u)) {
         const unsigned k = rface < 2 ? (unsigned)y + (unsigned)d.ny * z
@@ -450,7 +498,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
     // in-wave outlets: the neighbour lane takes the outlet's dJ/du_b through
     // its own u = (sum f e + F/2)/rho: lam_j += g . (e_j - u)/rho
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    if (a.outlet_wave) {
+    if (WALLS && a.outlet_wave) {
 #pragma unroll
       for (int fc = 0; fc < 2; ++fc) {
         if (!((a.outlet_wave >> fc) & 1u)) continue;
@@ -479,13 +527,17 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint(const AdjArgs a) {
       double lj = alpha * ls[j] + Bn * ls[L::opp(j)] + base + edot(ex, ey, ez, qx, qy, qz);
       if (reset) lj = 0.0;
       lj += edot(ex, ey, ez, s0, s1, s2) + sb;
-      a.lam_out[(size_t)j * N + n] = lj;
+      if (active) elem_st<NT>(a.lam_out + (size_t)j * N, n, lj);
     }
   }
 
   // flush the tile's particle gradients, one (entry, component) pair per
   // thread so that a tile's atomics are issued together
   __syncthreads();
+  if (faces && threadIdx.x < 18) {
+    const double v = face_acc[threadIdx.x];
+    if (v != 0.0) atomicAdd(a.gface + threadIdx.x, v);
+  }
   for (int t = threadIdx.x; t < 9 * cnt; t += BLOCK) {
     const int e = t / 9, k = t - 9 * e;
     const double v = acc[t];
@@ -604,14 +656,21 @@ __global__ void __launch_bounds__(BLOCK) k_rasterize_adjoint(Geom g, double h, i
   }
 }
 
+template <int Q, bool WALLS, bool FLAT>
+static void launch_step_adjoint(psclbm_ctx* c, const AdjArgs& a, size_t lds) {
+  // (rows of whole lines only: see the even steps' choice)
+  const bool nt = !FLAT && (double)c->geom.N * Q * sizeof(double) > 256.0 * 1024 * 1024;
+  if (nt) k_adjoint<Q, WALLS, FLAT, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+  else k_adjoint<Q, WALLS, FLAT, false><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+}
 template <int Q>
 static void launch_step_adjoint(psclbm_ctx* c, const AdjArgs& a, bool walls, size_t lds) {
   if (c->geom.flat) {
-    if (walls) k_adjoint<Q, true, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
-    else k_adjoint<Q, false, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+    if (walls) launch_step_adjoint<Q, true, true>(c, a, lds);
+    else launch_step_adjoint<Q, false, true>(c, a, lds);
   } else {
-    if (walls) k_adjoint<Q, true, false><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
-    else k_adjoint<Q, false, false><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+    if (walls) launch_step_adjoint<Q, true, false>(c, a, lds);
+    else launch_step_adjoint<Q, false, false>(c, a, lds);
   }
 }
 

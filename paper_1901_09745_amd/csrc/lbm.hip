@@ -258,13 +258,13 @@ constexpr int step_waves() {
   return WALLS ? 7 : 6;
 }
 
-// NT (even steps only): the lattice is streamed with non-temporal loads and
-// stores, each line being read and written by one wave.
+// NT: the accesses to the own cell's slots (the even step's, and the ring
+// step's loads), each line by one wave, are streamed with non-temporal hints.
 template <int Q, int PREC, int PAR, bool WALLS, bool FLAT, bool NT = false>
 __global__ void __launch_bounds__(BLOCK)
     __attribute__((amdgpu_waves_per_eu(step_waves<Q, PREC, WALLS>())))
     k_step(const StepArgs a) {
-  static_assert(!NT || PAR == 0, "non-temporal streaming in the even steps only");
+  static_assert(!NT || PAR != 1, "non-temporal streaming of the own cell's slots only");
   using L = Lattice<Q>;
   using C = typename Form<PREC>::C;
   using S = typename Form<PREC>::S;
@@ -1145,10 +1145,14 @@ template <int Q, int PREC, bool WALLS, bool FLAT>
 static int dispatch_step(psclbm_ctx* c, const StepArgs& a, int par, size_t lds_bytes) {
   const int nb = c->ntiles + a.dem_blocks;
   if (par == 2) {  // ring step: canonical FP64 in and out
-    if constexpr (PREC == PSCLBM_FP64)
-      k_step<Q, PREC, 2, WALLS, FLAT><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
-    else
+    if constexpr (PREC == PSCLBM_FP64) {
+      if ((double)c->geom.N * Q * sizeof(double) > 256.0 * 1024 * 1024)
+        k_step<Q, PREC, 2, WALLS, FLAT, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+      else
+        k_step<Q, PREC, 2, WALLS, FLAT><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+    } else {
       return PSCLBM_EINVAL;
+    }
   } else if (par == 1) {
     k_step<Q, PREC, 1, WALLS, FLAT><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
   } else if (c->geom.nt_even) {
