@@ -185,11 +185,9 @@ template <int PREC, int Q>
 struct Store {
   using S = typename Form<PREC>::S;
   using C = typename Form<PREC>::C;
-  // direction-i array `b` (= A + i N), element e: the deviation g_i in the
-  // compute type, or g_i / w_i as stored in the scaled (FP16) form
-  template <bool NT = false>
-  __device__ static C ld(S* b, unsigned e, int i, double rho0) {
-    const S v = elem_ld<NT>(b, e);
+  // the deviation g_i of a stored value in the compute type (g_i / w_i as
+  // stored in the scaled, FP16, form)
+  __device__ static C deviation(S v, int i, double rho0) {
     if constexpr (PREC == PSCLBM_FP64) {
       return v - Lattice<Q>::w(i) * rho0;
     } else if constexpr (PREC == PSCLBM_FP32) {
@@ -251,18 +249,25 @@ struct Store {
 // FP64 4.  The reduced 3D forms are bound by instruction issue, and more
 // waves hide more of the loads' and the tile list's latency under it, up to
 // the point where spills cost more.
-template <int Q, int PREC, bool WALLS>
+template <int Q, int PREC, bool WALLS, bool FLAT>
 constexpr int step_waves() {
   if (PREC == PSCLBM_FP64) return Q == 9 ? 5 : 4;
   if (Q == 9) return 8;
-  return WALLS ? 7 : 6;
+  return WALLS && !(FLAT && PREC == PSCLBM_FP32) ? 7 : 6;
 }
+
+// Forms whose loads of f start before the tile's list is waited for rather
+// than after it: FP64 in 3D on periodic lattices, whose four waves per SIMD
+// hide the least (256^3 940 -> 925 us; between walls 90 -> 92, the 2D channel
+// 9.2 -> 9.6, the reduced forms within 1 %).
+template <int Q, int PREC, bool WALLS>
+constexpr bool EARLY_LOADS = Q == 19 && PREC == PSCLBM_FP64 && !WALLS;
 
 // NT: the accesses to the own cell's slots (the even step's, and the ring
 // step's loads), each line by one wave, are streamed with non-temporal hints.
 template <int Q, int PREC, int PAR, bool WALLS, bool FLAT, bool NT = false>
 __global__ void __launch_bounds__(BLOCK)
-    __attribute__((amdgpu_waves_per_eu(step_waves<Q, PREC, WALLS>())))
+    __attribute__((amdgpu_waves_per_eu(step_waves<Q, PREC, WALLS, FLAT>())))
     k_step(const StepArgs a) {
   static_assert(!NT || PAR != 1, "non-temporal streaming of the own cell's slots only");
   using L = Lattice<Q>;
@@ -273,6 +278,7 @@ __global__ void __launch_bounds__(BLOCK)
   // slot fractions held in FP32 by the FP32 arithmetic forms
   using E = typename std::conditional<PREC == PSCLBM_FP64, double, float>::type;
   constexpr bool SC = scaled_form<PREC>();
+  constexpr bool EARLY = EARLY_LOADS<Q, PREC, WALLS>;
   extern __shared__ double smem_d[];
   __shared__ SlotLdsT<E> slot_lds;
   if ((int)blockIdx.x < a.dem_blocks) {
@@ -308,16 +314,42 @@ __global__ void __launch_bounds__(BLOCK)
   using Entry = LdsEntryT<E>;
   Entry* lds = reinterpret_cast<Entry*>(smem_d);
   double* acc = reinterpret_cast<double*>(lds + a.cap);
-  const int cnt = load_tile_list(a.tile_count, a.tile_list, a.cap, a.snap, tile, lds, acc, a.np);
-
   const Dims d = dims_of(a.g);
   // the wave's cells; z, and y unless FLAT, are uniform over the wave (scalar)
   const WaveCells<FLAT> wc = wave_cells<FLAT>(a.g, tile);
   const LaneCell cell = lane_cell<FLAT>(a.g, wc);
   const int x = cell.x, y = cell.y, z = wc.z;
   const bool active = (int)(threadIdx.x & 63) <= wc.last;
-  const unsigned n = (unsigned)x + d.sy * (unsigned)y + d.sz * (unsigned)z;
   const unsigned N = (unsigned)a.g.N;
+
+  // ---- f as stored: started before the tile's list is waited for in the forms
+  // EARLY_LOADS names, after it in the others ----
+  S raw[Q];
+  auto load = [&] {
+    // (lanes without a cell read the wave's first: no branch, so that the
+    // number of loads under way is known when the list's ids are waited for)
+    const bool any = wc.last >= 0;
+    const CellLinks<Q, WALLS, FLAT> lk(d, active ? x : any ? wc.x0 : 0,
+                                       active ? y : any ? wc.y0 : 0, any ? z : 0);
+    if constexpr (PAR == 1) {
+      if (lk.inner) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+          const int o = L::opp(i);  // arrives along e_i: leaves along e_o seen from here
+          raw[i] = elem(A + (size_t)o * N + (ptrdiff_t)lk.row_part(o), lk.lane_part(o));
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) raw[i] = *lk.at(A, N, L::opp(i));
+      }
+    } else {
+      S* from = PAR == 2 ? const_cast<S*>(static_cast<const S*>(a.src)) : A;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) raw[i] = elem_ld<NT>(dir_ptr(from, i, N), lk.n);
+    }
+  };
+  const int cnt = load_tile_list(a.tile_count, a.tile_list, a.cap, a.snap, tile, lds, acc, a.np,
+                                 [&] { if constexpr (EARLY) load(); });
   const double rho0 = a.g.rho0;
   double mass_dev = 0.0;
   // ---- solid fractions of the covering particles (Table 1), whole wave; in
@@ -343,29 +375,13 @@ __global__ void __launch_bounds__(BLOCK)
   const C rho0c = uni(a.g.rho0, a.rho0_f), inv_rho0 = uni(a.inv_rho0, a.inv_rho0_f);
   const double tm = a.tau - 0.5;
   E bscale = 1;  // B_s / eps_{n,s} of the cell (Eq. 13), formed with the weights
-  if (active) {
-    // ---- load f as deviations g_i = f_i - w_i rho0 ----
-    if constexpr (PAR == 1) {
-      const CellLinks<Q, WALLS, FLAT> lk(d, x, y, z);
-      if (lk.inner) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-          const int o = L::opp(i);  // arrives along e_i: leaves along e_o seen from here
-          g[i] = ST::ld(A + (size_t)o * N + (ptrdiff_t)lk.row_part(o), lk.lane_part(o), i, rho0);
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) g[i] = ST::ld(lk.at(A, N, L::opp(i)), 0u, i, rho0);
-      }
-    } else {
-      S* from = PAR == 2 ? const_cast<S*>(static_cast<const S*>(a.src)) : A;
-#pragma unroll
-      for (int i = 0; i < Q; ++i) g[i] = ST::template ld<NT>(dir_ptr(from, i, N), n, i, rho0);
-    }
-  }
+  if constexpr (!EARLY) load();
   if constexpr (Q == 19) {
     if (cnt > 0) collect_slots<D, FLAT>(a.g, wc, active, lds, cnt, a.h, s, a.err, slot_lds);
   }
+  // deviations g_i = f_i - w_i rho0 (in the scaled form g_i / w_i)
+#pragma unroll
+  for (int i = 0; i < Q; ++i) g[i] = ST::deviation(raw[i], i, rho0);
   // the slots' list entries, two to a register (entries < 2^16; the list
   // capacity is at most 512): registers held through the collision
   const unsigned e01 = (unsigned)s.e[0] | ((unsigned)s.e[1] << 16);
