@@ -42,7 +42,7 @@ __global__ void k_dem_bin(DemBinOut b, Geom g, int n, int three_d, const double*
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   for (long long k = i; k < b.nbins; k += (long long)gridDim.x * blockDim.x) b.stale[k] = 0;
   if (i >= n) return;
-  dem_bin_insert(b, three_d, g, i, x + 3 * i, u + 3 * i, r[i], err);
+  dem_bin_store(b, dem_bin_place(b, three_d, g, x + 3 * i), i, x + 3 * i, u + 3 * i, r[i], err);
   if (wsnap)
     for (int a = 0; a < 3; ++a) wsnap[3 * i + a] = w[3 * i + a];
 }
@@ -113,15 +113,20 @@ struct NextOut {
   unsigned* err;
 };
 
-// One wave per particle.  Unless fc_in holds them (the contact forces the
-// coupled step kernel gathered), the contacts are gathered here
-// (dem_contact_wave, with friction when FRIC and Hertz's normal force when
-// HERTZ).  Every lane then integrates the particle (the same values), lane 0
-// stores it, and the wave bins and rasterises it for the next sub-step or
-// coupled step (NextOut): a launch of its own for the binning cost 4.3 us a
-// sub-step (500 spheres, four sub-steps), as long as a third of the contacts.
-// Kinematic particles skip the contacts.
-template <bool FRIC, bool HERTZ>
+// One wave per particle with GATHER, RASTER_LANES lanes without.  With GATHER
+// the contacts are gathered here (dem_contact_wave, with friction when FRIC
+// and Hertz's normal force when HERTZ); without it their forces are those that
+// the coupled step kernel gathered (fc_in), or the motion is prescribed.  Every
+// lane then integrates the particle (the same values), lane 0 stores it, and
+// the lanes bin and rasterise it for the next sub-step or coupled step
+// (NextOut): a launch of its own for the binning cost 4.3 us a sub-step (500
+// spheres, four sub-steps), as long as a third of the contacts.
+// Without the contacts the arithmetic of a particle is the same in every lane
+// that works on it, and half a wave each does it in half the waves (64, 32, 16
+// lanes: a coupled step of 384x192x192 with 18,000 spheres FP32 462, 458, 456
+// us, of 256^3 with 8000 FP16 380, 377, 379, of 1024^2 with 1600 disks 30.1,
+// 29.0, 29.1).
+template <bool FRIC, bool HERTZ, bool GATHER>
 __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, IntArgs ia,
                                                       NextOut nx, double* x, double* u,
                                                       double* w, const double* r,
@@ -134,11 +139,10 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
   if (nx.db.count)
     for (long long k = gid; k < nx.db.nbins; k += (long long)gridDim.x * blockDim.x)
       nx.db.stale[k] = 0;
-  const int i = (int)(gid >> 6);
-  const int lane = (int)(threadIdx.x & 63);
-  if (i >= d.n) return;  // uniform over the wave
-  __shared__ int cand_lds[4 * CONTACT_LDS];
-  int* cand = cand_lds + CONTACT_LDS * (int)(threadIdx.x >> 6);
+  constexpr int LPP = GATHER ? 64 : RASTER_LANES;
+  const int i = (int)(gid / LPP);
+  const int lane = (int)(threadIdx.x % LPP);
+  if (i >= d.n) return;  // (with the contacts uniform over the wave)
   const double ri = r[i];
   // the particle's previous snapshot: its c_s is reused while r is unchanged
   double r_prev = -1.0, cs_prev = 0.0;
@@ -155,13 +159,13 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
   }
   double fsum[3] = {0.0, 0.0, 0.0};
   double tsum[3] = {0.0, 0.0, 0.0};
-  if constexpr (FRIC || HERTZ) {
+  if constexpr (GATHER) {
+    __shared__ int cand_lds[4 * CONTACT_LDS];
+    int* cand = cand_lds + CONTACT_LDS * (int)(threadIdx.x >> 6);
     dem_contact_wave<FRIC, HERTZ>(d, i, lane, xs, us, ri, fsum, cand, &fr, ws, tsum);
   } else if (fc_in) {  // contacts gathered by the step kernel's contact workgroups
 #pragma unroll
     for (int a = 0; a < 3; ++a) fsum[a] = fc_in[3 * i + a];
-  } else if (!ia.kinematic) {
-    dem_contact_wave(d, i, lane, xs, us, ri, fsum, cand);
   }
   integrate_state(ia, ri, Ff + (size_t)ia.fstride * i, Tf + (size_t)ia.tstride * i, fsum,
                   FRIC ? tsum : nullptr, xs, us, ws);
@@ -173,21 +177,24 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
       w[3 * i + a] = ws[a];
     }
   }
-  if (lane == 0) {
-    if (nx.db.count) dem_bin_insert(nx.db, d.three_d, nx.g, i, xs, us, ri, nx.err);
-    if constexpr (FRIC) {
-      if (nx.wnext)
-        for (int a = 0; a < 3; ++a) nx.wnext[3 * i + a] = ws[a];
+  // the bin's and the tiles' atomics first, then the stores that need them
+  const bool bin = nx.db.count && lane == 0;
+  DemPlace place = {0, 0};
+  if (bin) place = dem_bin_place(nx.db, d.three_d, nx.g, xs);
+  if (nx.build) {
+    PSnap P;
+    const bool ok = make_snap(d.three_d, xs, us, ws, ri, P, r_prev, cs_prev);
+    if (ok) bin_tiles<LPP>(nx.g, d.three_d, nx.h, P, i, lane, nx.tcount, nx.tile_list, nx.cap, nx.err);
+    if (lane == 0) {
+      nx.snap[i] = P;
+      if (!ok) atomicOr(nx.err, ERR_RADIUS);
     }
   }
-  if (!nx.build) return;
-  PSnap P;
-  const bool ok = make_snap(d.three_d, xs, us, ws, ri, P, r_prev, cs_prev);
-  if (lane == 0) {
-    nx.snap[i] = P;
-    if (!ok) atomicOr(nx.err, ERR_RADIUS);
+  if (bin) dem_bin_store(nx.db, place, i, xs, us, ri, nx.err);
+  if constexpr (FRIC) {
+    if (nx.wnext && lane == 0)
+      for (int a = 0; a < 3; ++a) nx.wnext[3 * i + a] = ws[a];
   }
-  if (ok) bin_tiles(nx.g, d.three_d, nx.h, P, i, lane, nx.tcount, nx.tile_list, nx.cap, nx.err);
 }
 
 // Kinematic particles (prescribed velocities): x += dt u.
@@ -293,25 +300,21 @@ static FricArgs fric_args(psclbm_ctx* c, const psclbm_dem_params* prm, const dou
   return fr;
 }
 
-// k_dem_contacts in the instantiation for friction and the Hertz contact.
+// k_dem_contacts in the instantiation for friction and the Hertz contact, or
+// without the contact code (contacts in fc_in, or prescribed motion).
 static int launch_contacts(psclbm_ctx* c, bool fric, bool hertz, int n, const DemArgs& d,
                            const FricArgs& fr, const IntArgs& ia, const NextOut& nx, double* x,
                            double* u, double* w, const double* r, const double* F,
                            const double* T, const double* fc_in) {
-  const dim3 grid((n + 3) / 4), block(256);
-  if (fric && hertz)
-    k_dem_contacts<true, true><<<grid, block, 0, c->stream>>>(d, fr, ia, nx, x, u, w, r, F, T,
-                                                             fc_in);
-  else if (fric)
-    k_dem_contacts<true, false><<<grid, block, 0, c->stream>>>(d, fr, ia, nx, x, u, w, r, F, T,
-                                                              fc_in);
-  else if (hertz)
-    k_dem_contacts<false, true><<<grid, block, 0, c->stream>>>(d, fr, ia, nx, x, u, w, r, F, T,
-                                                              fc_in);
-  else
-    k_dem_contacts<false, false><<<grid, block, 0, c->stream>>>(d, fr, ia, nx, x, u, w, r, F,
-                                                               T, fc_in);
-  return hip_ok(hipGetLastError());
+  const dim3 block(256);
+  auto go = [&](auto kernel, int lanes = 64) {
+    const dim3 grid((unsigned)(((long long)n * lanes + 255) / 256));
+    kernel<<<grid, block, 0, c->stream>>>(d, fr, ia, nx, x, u, w, r, F, T, fc_in);
+    return hip_ok(hipGetLastError());
+  };
+  if (fc_in || ia.kinematic) return go(k_dem_contacts<false, false, false>, RASTER_LANES);
+  if (fric) return hertz ? go(k_dem_contacts<true, true, true>) : go(k_dem_contacts<true, false, true>);
+  return hertz ? go(k_dem_contacts<false, true, true>) : go(k_dem_contacts<false, false, true>);
 }
 
 // What a sub-step's DEM kernel leaves for the next one: its rasterisation

@@ -1081,7 +1081,7 @@ __global__ void k_reduce(const double* part, int n, double* out) {
 // ---------------------------------------------------------------------------
 // Rasterisation: particle snapshot, then tile binning (the candidate box X +- (r + h) of Table 1).
 // ---------------------------------------------------------------------------
-// One wave per particle: the particle's snapshot (with V_a of Eq. 17 / 19),
+// RASTER_LANES lanes per particle: its snapshot (with V_a of Eq. 17 / 19),
 // its force / torque rows cleared in both buffers, and its entry in the list
 // of every tile of its shell box (at most two runs per axis after a periodic
 // wrap), the lanes striding over the tiles.  The list counts are double
@@ -1099,20 +1099,23 @@ __global__ void __launch_bounds__(256) k_rasterize(Geom g, int n, int three_d, d
     stale[k] = 0;
   if (db.count)
     for (long long k = gid; k < db.nbins; k += (long long)gridDim.x * blockDim.x) db.stale[k] = 0;
-  const int s = (int)(gid >> 6);
-  const int lane = (int)(threadIdx.x & 63);
-  if (s >= n) return;  // uniform over the wave
+  const int s = (int)(gid / RASTER_LANES);
+  const int lane = (int)(threadIdx.x % RASTER_LANES);
+  if (s >= n) return;
   PSnap P;
   const bool ok = make_snap(three_d, x + 3 * s, u + 3 * s, w + 3 * s, r[s], P);
+  // the bin's and the tiles' atomics first, then the stores that need them
+  const bool bin = db.count && lane == 0;
+  DemPlace place = {0, 0};
+  if (bin) place = dem_bin_place(db, three_d, g, x + 3 * s);
+  if (lane < 6) f0[6 * s + lane] = 0.0;
+  else if (lane < 12) f1[6 * s + lane - 6] = 0.0;
+  if (ok) bin_tiles<RASTER_LANES>(g, three_d, h, P, s, lane, count, tile_list, cap, err);
   if (lane == 0) {
     snap[s] = P;
     if (!ok) atomicOr(err, ERR_RADIUS);
-    if (db.count) dem_bin_insert(db, three_d, g, s, x + 3 * s, u + 3 * s, r[s], err);
   }
-  if (lane < 6) f0[6 * s + lane] = 0.0;
-  else if (lane < 12) f1[6 * s + lane - 6] = 0.0;
-  if (!ok) return;
-  bin_tiles(g, three_d, h, P, s, lane, count, tile_list, cap, err);
+  if (bin) dem_bin_store(db, place, s, x + 3 * s, u + 3 * s, r[s], err);
 }
 
 template <int D, bool FLAT>
@@ -1263,7 +1266,7 @@ int launch_rasterize(psclbm_ctx* c, const psclbm_particles* p, bool dem_bins) {
   const int three_d = c->geom.q == 19;
   const int next = c->tile_cur ^ 1;
   DemBinOut db = dem_bin_out(c, dem_bins);
-  long long blocks = ((long long)p->n + 3) / 4;
+  long long blocks = ((long long)p->n * RASTER_LANES + 255) / 256;
   long long clear = c->ntiles > db.nbins ? c->ntiles : db.nbins;
   const long long clear_blocks = (clear + 255) / 256;
   if (blocks < clear_blocks) blocks = clear_blocks < 4096 ? clear_blocks : 4096;

@@ -630,17 +630,17 @@ __device__ inline bool make_snap(int three_d, const double* x, const double* u, 
   return ok;
 }
 
-// Tiles touched along one axis by the cell range [lo, hi]: at most two runs
-// of tile indices (the second after a periodic wrap).
+// Tiles (of 2^sh cells) touched along one axis by the cell range [lo, hi]: at
+// most two runs of tile indices (the second after a periodic wrap).
 struct AxisRuns {
   int a0, a1, b0, b1;  // runs [a0, a1] and [b0, b1] (b0 > b1 when absent)
 };
 
-__device__ inline AxisRuns axis_runs(int lo, int hi, int L, int T, int periodic) {
+__device__ inline AxisRuns axis_runs(int lo, int hi, int L, int sh, int periodic) {
   AxisRuns r;
   r.b0 = 1;
   r.b1 = 0;
-  const int nt = (L + T - 1) / T;
+  const int last = (L - 1) >> sh;
   if (!periodic) {
     if (lo < 0) lo = 0;
     if (hi > L - 1) hi = L - 1;
@@ -649,28 +649,34 @@ __device__ inline AxisRuns axis_runs(int lo, int hi, int L, int T, int periodic)
       r.a1 = 0;
       return r;
     }
-    r.a0 = lo / T;
-    r.a1 = hi / T;
+    r.a0 = lo >> sh;
+    r.a1 = hi >> sh;
     return r;
   }
   if (hi - lo + 1 >= L) {
     r.a0 = 0;
-    r.a1 = nt - 1;
+    r.a1 = last;
     return r;
   }
-  const int wl = ((lo % L) + L) % L;
-  const int wh = ((hi % L) + L) % L;
-  if (wl <= wh) {
-    r.a0 = wl / T;
-    r.a1 = wh / T;
+  int wl, wh;
+  if (lo >= -L && hi < 2 * L) {  // the box of a centre in [0, L): no division
+    wl = lo < 0 ? lo + L : (lo >= L ? lo - L : lo);
+    wh = hi < 0 ? hi + L : (hi >= L ? hi - L : hi);
   } else {
-    const int t0 = wl / T, t1 = wh / T;
+    wl = ((lo % L) + L) % L;
+    wh = ((hi % L) + L) % L;
+  }
+  if (wl <= wh) {
+    r.a0 = wl >> sh;
+    r.a1 = wh >> sh;
+  } else {
+    const int t0 = wl >> sh, t1 = wh >> sh;
     if (t1 >= t0) {
       r.a0 = 0;
-      r.a1 = nt - 1;
+      r.a1 = last;
     } else {
       r.a0 = t0;
-      r.a1 = nt - 1;
+      r.a1 = last;
       r.b0 = 0;
       r.b1 = t1;
     }
@@ -678,14 +684,38 @@ __device__ inline AxisRuns axis_runs(int lo, int hi, int L, int T, int periodic)
   return r;
 }
 
-// Enters particle s (snapshot P) in the list of every tile of its shell box
-// X +- (r + h); the 64 lanes of the calling wave stride over the tiles.
+// k / n and k % n for 0 <= k < 2^20 and 1 <= n < 2^20 in FP32: (k + 1/2) / n
+// stays 1 / (2 n) from a whole number, the product is off by less than 2^-22 of
+// its value, so the quotient is exact while k < 2^20 (larger: by division).
+// Lanes a particle where only its rasterisation needs several (measured below).
+constexpr int RASTER_LANES = 32;
+
+struct SmallDiv {
+  int n;
+  float r;
+  __device__ explicit SmallDiv(int v) : n(v), r(__builtin_amdgcn_rcpf((float)v)) {}
+  __device__ int quot(int k) const {
+    return k < (1 << 20) ? (int)(((float)k + 0.5f) * r) : k / n;
+  }
+};
+
+// Enters particle s (snapshot P) in the list of every tile that its shell box
+// X +- (r + h) touches; LPP consecutive lanes of the calling wave (this one's
+// number among them: lane) stride over the tiles.  An atomic's return and the
+// store after it are 1-2 us, and a sphere of the 256^3 workload enters about
+// 200 tiles, so each lane starts four tiles' atomics before it waits for the
+// first.  (The scattered entries themselves bound it on large sets: counts spread
+// over lines of their own took 55 us against 22 for the 8000 spheres, and
+// leaving out the box corners' tiles, a fifth, gained nothing.)
+template <int LPP>
 __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSnap& P, int s,
                                  int lane, int* count, int* tile_list, int cap, unsigned* err) {
   const double R = P.r + h;
   const int L[3] = {g.nx, g.ny, g.nz};
   // (flat tiles: runs of x cells and of rows)
-  const int T[3] = {g.flat ? 1 : g.twx, g.flat ? 1 : g.twy, 1};
+  const int sx = g.flat ? 0 : 31 - __builtin_clz((unsigned)g.twx);
+  const int sh[3] = {sx, g.flat ? 0 : 8 - sx, 0};
+  static_assert(BLOCK == 256, "twx * twy == 2^8");
   AxisRuns runs[3];
   int la[3], lt[3];
 #pragma unroll
@@ -697,22 +727,36 @@ __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSn
       lo = (int)ceil(P.x[a] - R);
       hi = (int)floor(P.x[a] + R);
     }
-    runs[a] = axis_runs(lo, hi, L[a], T[a], g.periodic[a]);
+    runs[a] = axis_runs(lo, hi, L[a], sh[a], g.periodic[a]);
     la[a] = runs[a].a1 >= runs[a].a0 ? runs[a].a1 - runs[a].a0 + 1 : 0;
     lt[a] = la[a] + (runs[a].b1 >= runs[a].b0 ? runs[a].b1 - runs[a].b0 + 1 : 0);
   }
-  auto enter = [&](int t) {
-    const int slot = atomicAdd(&count[t], 1);
-    if (slot < cap)
-      tile_list[(size_t)t * cap + slot] = s;
-    else
-      atomicOr(err, ERR_SLOTS);
+  if (lt[0] <= 0 || lt[1] <= 0 || lt[2] <= 0) return;
+  // tile_at(k): the k-th candidate tile, or -1; `total` candidates
+  auto enter_all = [&](auto batch, int total, auto tile_at) {
+    constexpr int U = decltype(batch)::value;
+    for (int k0 = lane; k0 < total; k0 += LPP * U) {
+      int t[U], slot[U];
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int k = k0 + LPP * j;
+        t[j] = k < total ? tile_at(k) : -1;
+        slot[j] = t[j] >= 0 ? atomicAdd(&count[t[j]], 1) : 0;
+      }
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        if (t[j] < 0) continue;
+        if (slot[j] < cap)
+          tile_list[(size_t)t[j] * cap + slot[j]] = s;
+        else
+          atomicOr(err, ERR_SLOTS);
+      }
+    }
   };
   if (g.flat) {
     // per plane, the tiles from the first row of the box to its last (both
     // runs of a wrapped box, the tile they may share counted once), each entered
     // if one of its rows within the box holds one of the box's cells
-    if (la[0] <= 0 || la[1] <= 0 || la[2] <= 0) return;
     const bool two = runs[1].b1 >= runs[1].b0;
     auto first = [&](int y) { return (int)((unsigned)y * (unsigned)g.nx / BLOCK); };
     auto final = [&](int y) { return (int)(((unsigned)(y + 1) * (unsigned)g.nx - 1u) / BLOCK); };
@@ -720,10 +764,11 @@ __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSn
     int b0 = two ? first(runs[1].b0) : 1;
     int b1 = two ? final(runs[1].b1) : 0;
     if (two && b1 >= a0) b1 = a0 - 1;  // run b (from row 0) ends below run a
-    const int na = a1 - a0 + 1, per = na + (b1 >= b0 ? b1 - b0 + 1 : 0);
-    const int total = per * lt[2];
-    for (int k = lane; k < total; k += 64) {
-      const int iz = k / per, kt = k - iz * per;
+    const int na = a1 - a0 + 1;
+    const SmallDiv per(na + (b1 >= b0 ? b1 - b0 + 1 : 0));
+    // (fewer candidates, each with more work: one at a time)
+    enter_all(std::integral_constant<int, 1>{}, per.n * lt[2], [&](int k) {
+      const int iz = per.quot(k), kt = k - iz * per.n;
       const int tx = kt < na ? a0 + kt : b0 + (kt - na);
       const int tz = iz < la[2] ? runs[2].a0 + iz : runs[2].b0 + (iz - la[2]);
       const int p0 = BLOCK * tx, p1 = p0 + BLOCK - 1;
@@ -735,20 +780,19 @@ __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSn
         hit |= runs[0].a0 <= c1 && runs[0].a1 >= c0;
         hit |= runs[0].b1 >= runs[0].b0 && runs[0].b0 <= c1 && runs[0].b1 >= c0;
       }
-      if (hit) enter(tx + g.ntx * tz);
-    }
+      return hit ? tx + g.ntx * tz : -1;
+    });
     return;
   }
-  const int total = lt[0] * lt[1] * lt[2];
-  for (int k = lane; k < total; k += 64) {
-    const int ix = k % lt[0];
-    const int iy = (k / lt[0]) % lt[1];
-    const int iz = k / (lt[0] * lt[1]);
+  const SmallDiv dx(lt[0]), dy(lt[1]);
+  enter_all(std::integral_constant<int, 4>{}, lt[0] * lt[1] * lt[2], [&](int k) {
+    const int q = dx.quot(k), ix = k - q * lt[0];
+    const int iz = dy.quot(q), iy = q - iz * lt[1];
     const int tx = ix < la[0] ? runs[0].a0 + ix : runs[0].b0 + (ix - la[0]);
     const int ty = iy < la[1] ? runs[1].a0 + iy : runs[1].b0 + (iy - la[1]);
     const int tz = iz < la[2] ? runs[2].a0 + iz : runs[2].b0 + (iz - la[2]);
-    enter(tx + g.ntx * (ty + g.nty * tz));
-  }
+    return tx + g.ntx * (ty + g.nty * tz);
+  });
 }
 
 // DEM bin of a position along axis a (uniform bins of width bin_size).
@@ -764,18 +808,28 @@ __device__ inline int dem_bin_coord(double x, int L, int periodic, int nbin, dou
   return b;
 }
 
-// Enters particle s (position x, velocity u, radius r) in its DEM bin of the
-// target set with its record; called by one lane per particle.
-__device__ inline void dem_bin_insert(const DemBinOut& b, int three_d, const Geom& g, int s,
-                                      const double* x, const double* u, double r,
-                                      unsigned* err) {
+// A place for a particle at position x in its DEM bin of the target set: the
+// record's index, or -1 when the bin is full (called by one lane per particle,
+// early: the atomic's return is waited for at the record's store).
+struct DemPlace {
+  int bin, slot;
+};
+__device__ inline DemPlace dem_bin_place(const DemBinOut& b, int three_d, const Geom& g,
+                                         const double* x) {
   const int bx = dem_bin_coord(x[0], g.nx, g.periodic[0], b.nbin[0], b.bin_size[0]);
   const int by = dem_bin_coord(x[1], g.ny, g.periodic[1], b.nbin[1], b.bin_size[1]);
   const int bz = three_d ? dem_bin_coord(x[2], g.nz, g.periodic[2], b.nbin[2], b.bin_size[2]) : 0;
-  const int bin = bx + b.nbin[0] * (by + b.nbin[1] * bz);
-  const int k = atomicAdd(&b.count[bin], 1);
-  if (k < b.bin_cap) {
-    double* rc = b.rec + ((size_t)bin * b.bin_cap + k) * 8;
+  DemPlace p;
+  p.bin = bx + b.nbin[0] * (by + b.nbin[1] * bz);
+  p.slot = atomicAdd(&b.count[p.bin], 1);
+  return p;
+}
+
+// The record of particle s (position x, velocity u, radius r) at its place.
+__device__ inline void dem_bin_store(const DemBinOut& b, const DemPlace& p, int s,
+                                     const double* x, const double* u, double r, unsigned* err) {
+  if (p.slot < b.bin_cap) {
+    double* rc = b.rec + ((size_t)p.bin * b.bin_cap + p.slot) * 8;
     rc[0] = x[0];
     rc[1] = x[1];
     rc[2] = x[2];
