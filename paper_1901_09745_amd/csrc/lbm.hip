@@ -497,10 +497,10 @@ __global__ void __launch_bounds__(BLOCK)
       // x-face outlets: the velocity of the interior neighbour at this time
       // level, from the neighbour's lane of this wave
       double wu0 = 0.0, wu1 = 0.0, wu2 = 0.0;
-      if (a.outlet_wave) {
+      const int lane = (int)(threadIdx.x & 63);
+      if (a.outlet_wave && __any(x == 0 || x == d.nx - 1)) {
         C r_, j0, j1, j2;
         cell_moments<Q, SC>(g, r_, j0, j1, j2);
-        const int lane = (int)(threadIdx.x & 63);
         int src = lane;
         if ((a.outlet_wave & 1u) && x == 0) src = lane + 1;
         if ((a.outlet_wave & 2u) && x == d.nx - 1) src = lane - 1;
@@ -519,7 +519,8 @@ __global__ void __launch_bounds__(BLOCK)
         const bool on = f == 0 ? x == 0 : f == 1 ? x == d.nx - 1 : f == 2 ? y == 0
                       : f == 3 ? y == d.ny - 1 : f == 4 ? z == 0 : z == d.nz - 1;
         if (((a.outlet_mask >> f) & 1u) && on) {
-          if ((a.outlet_wave >> f) & 1u) {
+          // (a flat wave's first or last lane may have its neighbour in the next wave)
+          if (((a.outlet_wave >> f) & 1u) && !(FLAT && lane == (f == 0 ? SEG - 1 : 0))) {
             ub0 = wu0;
             ub1 = wu1;
             ub2 = wu2;
@@ -899,7 +900,8 @@ __device__ __forceinline__ size_t canonical_slot(const Dims& d, unsigned N, int 
 template <int Q, int PREC, int PAR>
 __global__ void __launch_bounds__(256) k_outlet_velocity(Geom g, const void* f, double fx,
                                                          double fy, double fz, double* out,
-                                                         long long stride, unsigned faces) {
+                                                         long long stride, unsigned faces,
+                                                         unsigned edges) {
   using L = Lattice<Q>;
   using ST = Store<PREC, Q>;
   using S = typename Form<PREC>::S;
@@ -918,6 +920,11 @@ __global__ void __launch_bounds__(256) k_outlet_velocity(Geom g, const void* f, 
     const int x = ax == 0 ? inner : a;
     const int y = ax == 0 ? a : ax == 1 ? inner : b;
     const int z = ax == 2 ? inner : b;
+    // edges: x faces whose cells take the velocity from the neighbour's lane but
+    // for those whose neighbour is in the next flat wave
+    if (((edges >> face) & 1u) &&
+        (((unsigned)(face ? d.nx - 1 : 0) + d.sy * (unsigned)y) % SEG) != (face ? 0u : SEG - 1u))
+      continue;
     const unsigned n = (unsigned)x + d.sy * (unsigned)y + d.sz * (unsigned)z;
     S v[Q];
 #pragma unroll
@@ -1335,7 +1342,8 @@ static StepArgs step_args(psclbm_ctx* c) {
     if (c->geom.face[f] == PSCLBM_MOVING_WALL) a.moving_mask |= 1u << f;
   }
   a.open_mask = a.inlet_mask | a.outlet_mask;
-  a.outlet_wave = outlet_wave_mask(c->geom, a.outlet_mask);
+  a.outlet_wave = c->geom.flat ? (c->geom.nx >= 2 ? a.outlet_mask & 3u : 0u)
+                               : outlet_wave_mask(c->geom, a.outlet_mask);
   a.original = c->cfg.weighting == PSCLBM_WEIGHT_ORIGINAL;
   a.dem_blocks = 0;
   std::memset(&a.dem, 0, sizeof(a.dem));
@@ -1344,19 +1352,22 @@ static StepArgs step_args(psclbm_ctx* c) {
   return a;
 }
 
-// Velocities of the outlet faces in `faces` from a state in storage form
-// `prec` at streaming parity `par`.
-static int outlet_velocity(psclbm_ctx* c, const void* f, int prec, int par, unsigned faces) {
+// Velocities of the outlets that the step does not take from its own lanes,
+// from a state in storage form `prec` at streaming parity `par`.
+static int outlet_velocity(psclbm_ctx* c, const void* f, int prec, int par, const StepArgs& a) {
   const double* F = c->cfg.body_force;
+  const unsigned edges = c->geom.flat ? a.outlet_wave : 0u;
+  const unsigned faces = (a.outlet_mask & ~a.outlet_wave) | edges;
+  if (!faces) return PSCLBM_OK;
   const dim3 grid((unsigned)grid_for(c->face_stride), (unsigned)__builtin_popcount(faces));
   if (par)
     PSCLBM_DISPATCH(c->geom.q, prec,
                     (k_outlet_velocity<Q, P, 1><<<grid, 256, 0, c->stream>>>(
-                        c->geom, f, F[0], F[1], F[2], c->outlet_u, c->face_stride, faces)));
+                        c->geom, f, F[0], F[1], F[2], c->outlet_u, c->face_stride, faces, edges)));
   else
     PSCLBM_DISPATCH(c->geom.q, prec,
                     (k_outlet_velocity<Q, P, 0><<<grid, 256, 0, c->stream>>>(
-                        c->geom, f, F[0], F[1], F[2], c->outlet_u, c->face_stride, faces)));
+                        c->geom, f, F[0], F[1], F[2], c->outlet_u, c->face_stride, faces, edges)));
   return hip_ok(hipGetLastError());
 }
 
@@ -1380,13 +1391,9 @@ int launch_step_contacts(psclbm_ctx* c, const DemArgs* dem, const double* x, con
     a.fc = c->fcontact;
   }
   // outlets whose neighbour is in another wave: velocities before the step
-  const unsigned separate = a.outlet_mask & ~a.outlet_wave;
-  if (separate) {
-    const int rc = outlet_velocity(c, c->f, c->prec, par, separate);
-    if (rc) return rc;
-  }
+  int rc = outlet_velocity(c, c->f, c->prec, par, a);
+  if (rc) return rc;
   const size_t lds = step_lds(c);
-  int rc;
   if (c->prec == PSCLBM_FP64)
     rc = dispatch_step_q<PSCLBM_FP64>(c, a, par, lds);
   else if (c->prec == PSCLBM_FP32)
@@ -1405,18 +1412,15 @@ int launch_recompute(psclbm_ctx* c, const double* f0, int nsteps, double* ring) 
   a.facc = nullptr;
   a.fzero = nullptr;
   a.mass_part = nullptr;
-  const unsigned separate = a.outlet_mask & ~a.outlet_wave;
   const size_t lds = step_lds(c);
   const size_t QN = (size_t)c->geom.q * (size_t)c->geom.N;
   for (int k = 0; k < nsteps; ++k) {
     const double* src = k == 0 ? f0 : ring + (size_t)(k - 1) * QN;
-    if (separate) {
-      const int rc = outlet_velocity(c, src, PSCLBM_FP64, 0, separate);
-      if (rc) return rc;
-    }
+    int rc = outlet_velocity(c, src, PSCLBM_FP64, 0, a);
+    if (rc) return rc;
     a.src = src;
     a.f = ring + (size_t)k * QN;
-    int rc = dispatch_step_q<PSCLBM_FP64>(c, a, 2, lds);
+    rc = dispatch_step_q<PSCLBM_FP64>(c, a, 2, lds);
     if (rc) return rc;
   }
   return PSCLBM_OK;
