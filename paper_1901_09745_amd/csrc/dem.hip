@@ -62,9 +62,10 @@ struct IntArgs {
 // force fc and contact torque tc (null: none): u += dt (F + fc + G)/m,
 // x += dt u, omega += dt (T + tc)/I, then the wrap into [0, L) on periodic
 // axes (kinematic: x += dt u only).
-__device__ inline void integrate_state(const IntArgs& p, double ri, const double* F,
-                                       const double* T, const double* fc, const double* tc,
-                                       double* x, double* u, double* w) {
+__device__ __forceinline__ void integrate_state(const IntArgs& p, double ri, const double* F,
+                                                const double* T, const double* fc,
+                                                const double* tc, double* x, double* u,
+                                                double* w) {
   const int D = p.three_d ? 3 : 2;
   if (!p.kinematic) {
     const double V = p.three_d ? (4.0 / 3.0) * M_PI * ri * ri * ri : M_PI * ri * ri;
@@ -157,6 +158,14 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
     us[a] = u[3 * i + a];
     ws[a] = w[3 * i + a];
   }
+  // the step's force and torque, loaded with the particle's state: an L2 latency
+  // that would otherwise follow the contacts
+  double fh[3], th[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    fh[a] = Ff[(size_t)ia.fstride * i + a];
+    th[a] = Tf[(size_t)ia.tstride * i + a];
+  }
   double fsum[3] = {0.0, 0.0, 0.0};
   double tsum[3] = {0.0, 0.0, 0.0};
   if constexpr (GATHER) {
@@ -167,8 +176,7 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
 #pragma unroll
     for (int a = 0; a < 3; ++a) fsum[a] = fc_in[3 * i + a];
   }
-  integrate_state(ia, ri, Ff + (size_t)ia.fstride * i, Tf + (size_t)ia.tstride * i, fsum,
-                  FRIC ? tsum : nullptr, xs, us, ws);
+  integrate_state(ia, ri, fh, th, fsum, FRIC ? tsum : nullptr, xs, us, ws);
   if (lane == 0) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {

@@ -248,6 +248,10 @@ __device__ inline void dem_contact_wave(const DemArgs& d, int i, int lane, const
                                         const FricArgs* fr = nullptr, const double* ws = nullptr,
                                         double* tsum = nullptr) {
   const int D = d.three_d ? 3 : 2;
+  // the previous contact list, one entry per lane (max_contacts <= 64): its
+  // loads start before the particle's own are waited for
+  const int pn_load = d.prev_n[i];
+  const int pid = lane < d.max_contacts ? d.prev_id[(size_t)i * d.max_contacts + lane] : 0;
   // the particle's own values are the same in every lane (scalar registers)
   const double ri = wave_uniform(r_i);
   const double xi0 = wave_uniform(xs[0]), xi1 = wave_uniform(xs[1]);
@@ -262,9 +266,7 @@ __device__ inline void dem_contact_wave(const DemArgs& d, int i, int lane, const
       wi1 = wave_uniform(ws[1]);
     }
   }
-  // the previous contact list, one entry per lane (max_contacts <= 64)
-  const int pn = __builtin_amdgcn_readfirstlane(d.prev_n[i]);
-  const int pid = lane < d.max_contacts ? d.prev_id[(size_t)i * d.max_contacts + lane] : 0;
+  const int pn = __builtin_amdgcn_readfirstlane(pn_load);
   // the position of id in the previous list, or -1
   auto prev_slot = [&](int id) {
     int at = -1;
