@@ -312,6 +312,27 @@ int scratch_address(void** out) {
   return PSCLBM_OK;
 }
 
+// Two runs of ints in one launch: a contact list's counts and its ids, which
+// two runtime copies took one after another (4 us each on the GPU, a reverse
+// pass makes four a step).
+__global__ void __launch_bounds__(256) k_copy_lists(const int* n_src, int* n_dst, long long np,
+                                                    const int* id_src, int* id_dst,
+                                                    long long nid) {
+  for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < np + nid;
+       k += (long long)gridDim.x * 256) {
+    if (k < np) n_dst[k] = n_src[k];
+    else id_dst[k - np] = id_src[k - np];
+  }
+}
+
+int copy_lists(psclbm_ctx* c, const int* n_src, int* n_dst, const int* id_src, int* id_dst) {
+  const long long np = c->cfg.max_particles, nid = np * c->cfg.max_contacts;
+  const long long blocks = (np + nid + 255) / 256;
+  k_copy_lists<<<(unsigned)(blocks < 4096 ? blocks : 4096), 256, 0, c->stream>>>(
+      n_src, n_dst, np, id_src, id_dst, nid);
+  return hip_ok(hipGetLastError());
+}
+
 __global__ void k_zero_words(unsigned* p, long long n) {
   for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < n;
        k += (long long)gridDim.x * blockDim.x)
@@ -539,27 +560,16 @@ int dem_reset_contacts(psclbm_ctx* ctx) {
 
 int dem_get_contacts(psclbm_ctx* ctx, int* d_count, int* d_ids) {
   if (!ctx || !d_count || !d_ids) return PSCLBM_EINVAL;
-  const size_t np = (size_t)ctx->cfg.max_particles;
-  if (np == 0) return PSCLBM_OK;
-  const size_t mc = (size_t)ctx->cfg.max_contacts;
-  int rc = hip_ok(hipMemcpyAsync(d_count, ctx->contact_n[ctx->contact_cur], sizeof(int) * np,
-                                 hipMemcpyDeviceToDevice, ctx->stream));
-  if (!rc)
-    rc = hip_ok(hipMemcpyAsync(d_ids, ctx->contact_id[ctx->contact_cur], sizeof(int) * np * mc,
-                               hipMemcpyDeviceToDevice, ctx->stream));
-  return rc;
+  if (ctx->cfg.max_particles == 0) return PSCLBM_OK;
+  return copy_lists(ctx, ctx->contact_n[ctx->contact_cur], d_count,
+                    ctx->contact_id[ctx->contact_cur], d_ids);
 }
 
 int dem_set_contacts(psclbm_ctx* ctx, const int* d_count, const int* d_ids) {
   if (!ctx || !d_count || !d_ids) return PSCLBM_EINVAL;
-  const size_t np = (size_t)ctx->cfg.max_particles;
-  if (np == 0) return PSCLBM_OK;
-  const size_t mc = (size_t)ctx->cfg.max_contacts;
-  int rc = hip_ok(hipMemcpyAsync(ctx->contact_n[ctx->contact_cur], d_count, sizeof(int) * np,
-                                 hipMemcpyDeviceToDevice, ctx->stream));
-  if (!rc)
-    rc = hip_ok(hipMemcpyAsync(ctx->contact_id[ctx->contact_cur], d_ids, sizeof(int) * np * mc,
-                               hipMemcpyDeviceToDevice, ctx->stream));
+  if (ctx->cfg.max_particles == 0) return PSCLBM_OK;
+  const int rc = copy_lists(ctx, d_count, ctx->contact_n[ctx->contact_cur], d_ids,
+                            ctx->contact_id[ctx->contact_cur]);
   ctx->springs_valid = 0;  // springs are not part of the saved lists
   return rc;
 }
