@@ -48,23 +48,22 @@ class PscDrag(torch.autograd.Function):
         P.psc_rasterize(G.ctx, xs, us, ws, rs)
         k = max(1, min(checkpoint_every, steps))
         checkpoints = []
-        Fsum = torch.zeros((n, 3), dtype=torch.float64, device=dev)
-        Tsum = torch.zeros_like(Fsum)
-        Ft, Tt = torch.zeros_like(Fsum), torch.zeros_like(Fsum)
+        total = torch.zeros((2, n, 3), dtype=torch.float64, device=dev)
+        now = torch.zeros_like(total)
+        Ft, Tt = now  # of one step; both are added to the total in one launch
         for t in range(steps):
             if t % k == 0:
                 checkpoints.append(G.get_f())
             G.step(1)
             if t >= steps - window and n > 0:
                 P.particle_forces(G.ctx, Ft, Tt)
-                Fsum += Ft
-                Tsum += Tt
+                total += now
         G.sync()
         ctx.G = G
         ctx.checkpoints = checkpoints
         ctx.meta = (steps, k, window, n)
         ctx.particles = (xs, us, ws, rs)
-        return Fsum, Tsum
+        return total[0].clone(), total[1].clone()
 
     @staticmethod
     def backward(ctx, gF, gT):
