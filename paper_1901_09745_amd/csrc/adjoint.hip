@@ -98,9 +98,7 @@ __global__ void __launch_bounds__(BLOCK)
   const bool active = (int)(threadIdx.x & 63) <= wc.last;
   const unsigned N = (unsigned)G.N;
   const Dims d = dims_of(G);
-  const bool any = wc.last >= 0;
-  const CellLinks<Q, WALLS, FLAT> lk(d, active ? x : any ? wc.x0 : 0,
-                                     active ? y : any ? wc.y0 : 0, any ? z : 0);
+  const CellLinks<Q, WALLS, FLAT> lk(d, x, y, z);
   const unsigned n = lk.n;
 
   // The sensitivity of each post-collision population, read where it streams
@@ -136,7 +134,7 @@ __global__ void __launch_bounds__(BLOCK)
   s.n = 0;
   if (cnt > 0) collect_slots<D, FLAT>(G, wc, active, lds, cnt, a.h, s, nullptr, slot_lds);
 
-  // from here on every lane computes (those without a cell the wave's first
+  // from here on every lane computes (those without a cell the wave's last
   // one, without slots and without output), so that lanes can exchange values
   {
     const double rho0 = G.rho0;

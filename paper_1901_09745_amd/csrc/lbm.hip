@@ -326,11 +326,11 @@ __global__ void __launch_bounds__(BLOCK)
   // EARLY_LOADS names, after it in the others ----
   S raw[Q];
   auto load = [&] {
-    // (lanes without a cell read the wave's first: no branch, so that the
-    // number of loads under way is known when the list's ids are waited for)
-    const bool any = wc.last >= 0;
-    const CellLinks<Q, WALLS, FLAT> lk(d, active ? x : any ? wc.x0 : 0,
-                                       active ? y : any ? wc.y0 : 0, any ? z : 0);
+    // (lanes without a cell load too: no branch, so that the number of loads
+    // under way is known when the list's ids are waited for; lane_cell has
+    // their cell in range, at x0 again in walled rows, where the select costs
+    // fewer registers than the lane's minimum kept: 4 spilled, not 8)
+    const CellLinks<Q, WALLS, FLAT> lk(d, WALLS && !FLAT && !active ? wc.x0 : x, y, z);
     if constexpr (PAR == 1) {
       if (lk.inner) {
 #pragma unroll
@@ -486,12 +486,11 @@ __global__ void __launch_bounds__(BLOCK)
   // walls, the moments' registers cost spills of loaded populations)
   constexpr bool FOLD = D == 3 && PREC != PSCLBM_FP64 && !WALLS;
   // no body force: the Guo terms vanish (uniform over the launch)
-  const bool forced = __builtin_amdgcn_readfirstlane(
-                          (int)(a.force[0] != 0.0 || a.force[1] != 0.0 || a.force[2] != 0.0)) != 0;
+  const bool forced = a.forced != 0;
 
   if (active) {
     // ---- inlet / outlet layers: reset to an equilibrium before collision ----
-    if (a.open_mask) {
+    if (WALLS && a.open_mask) {
       bool reset = false;
       double ub0 = 0.0, ub1 = 0.0, ub2 = 0.0;
       // x-face outlets: the velocity of the interior neighbour at this time
@@ -1331,6 +1330,7 @@ static StepArgs step_args(psclbm_ctx* c) {
   a.omega = 1.0 / c->cfg.tau;
   a.inv_rho0 = 1.0 / c->geom.rho0;
   for (int k = 0; k < 3; ++k) a.force_f[k] = (float)a.force[k];
+  a.forced = a.force[0] != 0.0 || a.force[1] != 0.0 || a.force[2] != 0.0;
   a.omega_f = (float)a.omega;
   a.inv_rho0_f = (float)a.inv_rho0;
   a.rho0_f = (float)c->geom.rho0;

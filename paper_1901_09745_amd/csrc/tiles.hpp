@@ -389,16 +389,20 @@ __device__ inline WaveCells<FLAT> wave_cells(const Geom& g, int tile) {
     const int left = g.nx - c.x0;
     c.last = c.y0 < g.ny && c.z < g.nz ? (left < SEG ? left : SEG) - 1 : -1;
   }
+  if (c.last < 0) c.x0 = c.y0 = c.z = 0;  // no cell: the lattice's first, for its loads
   return c;
 }
 
-// The calling lane's cell (when lane <= c.last).
+// The calling lane's cell; a lane past c.last, which has none, takes the last
+// lane's (the first when there is no cell at all), so that its loads are in
+// range.
 struct LaneCell {
   int x, y;
 };
 template <bool FLAT>
 __device__ __forceinline__ LaneCell lane_cell(const Geom& g, const WaveCells<FLAT>& c) {
-  const int t = c.x0 + (int)(threadIdx.x & 63);
+  const int lane = (int)(threadIdx.x & 63), last = c.last > 0 ? c.last : 0;
+  const int t = c.x0 + (lane < last ? lane : last);
   LaneCell l;
   l.x = t;
   l.y = c.y0;
