@@ -480,7 +480,7 @@ int lbm_step(psclbm_ctx* ctx, int nsteps) {
   if (!ctx || nsteps < 1) return PSCLBM_EINVAL;
   if (!ctx->rasterized) return PSCLBM_ESTATE;
   for (int k = 0; k < nsteps; ++k) {
-    int rc = launch_step(ctx);
+    int rc = launch_step(ctx, k == nsteps - 1);
     if (rc) return rc;
   }
   return PSCLBM_OK;

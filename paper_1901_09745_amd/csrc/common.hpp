@@ -392,12 +392,12 @@ int launch_read_forces(psclbm_ctx* c, double* force, double* torque);
 int launch_rasterize(psclbm_ctx* c, const psclbm_particles* p, bool dem_bins);
 // The step with the contact workgroups of dem (the DEM contact forces of the
 // step's start into fcontact); dem null: the plain step.
-int launch_step_contacts(psclbm_ctx* c, const DemArgs* dem, const double* x, const double* u,
-                         const double* r);
+int launch_step_contacts(psclbm_ctx* c, bool mass, const DemArgs* dem, const double* x,
+                         const double* u, const double* r);
 int launch_coupled(psclbm_ctx* c, const psclbm_dem_params* prm, double* x, double* u, double* w,
                    const double* r, int n, int nsteps);
 int launch_solid_fraction(psclbm_ctx* c, double* eps, int* ids, double* seps, int k);
-int launch_step(psclbm_ctx* c);
+int launch_step(psclbm_ctx* c, bool mass);
 int launch_recompute(psclbm_ctx* c, const double* f0, int nsteps, double* ring);
 int launch_mass(psclbm_ctx* c, double* h_mass);
 int launch_zero(psclbm_ctx* c, void* p, size_t bytes);

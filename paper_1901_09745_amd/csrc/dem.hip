@@ -403,7 +403,7 @@ int launch_coupled(psclbm_ctx* c, const psclbm_dem_params* prm, double* x, doubl
     for (int t = 0; t < nsteps; ++t) {
       int rc = launch_rasterize(c, p, false);
       if (!rc) c->np = n;
-      if (!rc) rc = launch_step(c);
+      if (!rc) rc = launch_step(c, t == nsteps - 1);
       if (rc) return rc;
     }
     return PSCLBM_OK;
@@ -424,7 +424,8 @@ int launch_coupled(psclbm_ctx* c, const psclbm_dem_params* prm, double* x, doubl
   for (int t = 0; t < nsteps; ++t) {
     // the step, with the contact workgroups on the binning of its start
     const DemArgs d0 = dem_args(c, prm, n, E);
-    rc = own_contacts ? launch_step(c) : launch_step_contacts(c, &d0, x, u, r);
+    const bool mass = t == nsteps - 1;
+    rc = own_contacts ? launch_step(c, mass) : launch_step_contacts(c, mass, &d0, x, u, r);
     if (rc) return rc;
     const double* F = nullptr;
     const double* T = nullptr;

@@ -197,23 +197,18 @@ struct Store {
       return static_cast<float>(v);
     }
   }
-  // stores deviation g of direction i (g / w_i in the scaled form); returns
-  // the deviation memory now holds in FP64 (exactly, and in the FP16 form to
+  // deviation g of direction i (g / w_i in the scaled form) as stored
+  __device__ static S stored(int i, C g, double rho0) {
+    if constexpr (PREC == PSCLBM_FP64) return Lattice<Q>::w(i) * rho0 + g;
+    else return static_cast<S>(g);
+  }
+  // the deviation memory then holds, in FP64 (exactly, and in the FP16 form to
   // the rounding of h w_i: the per-cell part of the mass sum)
-  template <bool NT = false>
-  __device__ static double st(S* b, unsigned e, int i, C g, double rho0) {
-    if constexpr (PREC == PSCLBM_FP64) {
-      const double f = Lattice<Q>::w(i) * rho0 + g;
-      elem_st<NT>(b, e, f);
-      return f - Lattice<Q>::w(i) * rho0;
-    } else if constexpr (PREC == PSCLBM_FP32) {
-      elem_st<NT>(b, e, g);
-      return static_cast<double>(g);
-    } else {
-      const _Float16 h = static_cast<_Float16>(g);
-      elem_st<NT>(b, e, h);
-      return static_cast<double>(static_cast<float>(h)) * Lattice<Q>::w(i);
-    }
+  __device__ static double held(int i, C g, double rho0) {
+    const S v = stored(i, g, rho0);
+    if constexpr (PREC == PSCLBM_FP64) return v - Lattice<Q>::w(i) * rho0;
+    else if constexpr (PREC == PSCLBM_FP32) return static_cast<double>(v);
+    else return static_cast<double>(static_cast<float>(v)) * Lattice<Q>::w(i);
   }
   // Exact canonical FP64 value of stored population i.
   __device__ static double to_f64(const S* a, size_t idx, int i, double rho0) {
@@ -351,7 +346,6 @@ __global__ void __launch_bounds__(BLOCK)
   const int cnt = load_tile_list(a.tile_count, a.tile_list, a.cap, a.snap, tile, lds, acc, a.np,
                                  [&] { if constexpr (EARLY) load(); });
   const double rho0 = a.g.rho0;
-  double mass_dev = 0.0;
   // ---- solid fractions of the covering particles (Table 1), whole wave; in
   // 3D after the loads of f are issued, so that their latency overlaps the
   // slot search (in 2D the registers this holds cost more than it saves) ----
@@ -822,30 +816,33 @@ __global__ void __launch_bounds__(BLOCK)
         }
       }
     }
-    double cell_dev = 0.0;  // FP64 sum of the stored deviations, in every form
     if constexpr (PAR == 0) {  // own cell, opposite slot
       const unsigned no = (unsigned)xo + d.sy * (unsigned)y + d.sz * (unsigned)z;
 #pragma unroll
       for (int i = 0; i < Q; ++i)
-        cell_dev += ST::template st<NT>(dir_ptr(A, L::opp(i), N), no, i, g[i], rho0);
+        elem_st<NT>(dir_ptr(A, L::opp(i), N), no, ST::stored(i, g[i], rho0));
     } else {
       const CellLinks<Q, WALLS, FLAT> lk(d, xo, y, z);
       if (lk.inner) {
 #pragma unroll
         for (int i = 0; i < Q; ++i)
-          cell_dev += ST::st(A + (size_t)i * N + (ptrdiff_t)lk.row_part(i), lk.lane_part(i), i,
-                             g[i], rho0);
+          elem_st<false>(A + (size_t)i * N + (ptrdiff_t)lk.row_part(i), lk.lane_part(i),
+                         ST::stored(i, g[i], rho0));
       } else {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) cell_dev += ST::st(lk.at(A, N, i), 0u, i, g[i], rho0);
+        for (int i = 0; i < Q; ++i) *lk.at(A, N, i) = ST::stored(i, g[i], rho0);
       }
     }
-    mass_dev = cell_dev;
   }
 
-  // ---- per-workgroup FP64 mass partial (sum of the stored deviations) ----
+  // ---- per-workgroup FP64 mass partial (sum of the stored deviations), after
+  // the last step of a call ----
   __shared__ double wsum[BLOCK / 64];
   if (a.mass_part) {
+    double mass_dev = 0.0;
+    if (active)
+#pragma unroll
+      for (int i = 0; i < Q; ++i) mass_dev += ST::held(i, g[i], rho0);
     mass_dev = wave_sum(mass_dev);
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = mass_dev;
   }
@@ -1376,12 +1373,20 @@ static size_t step_lds(const psclbm_ctx* c) {
                    : 0;
 }
 
-int launch_step(psclbm_ctx* c) { return launch_step_contacts(c, nullptr, nullptr, nullptr, nullptr); }
+int launch_step(psclbm_ctx* c, bool mass) {
+  return launch_step_contacts(c, mass, nullptr, nullptr, nullptr, nullptr);
+}
 
-int launch_step_contacts(psclbm_ctx* c, const DemArgs* dem, const double* x, const double* u,
-                         const double* r) {
+// mass: the state is the call's result, so its mass partials are formed.  The
+// partials of the steps before it were overwritten unread; without their
+// conversions and FP64 sums (57 of some 730 vector instructions a wave in the
+// FP16 form) a step takes 339, not 352 us (FP16 spheres, 256^3), 54.2, not
+// 55.4 (FP32 open box 200x100x100), 21.3, not 22.0 (FP32 disks, 1024^2).
+int launch_step_contacts(psclbm_ctx* c, bool mass, const DemArgs* dem, const double* x,
+                         const double* u, const double* r) {
   const int par = (int)(c->steps & 1);
   StepArgs a = step_args(c);
+  if (!mass) a.mass_part = nullptr;
   if (dem && dem->n > 0) {
     a.dem_blocks = ((dem->n + BLOCK / 64 - 1) / (BLOCK / 64) + 7) / 8 * 8;
     a.dem = *dem;
@@ -1403,7 +1408,7 @@ int launch_step_contacts(psclbm_ctx* c, const DemArgs* dem, const double* x, con
   if (rc) return rc;
   c->force_buf ^= 1;
   c->steps += 1;
-  c->mass_valid = 1;
+  c->mass_valid = mass;
   return PSCLBM_OK;
 }
 

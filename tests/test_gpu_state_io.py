@@ -73,3 +73,33 @@ def test_force_rows_alone_and_together(n):
         out = torch.full((n, 3), 7.0, dtype=torch.float64, device="cuda")
         P.particle_forces(G.ctx, *((out, None) if k == 0 else (None, out)))
         assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("chunks", [(1,), (2,), (1, 3, 2)])
+@pytest.mark.parametrize("path", ["step", "coupled", "coupled_empty"])
+@pytest.mark.parametrize("form", ["fp64", "fp32", "fp16"])
+def test_mass_is_the_sum_of_the_state(form, path, chunks):
+    """The mass partials that a call's last step forms describe the state it
+    leaves.  Tolerance: the sum of the state exactly; the device's is a tree of
+    about 40 roundings of deviations below rho0, and one of each population."""
+    import math
+    import torch
+    import paper_1901_09745_amd.psclbm as P
+    lat = W.LatticeSpec(q=19, nx=9, ny=17, nz=13, tau=0.7, force=(1e-4, 0, 0),
+                        faces=("periodic",) * 2 + ("bounce_back",) * 2 + ("periodic",) * 2)
+    n = 0 if path == "coupled_empty" else 1
+    x, u = np.full((n, 3), [4.2, 8.3, 6.1]), np.full((n, 3), [0.01, 0.0, 0.02])
+    dp = P.DeviceParticles(x, u, np.zeros((n, 3)), np.full(n, 3.0))
+    prm = P.make_dem_params(W.DemSpec(E_p=1e-3, eta_n=0.05, n_sub=1, kinematic=True))
+    _print_case(test="mass", form=form, path=path, chunks=chunks)
+    G = gpu_lattice(lat, W.Particles(x, u, np.zeros((n, 3)), np.full(n, 3.0)), form)
+    G.set_f(torch.from_numpy(W.random_state(lat, 8)).cuda())
+    G.rasterize(dp)
+    for k in chunks:
+        if path == "step":
+            G.step(k)
+        else:
+            G.coupled_step(prm, dp, k)
+        m = G.mass()
+        ref = math.fsum(G.get_f().cpu().numpy().ravel().tolist())
+        assert abs(m - ref) <= 64 * 2.0 ** -53 * ref
