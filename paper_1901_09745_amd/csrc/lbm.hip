@@ -724,7 +724,7 @@ __global__ void __launch_bounds__(BLOCK)
     }
   }
 
-  // ---- pass 2 (covered cells of the other forms): sum_s B_s [f^eq_i(rho,
+  // ---- second pass (covered cells of the other forms): sum_s B_s [f^eq_i(rho,
   // u_s) - f^eq_i(rho, u)] and the momentum exchange ----
   if constexpr (!FOLD) {
     // slot k of this cell: the equilibrium difference into g and, unless the
