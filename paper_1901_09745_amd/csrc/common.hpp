@@ -175,10 +175,11 @@ struct StepArgs {
   int forced;              // a body force acts
   int original;            // original weighting (Eqs. 7-9, 11) instead of Eqs. 12-14
   const void* src;         // ring step: canonical FP64 state read (f is written)
-  // coupled step: the leading dem_blocks workgroups gather the DEM contacts
-  // of four particles each (positions px, velocities pu, radii pr at the
-  // start of the step) into fc [n][3]; the tiles follow
+  // coupled step: dem_blocks workgroups (a multiple of 8) gather the DEM
+  // contacts of four particles each (positions px, velocities pu, radii pr at
+  // the start of the step) into fc [n][3], before or among those of the tiles
   int dem_blocks;
+  int dem_shift;           // and their spread among the tiles (ContactBlocks)
   DemArgs dem;
   const double* px;
   const double* pu;

@@ -258,6 +258,43 @@ constexpr int step_waves() {
 template <int Q, int PREC, bool WALLS>
 constexpr bool EARLY_LOADS = Q == 19 && PREC == PSCLBM_FP64 && !WALLS;
 
+// Where the contact workgroups stand among the tiles.  Their waves wait on
+// chains of scattered loads; as the grid's first workgroups they have the chip
+// to themselves, and memory idle, for some 25 us (20,000 spheres).  The 3D
+// FP64 and FP32 forms, whose lattices leave issue slots free, spread them:
+// groups of 8 workgroups (one an XCD, so that the round robin of the tile
+// workgroups is that of their own index), one in 2^shift, the largest power
+// with which they end before the grid does.  384x192x192 with 20,000 spheres:
+// FP64 867 -> 854 us a coupled step, FP32 452 -> 443.  The FP16 form (352 ->
+// 355), bound by issue, and 2D (28.1 -> 28.6) keep them first, and so do grids
+// below SPREAD_TILES, 16 tiles a CU: 6912 tiles gain 1 % in both forms, 2048
+// lose 0.7 % in FP32.
+constexpr int SPREAD_TILES = 4096;
+template <int Q, int PREC>
+constexpr bool SPREAD_CONTACTS = Q == 19 && PREC != PSCLBM_FP32_FP16STORE;
+
+template <bool SPREAD>
+struct ContactBlocks {
+  int groups, shift, g;  // groups of 8; the calling workgroup's group
+  __device__ __forceinline__ ContactBlocks(int blocks, int s)
+      : groups(blocks >> 3), shift(SPREAD ? s : 0), g((int)blockIdx.x >> 3) {}
+  // the calling workgroup is a contact workgroup, and its index among them
+  __device__ __forceinline__ bool contact() const {
+    if constexpr (!SPREAD) return g < groups;
+    return (g & ((1 << shift) - 1)) == 0 && (g >> shift) < groups;
+  }
+  __device__ __forceinline__ int index() const {
+    if constexpr (!SPREAD) return (int)blockIdx.x;
+    return ((g >> shift) << 3) + (int)(blockIdx.x & 7);
+  }
+  // contact workgroups before a tile workgroup
+  __device__ __forceinline__ int before() const {
+    if constexpr (!SPREAD) return 8 * groups;
+    const int n = (g + (1 << shift) - 1) >> shift;
+    return 8 * (n < groups ? n : groups);
+  }
+};
+
 // NT: the accesses to the own cell's slots (the even step's, and the ring
 // step's loads), each line by one wave, are streamed with non-temporal hints.
 template <int Q, int PREC, int PAR, bool WALLS, bool FLAT, bool NT = false>
@@ -276,10 +313,11 @@ __global__ void __launch_bounds__(BLOCK)
   constexpr bool EARLY = EARLY_LOADS<Q, PREC, WALLS>;
   extern __shared__ double smem_d[];
   __shared__ SlotLdsT<E> slot_lds;
-  if ((int)blockIdx.x < a.dem_blocks) {
+  const ContactBlocks<SPREAD_CONTACTS<Q, PREC>> cbs(a.dem_blocks, a.dem_shift);
+  if (cbs.contact()) {
     // contact workgroup of the coupled step: one wave per particle gathers
     // its DEM contact force from the binning of the step's start
-    const int i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (BLOCK / 64) + threadIdx.x / 64));
+    const int i = __builtin_amdgcn_readfirstlane((int)(cbs.index() * (BLOCK / 64) + threadIdx.x / 64));
     if (i < a.dem.n) {
       const int lane = (int)(threadIdx.x & 63);
       double xs[3], us[3], fs[3];
@@ -299,10 +337,9 @@ __global__ void __launch_bounds__(BLOCK)
     return;
   }
   S* __restrict__ A = static_cast<S*>(a.f);
-  // the tiles: workgroups dem_blocks.. (a multiple of 8, so that the XCD
-  // round robin of the tile workgroups is that of their own index)
+  // the tiles: the other workgroups
   const int nb = (int)gridDim.x - a.dem_blocks;
-  const int bid = (int)blockIdx.x - a.dem_blocks;
+  const int bid = (int)blockIdx.x - cbs.before();
   const int tile = tile_of(a.g, bid, nb);
 
   // particle list of the tile (LDS) and its force accumulators
@@ -1342,7 +1379,7 @@ static StepArgs step_args(psclbm_ctx* c) {
   a.outlet_wave = c->geom.flat ? (c->geom.nx >= 2 ? a.outlet_mask & 3u : 0u)
                                : outlet_wave_mask(c->geom, a.outlet_mask);
   a.original = c->cfg.weighting == PSCLBM_WEIGHT_ORIGINAL;
-  a.dem_blocks = 0;
+  a.dem_blocks = a.dem_shift = 0;
   std::memset(&a.dem, 0, sizeof(a.dem));
   a.px = a.pu = a.pr = nullptr;
   a.fc = nullptr;
@@ -1389,6 +1426,9 @@ int launch_step_contacts(psclbm_ctx* c, bool mass, const DemArgs* dem, const dou
   if (!mass) a.mass_part = nullptr;
   if (dem && dem->n > 0) {
     a.dem_blocks = ((dem->n + BLOCK / 64 - 1) / (BLOCK / 64) + 7) / 8 * 8;
+    if (c->ntiles >= SPREAD_TILES)
+      while (((long long)a.dem_blocks << (a.dem_shift + 1)) <= (c->ntiles + a.dem_blocks) / 8 * 8)
+        ++a.dem_shift;
     a.dem = *dem;
     a.px = x;
     a.pu = u;
