@@ -217,8 +217,10 @@ struct Store {
     } else if constexpr (PREC == PSCLBM_FP32) {
       return Lattice<Q>::w(i) * rho0 + static_cast<double>(a[idx]);
     } else {
-      return Lattice<Q>::w(i) * rho0 +
-             static_cast<double>(static_cast<float>(a[idx])) * Lattice<Q>::w(i);
+      // h w added to w rho0 in one rounding (left to the compiler, the rest
+      // population's w rho0 was the fused product and h w rounded by itself)
+      return fma(static_cast<double>(static_cast<float>(a[idx])), Lattice<Q>::w(i),
+                 Lattice<Q>::w(i) * rho0);
     }
   }
   __device__ static void from_f64(S* a, size_t idx, int i, double f, double rho0) {
