@@ -651,12 +651,18 @@ __global__ void __launch_bounds__(BLOCK)
     const C omB = (C)1 - Bn;
     const C relax = omB * omega;
 
-    // ---- the slots (FOLD): the moments A = sum_s B_s (u_s - u) and the
-    // symmetric M = sum_s B_s (u_s u_s - u u) (diagonal in mD, off-diagonal
-    // doubled in mH, formed as B_s [(u_s - u)(u_s + u)^T + transpose] / 2), and
-    // the momentum exchange ----
-    C mA[3] = {0, 0, 0}, mD[3] = {0, 0, 0}, mH[3] = {0, 0, 0};
+    // The weights multiply each direction's own sum (the FP32 forms' split
+    // product, wmul): formed once per cell and shared by the directions, with
+    // opposite pairs relaxed in their sums and differences, the same terms took
+    // 1-3 % less time but correlated the cell's equilibrium errors over its
+    // directions (FP32 open box with a sphere: velocity error 4.03e-7 -> 4.29e-7
+    // against FP64, torque errors of single placements doubled).
     if constexpr (FOLD) {
+      // ---- the slots: the moments A = sum_s B_s (u_s - u) and the symmetric
+      // M = sum_s B_s (u_s u_s - u u) (diagonal in mD, off-diagonal doubled
+      // in mH, formed as B_s [(u_s - u)(u_s + u)^T + transpose] / 2), and the
+      // momentum exchange ----
+      C mA[3] = {0, 0, 0}, mD[3] = {0, 0, 0}, mH[3] = {0, 0, 0};
       if (s.n > 0) {
 #pragma unroll
         for (int k = 0; k < KSLOTS; ++k) {
@@ -679,91 +685,95 @@ __global__ void __launch_bounds__(BLOCK)
           }
         }
       }
-    }
-    // ---- one pass over the opposite pairs, in their sum S = g_i + g_-i and
-    // difference A = g_i - g_-i.  With f^eq_i = w_i (sym +- ant), sym = drho +
-    // rho (4.5 (e.u)^2 - 1.5 u^2) and ant = 3 rho e.u, the non-equilibrium
-    // parts are Fs = S - 2 w_i sym and Fa = A - 2 w_i ant, and BGK weighted by
-    // 1 - B_n plus the bounce-back B_n (fneq_-i - fneq_i) (Eqs. 2, 10, 12) is
-    //   dS = -relax / 2 Fs,  dA = -(relax + 2 B_n) / 2 Fa,
-    //   g_i += dS + dA,  g_-i += dS - dA:
-    // 12 operations a pair against 23 (FP32) and 15 (scaled) for the two
-    // directions apart, and the increments stay explicit, so an equilibrium is
-    // kept exactly.  Folded, the particles' sum_s B_s [f^eq_i(rho, u_s) -
-    // f^eq_i(rho, u)], which is w_i rho [3 e.A + 4.5 e.M.e - 1.5 tr M], adds its
-    // even and odd parts to dS and dA.  The
-    // weights enter once per cell: w_i = wd times 1 (diagonals) or AX (axes,
-    // a power of two), with wd split as in wmul. ----
-    constexpr int diag = Q == 9 ? 5 : 7;
-    constexpr int AX = SC ? 1 : (Q == 9 ? 4 : 2);
-    const C r3 = (C)3 * rho, r45 = (C)4.5 * rho;
-    const C c0 = drho - (C)1.5 * rho * uu;
-    const C k0 = wq<Q, SC>(diag, (C)2 * c0), k45 = wq<Q, SC>(diag, (C)2 * r45),
-            k3 = wq<Q, SC>(diag, (C)2 * r3);
-    const C hs = (C)-0.5 * relax, ha = hs - Bn;
-    C pA[3], pD[3], pH[3], p0 = 0;  // the particles' moments, times wd
-    if constexpr (FOLD) {
-      const C w3 = wq<Q, SC>(diag, r3), w45 = wq<Q, SC>(diag, r45);
+      // ---- one pass over the directions: BGK + Guo weighted by 1 - B_n, the
+      // bounce-back of the non-equilibrium part, B_n (fneq_{-i} - fneq_i), and
+      // the particles' sum_s B_s [f^eq_i(rho, u_s) - f^eq_i(rho, u)], which is
+      // w_i rho [3 e_i.A + 4.5 e_i.M.e_i - 1.5 tr M] (Eqs. 2-4, 10-12) ----
+      const C r3 = (C)3 * rho, r45 = (C)4.5 * rho;
+      const C pA[3] = {r3 * mA[0], r3 * mA[1], r3 * mA[2]};
+      const C pD[3] = {r45 * mD[0], r45 * mD[1], r45 * mD[2]};
+      const C pH[3] = {r45 * mH[0], r45 * mH[1], r45 * mH[2]};
+      const C p0 = (C)-1.5 * rho * (mD[0] + mD[1] + mD[2]);
+      auto collide = [&](auto guo) {
+        constexpr bool GUO = decltype(guo)::value;
+        // (opaque: what the two copies share is not hoisted above the branch,
+        // where it spilled 2-6 registers: 256^3 FP16 8.05 -> 7.79 ms in 20 steps)
+        C vx = ux, vy = uy, vz = uz;
+        asm volatile("" : "+v"(vx), "+v"(vy), "+v"(vz));
+        const C gk = omB * kguo;
+        // g_i - relax fneq_i + B_n (fneq_-i - fneq_i) as g_i - (relax + B_n)
+        // fneq_i + B_n fneq_-i: the non-equilibrium parts stay explicit, so an
+        // equilibrium is kept exactly (no rounding of 1 - relax - B_n enters)
+        const C rB = relax + Bn;
+        {
+          C x0 = p0;
+          if constexpr (GUO) x0 -= gk * (C)3 * uF;
+          const C fneq = g[0] - wq<Q, SC>(0, drho - rho * (C)1.5 * uu);
+          g[0] = g[0] - relax * fneq + wq<Q, SC>(0, x0);
+        }
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        pA[c] = w3 * mA[c];
-        pD[c] = w45 * mD[c];
-        pH[c] = w45 * mH[c];
+        for (int i = 1; i < Q; ++i) {
+          const int o = L::opp(i);
+          if (o < i) continue;
+          const int ex = L::ex(i), ey = L::ey(i), ez = L::ez(i);
+          const C eu = edot(ex, ey, ez, vx, vy, vz);
+          const C sym = drho + rho * ((C)4.5 * eu * eu - (C)1.5 * uu);
+          const C fn_i = g[i] - wq<Q, SC>(i, sym + rho * (C)3 * eu);
+          const C fn_o = g[o] - wq<Q, SC>(i, sym - rho * (C)3 * eu);
+          // the even and odd parts under e -> -e of the particles' term and
+          // of the Guo term (Eq. 4)
+          C ps = p0;
+          eacc(ex * ex, ps, pD[0]);
+          eacc(ey * ey, ps, pD[1]);
+          eacc(ez * ez, ps, pD[2]);
+          eacc(ex * ey, ps, pH[0]);
+          eacc(ex * ez, ps, pH[1]);
+          eacc(ey * ez, ps, pH[2]);
+          C pa = edot(ex, ey, ez, pA[0], pA[1], pA[2]);
+          if constexpr (GUO) {
+            const C eF = edot(ex, ey, ez, F0, F1, F2);
+            ps += gk * ((C)9 * eu * eF - (C)3 * uF);
+            pa += gk * ((C)3 * eF);
+          }
+          g[i] = g[i] - rB * fn_i + Bn * fn_o + wq<Q, SC>(i, ps + pa);
+          g[o] = g[o] - rB * fn_o + Bn * fn_i + wq<Q, SC>(i, ps - pa);
+        }
+      };
+      if (forced)
+        collide(std::true_type{});
+      else
+        collide(std::false_type{});
+    } else {
+      // ---- pass 1: BGK + Guo weighted by (1 - B_n), plus the bounce-back of
+      // the non-equilibrium part, B_n (fneq_{-i} - fneq_i); one opposite pair
+      // at a time (Eqs. 2-4, 10, 12), the relaxation and the bounce-back
+      // applied as in the folded collision above ----
+      const C rB = relax + Bn;
+      {
+        const C wi = SC ? (C)1 : (C)L::w(0);
+        const C fneq = g[0] - wq<Q, SC>(0, drho - rho * (C)1.5 * uu);
+        g[0] = g[0] - relax * fneq - omB * kguo * wi * (C)3 * uF;
       }
-      p0 = (C)(-1.0 / 3.0) * (pD[0] + pD[1] + pD[2]);
-    }
-    constexpr C rest = (C)(SC ? 1.0 : L::w(0) / L::w(diag));  // w_0 / wd
-    {
-      C d0 = (C)2 * hs * (g[0] - wq<Q, SC>(0, c0));
-      if constexpr (FOLD) d0 += rest * p0;
-      g[0] += d0;
-    }
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-      const int o = L::opp(i);
-      if (o < i) continue;
-      const int ex = L::ex(i), ey = L::ey(i), ez = L::ez(i);
-      const C m = ex * ex + ey * ey + ez * ez == 1 ? (C)AX : (C)1;
-      const C eu = edot(ex, ey, ez, ux, uy, uz);
-      const C Fs = (g[i] + g[o]) - m * ((k45 * eu) * eu + k0);
-      const C Fa = (g[i] - g[o]) - (m * k3) * eu;
-      C dS = hs * Fs, dA = ha * Fa;
-      if constexpr (FOLD) {
-        C ps = p0;
-        eacc(ex * ex, ps, pD[0]);
-        eacc(ey * ey, ps, pD[1]);
-        eacc(ez * ez, ps, pD[2]);
-        eacc(ex * ey, ps, pH[0]);
-        eacc(ex * ez, ps, pH[1]);
-        eacc(ey * ez, ps, pH[2]);
-        dS += m * ps;
-        dA += m * edot(ex, ey, ez, pA[0], pA[1], pA[2]);
-      }
-      g[i] += dS + dA;
-      g[o] += dS - dA;
-    }
-    // ---- the Guo term (Eq. 4), weighted by 1 - B_n, in a pass of its own:
-    // two copies of the loop above (with it and without) had their common
-    // part hoisted over the branch and spilled 20-190 registers ----
-    if (forced) {
-      const C g3 = wq<Q, SC>(diag, omB * kguo * (C)3), g9 = (C)3 * g3;
-      const C gu = g3 * uF;
-      g[0] -= rest * gu;
 #pragma unroll
       for (int i = 1; i < Q; ++i) {
         const int o = L::opp(i);
         if (o < i) continue;
-        const int ex = L::ex(i), ey = L::ey(i), ez = L::ez(i);
-        const C m = ex * ex + ey * ey + ez * ez == 1 ? (C)AX : (C)1;
-        const C eF = edot(ex, ey, ez, F0, F1, F2);
-        const C even = m * ((g9 * eF) * edot(ex, ey, ez, ux, uy, uz) - gu), odd = (m * g3) * eF;
-        g[i] += even + odd;
-        g[o] += even - odd;
+        const C wi = SC ? (C)1 : (C)L::w(i);
+        const C eu = edot(L::ex(i), L::ey(i), L::ez(i), ux, uy, uz);
+        const C eF = edot(L::ex(i), L::ey(i), L::ez(i), F0, F1, F2);
+        const C sym = drho + rho * ((C)4.5 * eu * eu - (C)1.5 * uu);
+        const C fn_i = g[i] - wq<Q, SC>(i, sym + rho * (C)3 * eu);
+        const C fn_o = g[o] - wq<Q, SC>(i, sym - rho * (C)3 * eu);
+        // Guo term (Eq. 4): even and odd parts under e -> -e
+        const C Fsym = kguo * wi * ((C)9 * eu * eF - (C)3 * uF);
+        const C Fant = kguo * wi * ((C)3 * eF);
+        g[i] = g[i] - rB * fn_i + Bn * fn_o + omB * (Fsym + Fant);
+        g[o] = g[o] - rB * fn_o + Bn * fn_i + omB * (Fsym - Fant);
       }
     }
   }
 
-  // ---- second pass (covered cells of the other forms): sum_s B_s [f^eq_i(rho,
+  // ---- pass 2 (covered cells of the other forms): sum_s B_s [f^eq_i(rho,
   // u_s) - f^eq_i(rho, u)] and the momentum exchange ----
   if constexpr (!FOLD) {
     // slot k of this cell: the equilibrium difference into g and, unless the
@@ -772,23 +782,18 @@ __global__ void __launch_bounds__(BLOCK)
       const SlotKin t = slot_kin(k);
       const C du2 = t.dv[0] * t.sv[0] + t.dv[1] * t.sv[1] + t.dv[2] * t.sv[2];  // |u_s|^2 - |u|^2
       const C rB = rho * t.Bs;
-      // w_i rho B_s [4.5 ((e.u_s)^2 - (e.u)^2) - 1.5 (|u_s|^2 - |u|^2) + 3 e.(u_s
-      // - u)], even and odd parts, the weights as in the collision above
-      constexpr int diag = Q == 9 ? 5 : 7;
-      constexpr int AX = SC ? 1 : (Q == 9 ? 4 : 2);
-      const C k3 = wq<Q, SC>(diag, (C)3 * rB);
-      const C k45 = (C)1.5 * k3, k0 = (C)-0.5 * k3 * du2;
-      g[0] += (C)(SC ? 1.0 : L::w(0) / L::w(diag)) * k0;
+      g[0] -= wq<Q, SC>(0, rB * (C)1.5 * du2);
 #pragma unroll
       for (int i = 1; i < Q; ++i) {
         const int o = L::opp(i);
         if (o < i) continue;
         const C de = edot(L::ex(i), L::ey(i), L::ez(i), t.dv[0], t.dv[1], t.dv[2]);
         const C se = edot(L::ex(i), L::ey(i), L::ez(i), t.sv[0], t.sv[1], t.sv[2]);
-        const C m = L::ex(i) * L::ex(i) + L::ey(i) * L::ey(i) + L::ez(i) * L::ez(i) == 1 ? (C)AX : (C)1;
-        const C even = m * ((k45 * de) * se + k0), odd = (m * k3) * de;
-        g[i] += even + odd;
-        g[o] += even - odd;
+        // 4.5 [(e.u_s)^2 - (e.u)^2] - 1.5 (|u_s|^2 - |u|^2), and 3 e.(u_s - u)
+        const C ds_s = (C)4.5 * de * se - (C)1.5 * du2;
+        const C ds_a = (C)3 * de;
+        g[i] += wq<Q, SC>(i, rB * (ds_s + ds_a));
+        g[o] += wq<Q, SC>(i, rB * (ds_s - ds_a));
       }
       if (a.facc) exchange(t, mv);
     };
