@@ -704,7 +704,7 @@ int launch_adjoint(psclbm_ctx* c, const double* f, const double* lam_in, double*
     if (c->geom.face[fc] == PSCLBM_OUTLET_EQ) a.outlet_mask |= 1u << fc;
     if (c->geom.face[fc] == PSCLBM_MOVING_WALL) a.moving_mask |= 1u << fc;
   }
-  a.outlet_wave = outlet_wave_mask(c->geom, a.outlet_mask);
+  a.outlet_wave = c->geom.flat ? 0u : outlet_wave_mask(c->geom, a.outlet_mask);
   const unsigned separate = a.outlet_mask & ~a.outlet_wave;
   const double* F = c->cfg.body_force;
   const int fgrid = (int)((c->face_stride + 255) / 256 < 4096 ? (c->face_stride + 255) / 256 : 4096);

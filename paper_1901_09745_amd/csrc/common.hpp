@@ -187,14 +187,15 @@ struct StepArgs {
   double* fc;
 };
 
-// Outlet faces whose cells share a wave with their interior neighbour, so that
-// the neighbour's velocity (and, in the adjoint, the sensitivity flowing back
-// to it) moves between lanes: the x faces, since a wave is one 64-cell x-row
-// segment (segments start at multiples of 64); x = nx-1 only when it is not
-// the first lane of a segment.
+// Outlet faces whose cells take their interior neighbour's velocity (and, in the
+// adjoint, give back the sensitivity flowing to it) from the neighbour's lane:
+// the x faces, x = nx-1 only when it is not the first lane of a 64-cell segment
+// of its row.  A flat tile's waves, which start and end anywhere in a row, go by
+// the same rule, so that a face's velocities are formed in one arithmetic
+// whatever the tiles; those of its cells whose neighbour is in another wave read
+// it from a pass before the step.
 inline unsigned outlet_wave_mask(const Geom& g, unsigned outlet_mask) {
   unsigned m = 0;
-  if (g.flat) return 0;  // a flat wave may start at x = nx-1 or end at x = 0
   if ((outlet_mask & 1u) && g.nx >= 2) m |= 1u;
   if ((outlet_mask & 2u) && g.nx >= 2 && (g.nx - 1) % SEG != 0) m |= 2u;
   return m;

@@ -945,6 +945,7 @@ __global__ void __launch_bounds__(256) k_outlet_velocity(Geom g, const void* f, 
   using L = Lattice<Q>;
   using ST = Store<PREC, Q>;
   using S = typename Form<PREC>::S;
+  using C = typename Form<PREC>::C;
   unsigned left = faces;  // this block's face: the blockIdx.y-th set bit
   for (unsigned k = 0; k < blockIdx.y; ++k) left &= left - 1;
   const int face = __ffs((int)left) - 1;
@@ -969,6 +970,19 @@ __global__ void __launch_bounds__(256) k_outlet_velocity(Geom g, const void* f, 
     S v[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) v[i] = A[canonical_slot<Q, PAR>(d, N, x, y, z, n, i)];
+    double* o = out + ((size_t)face * stride + k) * 3;
+    if ((edges >> face) & 1u) {  // in the step's arithmetic, as the face's other cells have it
+      C h[Q], r, j0, j1, j2;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) h[i] = ST::deviation(v[i], i, g.rho0);
+      cell_moments<Q, scaled_form<PREC>()>(h, r, j0, j1, j2);
+      const C ir = inv_density((C)g.rho0 + r), ir0 = (C)(1.0 / g.rho0);
+      const C qr = r * ir;
+      o[0] = (double)eq5_velocity(j0, (C)0.5 * (C)fx, qr, ir, ir0);
+      o[1] = (double)eq5_velocity(j1, (C)0.5 * (C)fy, qr, ir, ir0);
+      o[2] = (double)eq5_velocity(j2, (C)0.5 * (C)fz, qr, ir, ir0);
+      continue;
+    }
     double rho = 0, j0 = 0, j1 = 0, j2 = 0;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -978,7 +992,6 @@ __global__ void __launch_bounds__(256) k_outlet_velocity(Geom g, const void* f, 
       eacc(L::ey(i), j1, fi);
       eacc(L::ez(i), j2, fi);
     }
-    double* o = out + ((size_t)face * stride + k) * 3;
     o[0] = (j0 + 0.5 * fx) / rho;
     o[1] = (j1 + 0.5 * fy) / rho;
     o[2] = (j2 + 0.5 * fz) / rho;
@@ -1383,8 +1396,7 @@ static StepArgs step_args(psclbm_ctx* c) {
     if (c->geom.face[f] == PSCLBM_MOVING_WALL) a.moving_mask |= 1u << f;
   }
   a.open_mask = a.inlet_mask | a.outlet_mask;
-  a.outlet_wave = c->geom.flat ? (c->geom.nx >= 2 ? a.outlet_mask & 3u : 0u)
-                               : outlet_wave_mask(c->geom, a.outlet_mask);
+  a.outlet_wave = outlet_wave_mask(c->geom, a.outlet_mask);
   a.original = c->cfg.weighting == PSCLBM_WEIGHT_ORIGINAL;
   a.dem_blocks = a.dem_shift = 0;
   std::memset(&a.dem, 0, sizeof(a.dem));

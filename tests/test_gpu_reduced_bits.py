@@ -33,6 +33,12 @@ CASES = {
     "3d_walls": (19, 64, 22, 20, WALLS_X, 0.0, "modified"),
     "3d_forced_walls": (19, 70, 22, 20, WALLS_X, 2e-5, "modified"),
     "3d_open": (19, 70, 40, 20, OPEN, 0.0, "modified"),
+    # flat waves with x = 0 in the last lane (65 y, 67 y = 63 mod 64) and x = nx - 1
+    # in the first; x = 64 alone in its segment
+    "3d_open_65": (19, 65, 70, 20, OPEN, 0.0, "modified"),
+    "3d_out_65": (19, 65, 70, 20, (OUT, OUT, OUT, IN, PER, PER), 0.0, "modified"),
+    "3d_out_67": (19, 67, 70, 20, (OUT, OUT, OUT, IN, PER, PER), 1e-5, "modified"),
+    "2d_out_67": (9, 67, 70, 1, (OUT, OUT, OUT, IN, PER, PER), 1e-5, "modified"),
     "3d_original": (19, 64, 22, 20, (PER,) * 6, 0.0, "original"),
 }
 
