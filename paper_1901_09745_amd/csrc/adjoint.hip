@@ -82,7 +82,9 @@ __device__ __forceinline__ double feq_i(int i, double rho, double ux, double uy,
 // the LDS atomics, 162 with the hints (5.0 TB/s).  1024^2 with 1600 disks 60
 // -> 52 us (open faces compiled out, three waves); the 512x256 channel 17.0 ->
 // 13.1 (the inlet's gradient summed per tile).
-template <int Q, bool WALLS, bool FLAT, bool NT>
+// WIDE: arrays of 4 GiB or more a direction (the reduced forms hold up to 2^31
+// cells, and the sensitivities are FP64 in every form), addressed in 64 bits.
+template <int Q, bool WALLS, bool FLAT, bool NT, bool WIDE = false>
 __global__ void __launch_bounds__(BLOCK)
     __attribute__((amdgpu_waves_per_eu(Q == 9 && !WALLS ? 3 : 2))) k_adjoint(const AdjArgs a) {
   using L = Lattice<Q>;
@@ -111,13 +113,14 @@ __global__ void __launch_bounds__(BLOCK)
     if (lk.inner) {
 #pragma unroll
       for (int i = 0; i < Q; ++i)
-        ls[i] = elem(a.lam_in + (size_t)i * N + (ptrdiff_t)lk.row_part(i), lk.lane_part(i));
+        ls[i] = elem_ld<false, WIDE>(a.lam_in + (size_t)i * N + (ptrdiff_t)lk.row_part(i),
+                                     lk.lane_part(i));
     } else {
 #pragma unroll
       for (int i = 0; i < Q; ++i) ls[i] = *lk.at(a.lam_in, N, i);
     }
 #pragma unroll
-    for (int i = 0; i < Q; ++i) fv[i] = elem_ld<NT>(a.f + (size_t)i * N, n);
+    for (int i = 0; i < Q; ++i) fv[i] = elem_ld<NT, WIDE>(a.f + (size_t)i * N, n);
   };
   LdsEntry* lds = reinterpret_cast<LdsEntry*>(smem_d);
   double* acc = reinterpret_cast<double*>(lds + a.cap);  // [cap][9]
@@ -525,7 +528,7 @@ __global__ void __launch_bounds__(BLOCK)
       double lj = alpha * ls[j] + Bn * ls[L::opp(j)] + base + edot(ex, ey, ez, qx, qy, qz);
       if (reset) lj = 0.0;
       lj += edot(ex, ey, ez, s0, s1, s2) + sb;
-      if (active) elem_st<NT>(a.lam_out + (size_t)j * N, n, lj);
+      if (active) elem_st<NT, WIDE>(a.lam_out + (size_t)j * N, n, lj);
     }
   }
 
@@ -656,6 +659,10 @@ __global__ void __launch_bounds__(BLOCK) k_rasterize_adjoint(Geom g, double h, i
 
 template <int Q, bool WALLS, bool FLAT>
 static void launch_step_adjoint(psclbm_ctx* c, const AdjArgs& a, size_t lds) {
+  if ((double)c->geom.N * sizeof(double) >= 4294967296.0) {  // (one kernel for all of them)
+    k_adjoint<Q, true, FLAT, false, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+    return;
+  }
   // (rows of whole lines only: see the even steps' choice)
   const bool nt = !FLAT && (double)c->geom.N * Q * sizeof(double) > 256.0 * 1024 * 1024;
   if (nt) k_adjoint<Q, WALLS, FLAT, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);

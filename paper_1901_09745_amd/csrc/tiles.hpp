@@ -461,17 +461,20 @@ __device__ __forceinline__ GlobalT<S>& elem(S* base, unsigned e) {
   return *(GlobalT<S>*)(gb + (e * (unsigned)sizeof(S)));
 }
 
-// The same element read or written with a non-temporal hint when NT: the
-// line is streamed through the caches rather than kept in them.
-template <bool NT, typename S>
+// The same element read or written with a non-temporal hint when NT (the line
+// is streamed through the caches rather than kept in them) and through a 64-bit
+// offset when WIDE (arrays of 4 GiB or more).
+template <bool NT, bool WIDE = false, typename S>
 __device__ __forceinline__ S elem_ld(S* base, unsigned e) {
-  if constexpr (NT) return __builtin_nontemporal_load(&elem(base, e));
-  else return elem(base, e);
+  auto& v = WIDE ? *(GlobalT<S>*)(base + e) : elem(base, e);
+  if constexpr (NT) return __builtin_nontemporal_load(&v);
+  else return v;
 }
-template <bool NT, typename S>
+template <bool NT, bool WIDE = false, typename S>
 __device__ __forceinline__ void elem_st(S* base, unsigned e, S v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, &elem(base, e));
-  else elem(base, e) = v;
+  auto& to = WIDE ? *(GlobalT<S>*)(base + e) : elem(base, e);
+  if constexpr (NT) __builtin_nontemporal_store(v, &to);
+  else to = v;
 }
 
 // The links of one cell: its neighbours through the periodic wrap, and the
