@@ -98,7 +98,12 @@ typedef struct {
   int precision;              /* PSCLBM_FP64, PSCLBM_FP32 or PSCLBM_FP32_FP16STORE */
   int max_particles;          /* capacity of the particle snapshot, >= 0 */
   double max_radius;          /* largest particle radius the DEM bins are sized for */
-  int max_tile_particles;     /* capacity of each tile's particle list (e.g. 256) */
+  int max_tile_particles;     /* particles in the list of a tile of 256 cells, 1..512 (e.g. 256):
+                                 those whose shell boxes touch its 64 x 4, 128 x 2 or 256 x 1
+                                 cells of a plane (the widest that pads the rows least; 2D 64 x
+                                 4).  Lattices whose rows leave much of such tiles empty take
+                                 256 cells in succession instead (max_tile_particles up to
+                                 160), with lists that hold whatever these would have held */
   int max_contacts;           /* DEM contact capacity per particle (e.g. 16) */
   int weighting;              /* PSCLBM_WEIGHT_MODIFIED (Eqs. 12-14, cell total clamped, Table 1) or
                                  PSCLBM_WEIGHT_ORIGINAL (Eqs. 7-9, 11: each particle's

@@ -1,6 +1,7 @@
 // extern "C" entry points of the gfx950 PSC-LBM library (see include/psclbm.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -156,7 +157,7 @@ int xcd_runs(const psclbm_config* c, bool flat, int twx) {
 struct Layout {
   size_t f, err, scalar, tile_count, tile_list, snap, facc0, facc1, mass_part, outlet_u, outlet_g;
   size_t bin_count, bin_rec, cn0, cn1, cid0, cid1, fcont, spr0, spr1, ws0, ws1, total;
-  int ntx, nty, ntz, ntiles, twx, twy, flat, list_cap;
+  int ntx, nty, ntz, ntiles, twx, twy, flat, list_cap, more_cap;
   long long face_stride;
   int nbin[3];
   double bin_size[3];
@@ -178,10 +179,22 @@ Layout plan(const psclbm_config* c, bool may_be_flat = true) {
   l.ntz = c->nz;
   l.ntiles = l.ntx * l.nty * l.ntz;
   const int np = c->max_particles;
-  // (a flat tile's cells lie in two or three of the row tiles: its list is
-  // given half as much again)
-  l.list_cap = l.flat ? c->max_tile_particles + c->max_tile_particles / 2 : c->max_tile_particles;
-  const int cap = np > 0 ? l.list_cap : 1;
+  l.list_cap = c->max_tile_particles;
+  l.more_cap = 0;
+  if (l.flat && np > 0) {
+    // A flat tile's list takes every particle of the row tiles that it overlaps
+    // (a list that a row tile had room for never overflows on a flat one): its
+    // 256 cells lie in at most `rows` rows, these in `bands` rows of row tiles,
+    // and in each row they touch a run of row tiles.
+    const int rows = std::min((BLOCK - 2) / c->nx + 2, c->ny);
+    const int across = (c->nx + l.twx - 1) / l.twx;
+    const int bands = std::min((rows + l.twy - 2) / l.twy + 1, (c->ny + l.twy - 1) / l.twy);
+    const long long tiles = std::min(bands * (long long)across, BLOCK / l.twx + 2LL * rows);
+    const int all = (int)std::min(tiles * c->max_tile_particles, (long long)np);
+    l.list_cap = std::min(c->max_tile_particles + c->max_tile_particles / 2, all);
+    l.more_cap = all - l.list_cap;
+  }
+  const int cap = np > 0 ? l.list_cap + l.more_cap : 1;
   bool outlet = false;
   for (int f = 0; f < 6; ++f) outlet |= c->face_bc[f] == PSCLBM_OUTLET_EQ;
   long long fs = (long long)c->ny * c->nz;
@@ -236,6 +249,16 @@ Layout plan(const psclbm_config* c, bool may_be_flat = true) {
   l.ws1 = take(sizeof(double) * 3 * (size_t)(np > 0 ? np : 1));
   l.total = off;
   return l;
+}
+
+// The tiles' particle lists at `at`.
+TileLists tile_lists(const Layout& l, char* at) {
+  TileLists t;
+  t.ids = reinterpret_cast<int*>(at);
+  t.more = t.ids + (size_t)l.ntiles * l.list_cap;
+  t.cap = l.list_cap;
+  t.more_cap = l.more_cap;
+  return t;
 }
 
 // The lattice geometry the kernels take, from a validated configuration.
@@ -372,9 +395,8 @@ int lbm_init(const psclbm_config* cfg, void* d_workspace, size_t bytes, void* hi
   c->tile_count_buf[1] = c->tile_count_buf[0] + l.ntiles;
   c->tile_cur = 0;
   c->tile_count = c->tile_count_buf[0];
-  c->tile_list = reinterpret_cast<int*>(base + l.tile_list);
+  c->lists = tile_lists(l, base + l.tile_list);
   c->ntiles = l.ntiles;
-  c->list_cap = l.list_cap;
   c->snap = reinterpret_cast<PSnap*>(base + l.snap);
   c->facc[0] = reinterpret_cast<double*>(base + l.facc0);
   c->facc[1] = reinterpret_cast<double*>(base + l.facc1);
@@ -657,9 +679,8 @@ int psc_solid_fraction_noalloc(const psclbm_config* cfg, const psclbm_particles*
   c.tile_count_buf[1] = c.tile_count_buf[0] + l.ntiles;
   c.tile_cur = 0;
   c.tile_count = c.tile_count_buf[0];
-  c.tile_list = reinterpret_cast<int*>(base + o_list);
+  c.lists = tile_lists(l, base + o_list);
   c.ntiles = l.ntiles;
-  c.list_cap = l.list_cap;
   c.snap = reinterpret_cast<PSnap*>(base + o_snap);
   c.facc[0] = c.facc[1] = reinterpret_cast<double*>(base + o_facc);
   // the array keeps the last call's contents: clear the error word and the

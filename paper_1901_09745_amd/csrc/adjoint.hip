@@ -45,9 +45,9 @@ struct AdjArgs {
   double tau, omega;
   double force[3];
   double h;
-  int np, cap;
+  int np;
   const int* tile_count;
-  const int* tile_list;
+  TileLists lists;
   const PSnap* snap;
   const double* f;        // canonical FP64 state entering the step
   const double* lam_in;   // dJ/df(t+1), canonical
@@ -123,19 +123,19 @@ __global__ void __launch_bounds__(BLOCK)
     for (int i = 0; i < Q; ++i) fv[i] = elem_ld<NT, WIDE>(a.f + (size_t)i * N, n);
   };
   LdsEntry* lds = reinterpret_cast<LdsEntry*>(smem_d);
-  double* acc = reinterpret_cast<double*>(lds + a.cap);  // [cap][9]
+  double* acc = reinterpret_cast<double*>(lds + a.lists.cap);  // [lists.cap][9]
   // dJ/d(face velocity) of the tile: every cell of an inlet adds to the same
   // three numbers, and atomics of one address are taken in turn
   __shared__ double face_acc[18];
   const bool faces = WALLS && a.gface;  // (a periodic lattice has no such face)
   if (faces && threadIdx.x < 18) face_acc[threadIdx.x] = 0.0;
-  const int cnt = load_tile_list(a.tile_count, a.tile_list, a.cap, a.snap, tile, lds, nullptr,
-                                 a.np, issue);
-  for (int k = threadIdx.x; k < 9 * cnt; k += BLOCK) acc[k] = 0.0;
+  const TileList tl = load_tile_list(a.tile_count, a.lists, a.snap, tile, lds, nullptr, a.np, issue);
+  const int cnt = tl.cnt;
+  for (int k = threadIdx.x; k < 9 * tl.held; k += BLOCK) acc[k] = 0.0;
   if (cnt > 0 || faces) __syncthreads();
   Slots s;
   s.n = 0;
-  if (cnt > 0) collect_slots<D, FLAT>(G, wc, active, lds, cnt, a.h, s, nullptr, slot_lds);
+  if (cnt > 0) collect_slots<D, FLAT, FLAT>(G, wc, active, tl, a.h, s, nullptr, slot_lds);
 
   // from here on every lane computes (those without a cell the wave's last
   // one, without slots and without output), so that lanes can exchange values
@@ -351,16 +351,26 @@ __global__ void __launch_bounds__(BLOCK)
     // accumulators: summed first over aligned blocks of up to 8 lanes whose
     // slot holds the same entry, so that the LDS unit, which takes lanes of one
     // address in turn, sees a block's leader only
+    // (or, for an entry that LDS does not hold, the particle's own)
+    auto add = [&](int e, int j, double t) {
+      if constexpr (FLAT) {
+        if (tl.over && e >= tl.held) {
+          double* dst = j < 3 ? a.gX : (j < 6 ? a.gU : a.gW);
+          if (dst) atomicAdd(dst + 3 * tl.id_past(e) + (j % 3), t);
+          return;
+        }
+      }
+      atomicAdd(acc + 9 * e + j, t);
+    };
     auto accumulate = [&](int e, bool has, auto& v) {
       constexpr int NV = sizeof(v) / sizeof(v[0]);
       bool lead;
       const unsigned mf = merge_flags(has ? e : -1, lane, lead);
-      double* ac = acc + 9 * e;
 #pragma unroll
       for (int j = 0; j < NV; ++j) {
         if (D == 2 && (j == 2 || (j > 4 && j < 8))) continue;  // out of the plane
         const double t = merge_sum(v[j], mf);
-        if (lead) atomicAdd(ac + j, t);
+        if (lead) add(e, j, t);
       }
     };
 #pragma unroll
@@ -373,7 +383,7 @@ __global__ void __launch_bounds__(BLOCK)
       const int e = has ? s.e[k] : 0;
       if (has) {
         const double epsk = s.eps[k];
-        const LdsEntry& P = lds[e];
+        const auto& P = tile_entry<FLAT, true>(tl, e);
         const double rx = min_image((double)x - P.x, d.px, d.nx);
         const double ry = min_image((double)y - P.y, d.py, d.ny);
         const double rz = D == 3 ? min_image((double)z - P.z, d.pz, d.nz) : 0.0;
@@ -446,7 +456,7 @@ __global__ void __launch_bounds__(BLOCK)
       for (int k = 0; k < KSLOTS; ++k) {
         if (!several || k >= s.n) continue;
         const int e = s.e[k];
-        const LdsEntry& P = lds[e];
+        const auto& P = tile_entry<FLAT, true>(tl, e);
         const double rx = min_image((double)x - P.x, d.px, d.nx);
         const double ry = min_image((double)y - P.y, d.py, d.ny);
         const double rz = D == 3 ? min_image((double)z - P.z, d.pz, d.nz) : 0.0;
@@ -455,10 +465,9 @@ __global__ void __launch_bounds__(BLOCK)
         const bool band = dist < P.r + a.h && dist > P.r - a.h && lin > 0.0 && lin < 1.0;
         if (!band) continue;
         const double gd = cSG / dist;
-        double* ac = acc + 9 * e;
-        atomicAdd(ac + 0, gd * rx);
-        atomicAdd(ac + 1, gd * ry);
-        if constexpr (D == 3) atomicAdd(ac + 2, gd * rz);
+        add(e, 0, gd * rx);
+        add(e, 1, gd * ry);
+        if constexpr (D == 3) add(e, 2, gd * rz);
       }
     }
 
@@ -539,7 +548,7 @@ __global__ void __launch_bounds__(BLOCK)
     const double v = face_acc[threadIdx.x];
     if (v != 0.0) atomicAdd(a.gface + threadIdx.x, v);
   }
-  for (int t = threadIdx.x; t < 9 * cnt; t += BLOCK) {
+  for (int t = threadIdx.x; t < 9 * tl.held; t += BLOCK) {
     const int e = t / 9, k = t - 9 * e;
     const double v = acc[t];
     if (v == 0.0) continue;
@@ -619,23 +628,23 @@ __global__ void k_outlet_adjoint(Geom g, int face, const double* f, const double
 // Table 1 chain alone: dJ/dX_s += sum_n dJ/deps_{n,s} r/|r| on the linear band,
 // for sensitivities given per recorded slot (the order of psc_get_solid_fraction).
 template <int D, bool FLAT>
-__global__ void __launch_bounds__(BLOCK) k_rasterize_adjoint(Geom g, double h, int np, int cap,
+__global__ void __launch_bounds__(BLOCK) k_rasterize_adjoint(Geom g, double h, int np,
                                                            const int* tile_count,
-                                                           const int* tile_list,
+                                                           TileLists lists,
                                                            const PSnap* snap, const double* gs,
                                                            int kout, double* gX) {
   extern __shared__ double smem_d[];
   __shared__ SlotLds slot_lds;
   LdsEntry* lds = reinterpret_cast<LdsEntry*>(smem_d);
   const int tile = blockIdx.x;
-  const int cnt = load_tile_list(tile_count, tile_list, cap, snap, tile, lds, nullptr, np);
+  const TileList tl = load_tile_list(tile_count, lists, snap, tile, lds, nullptr, np);
   const WaveCells<FLAT> wc = wave_cells<FLAT>(g, tile);
   const LaneCell cell = lane_cell<FLAT>(g, wc);
   const int x = cell.x, y = cell.y, z = wc.z;
   const bool active = (int)(threadIdx.x & 63) <= wc.last;
   Slots s;
   s.n = 0;
-  if (cnt > 0) collect_slots<D, FLAT>(g, wc, active, lds, cnt, h, s, nullptr, slot_lds);
+  if (tl.cnt > 0) collect_slots<D, FLAT, FLAT>(g, wc, active, tl, h, s, nullptr, slot_lds);
   if (!active) return;
   const long long n = x + (long long)g.nx * (y + (long long)g.ny * z);
 #pragma unroll
@@ -643,7 +652,7 @@ __global__ void __launch_bounds__(BLOCK) k_rasterize_adjoint(Geom g, double h, i
     if (k >= kout || k >= s.n) break;
     const double gk = gs[(size_t)n * kout + k];
     if (gk == 0.0) continue;
-    const LdsEntry& P = lds[s.e[k]];
+    const auto& P = tile_entry<FLAT>(tl, s.e[k]);
     const double rx = min_image((double)x - P.x, g.periodic[0], g.nx);
     const double ry = min_image((double)y - P.y, g.periodic[1], g.ny);
     const double rz = D == 3 ? min_image((double)z - P.z, g.periodic[2], g.nz) : 0.0;
@@ -689,9 +698,8 @@ int launch_adjoint(psclbm_ctx* c, const double* f, const double* lam_in, double*
   for (int k = 0; k < 3; ++k) a.force[k] = c->cfg.body_force[k];
   a.h = c->cfg.shell_h;
   a.np = c->np;
-  a.cap = c->list_cap;
   a.tile_count = c->tile_count;
-  a.tile_list = c->tile_list;
+  a.lists = c->lists;
   a.snap = c->snap;
   a.f = f;
   a.lam_in = lam_in;
@@ -720,9 +728,7 @@ int launch_adjoint(psclbm_ctx* c, const double* f, const double* lam_in, double*
     k_outlet_velocity_canon<<<fgrid, 256, 0, c->stream>>>(c->geom, fc, f, F[0], F[1], F[2],
                                                           c->outlet_u, c->face_stride);
   }
-  const size_t lds = c->np > 0 ? (sizeof(LdsEntry) + 9 * sizeof(double)) *
-                                     (size_t)c->list_cap
-                               : 0;
+  const size_t lds = c->np > 0 ? (sizeof(LdsEntry) + 9 * sizeof(double)) * (size_t)c->lists.cap : 0;
   const bool walls = !(c->geom.periodic[0] && c->geom.periodic[1] && c->geom.periodic[2]);
   if (c->geom.q == 9) launch_step_adjoint<9>(c, a, walls, lds);
   else launch_step_adjoint<19>(c, a, walls, lds);
@@ -742,9 +748,9 @@ int launch_adjoint(psclbm_ctx* c, const double* f, const double* lam_in, double*
 
 template <int D, bool FLAT>
 static int rasterize_adjoint(psclbm_ctx* c, const double* gs, int kslots, double* gX) {
-  const size_t lds = (sizeof(LdsEntry) + sizeof(double)) * (size_t)c->list_cap;
+  const size_t lds = (sizeof(LdsEntry) + sizeof(double)) * (size_t)c->lists.cap;
   k_rasterize_adjoint<D, FLAT><<<c->ntiles, BLOCK, lds, c->stream>>>(
-      c->geom, c->cfg.shell_h, c->np, c->list_cap, c->tile_count, c->tile_list, c->snap, gs,
+      c->geom, c->cfg.shell_h, c->np, c->tile_count, c->lists, c->snap, gs,
       kslots, gX);
   return hip_ok(hipGetLastError());
 }

@@ -107,8 +107,7 @@ struct NextOut {
   int* tcount;
   int* tstale;
   long long ntiles;
-  int* tile_list;
-  int cap;
+  TileLists lists;
   DemBinOut db;
   double* wnext;  // friction: the updated spins, which the next step's contacts read
   unsigned* err;
@@ -192,7 +191,7 @@ __global__ void __launch_bounds__(256) k_dem_contacts(DemArgs d, FricArgs fr, In
   if (nx.build) {
     PSnap P;
     const bool ok = make_snap(d.three_d, xs, us, ws, ri, P, r_prev, cs_prev);
-    if (ok) bin_tiles<LPP>(nx.g, d.three_d, nx.h, P, i, lane, nx.tcount, nx.tile_list, nx.cap, nx.err);
+    if (ok) bin_tiles<LPP>(nx.g, d.three_d, nx.h, P, i, lane, nx.tcount, nx.lists, nx.err);
     if (lane == 0) {
       nx.snap[i] = P;
       if (!ok) atomicOr(nx.err, ERR_RADIUS);
@@ -337,8 +336,7 @@ static NextOut next_out(psclbm_ctx* c, bool build, bool bins, double* wnext) {
   nx.tcount = c->tile_count_buf[c->tile_cur ^ 1];
   nx.tstale = c->tile_count_buf[c->tile_cur];
   nx.ntiles = c->ntiles;
-  nx.tile_list = c->tile_list;
-  nx.cap = c->list_cap;
+  nx.lists = c->lists;
   nx.db = dem_bin_out(c, bins);
   nx.wnext = wnext;
   nx.err = c->err;

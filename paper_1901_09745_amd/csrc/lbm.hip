@@ -241,16 +241,17 @@ struct Store {
 // Waves per SIMD of each form, the register budget of the tiles (which the
 // contact workgroups' code must fit as well), each as measured fastest: 2D
 // FP32 / FP16 8 (their slot fractions held in FP32, so that eight
-// workgroups' LDS fits a CU), walled 3D FP32 / FP16 7, periodic 3D FP32 /
-// FP16 6 (the per-cell moments keep their registers lower), 2D FP64 5, 3D
-// FP64 4.  The reduced 3D forms are bound by instruction issue, and more
+// workgroups' LDS fits a CU), walled 3D FP32 / FP16 7 in row tiles and 6 in flat
+// ones (whose look-ups past LDS spill 10 registers at 7: FP16, 300x180x190 286
+// us against 265), periodic 3D FP32 / FP16 6 (the per-cell moments keep their
+// registers lower), 2D FP64 5, 3D FP64 4.  The reduced 3D forms are bound by instruction issue, and more
 // waves hide more of the loads' and the tile list's latency under it, up to
 // the point where spills cost more.
 template <int Q, int PREC, bool WALLS, bool FLAT>
 constexpr int step_waves() {
   if (PREC == PSCLBM_FP64) return Q == 9 ? 5 : 4;
   if (Q == 9) return 8;
-  return WALLS && !(FLAT && PREC == PSCLBM_FP32) ? 7 : 6;
+  return WALLS && !FLAT ? 7 : 6;
 }
 
 // Forms whose loads of f start before the tile's list is waited for rather
@@ -299,7 +300,8 @@ struct ContactBlocks {
 
 // NT: the accesses to the own cell's slots (the even step's, and the ring
 // step's loads), each line by one wave, are streamed with non-temporal hints.
-template <int Q, int PREC, int PAR, bool WALLS, bool FLAT, bool NT = false>
+// MORE: the tiles' lists may be longer than what LDS holds (flat tiles).
+template <int Q, int PREC, int PAR, bool WALLS, bool FLAT, bool MORE = false, bool NT = false>
 __global__ void __launch_bounds__(BLOCK)
     __attribute__((amdgpu_waves_per_eu(step_waves<Q, PREC, WALLS, FLAT>())))
     k_step(const StepArgs a) {
@@ -347,7 +349,7 @@ __global__ void __launch_bounds__(BLOCK)
   // particle list of the tile (LDS) and its force accumulators
   using Entry = LdsEntryT<E>;
   Entry* lds = reinterpret_cast<Entry*>(smem_d);
-  double* acc = reinterpret_cast<double*>(lds + a.cap);
+  double* acc = reinterpret_cast<double*>(lds + a.lists.cap);
   const Dims d = dims_of(a.g);
   // the wave's cells; z, and y unless FLAT, are uniform over the wave (scalar)
   const WaveCells<FLAT> wc = wave_cells<FLAT>(a.g, tile);
@@ -382,8 +384,9 @@ __global__ void __launch_bounds__(BLOCK)
       for (int i = 0; i < Q; ++i) raw[i] = elem_ld<NT>(dir_ptr(from, i, N), lk.n);
     }
   };
-  const int cnt = load_tile_list(a.tile_count, a.tile_list, a.cap, a.snap, tile, lds, acc, a.np,
-                                 [&] { if constexpr (EARLY) load(); });
+  const TileListT<E> tl = load_tile_list(a.tile_count, a.lists, a.snap, tile, lds, acc, a.np,
+                                         [&] { if constexpr (EARLY) load(); });
+  const int cnt = tl.cnt;
   const double rho0 = a.g.rho0;
   // ---- solid fractions of the covering particles (Table 1), whole wave; in
   // 3D after the loads of f are issued, so that their latency overlaps the
@@ -391,7 +394,7 @@ __global__ void __launch_bounds__(BLOCK)
   SlotsT<E> s;
   s.n = 0;
   if constexpr (Q == 9) {
-    if (cnt > 0) collect_slots<D, FLAT>(a.g, wc, active, lds, cnt, a.h, s, a.err, slot_lds);
+    if (cnt > 0) collect_slots<D, FLAT, MORE>(a.g, wc, active, tl, a.h, s, a.err, slot_lds);
   }
 
   C g[Q];
@@ -410,13 +413,13 @@ __global__ void __launch_bounds__(BLOCK)
   E bscale = 1;  // B_s / eps_{n,s} of the cell (Eq. 13), formed with the weights
   if constexpr (!EARLY) load();
   if constexpr (Q == 19) {
-    if (cnt > 0) collect_slots<D, FLAT>(a.g, wc, active, lds, cnt, a.h, s, a.err, slot_lds);
+    if (cnt > 0) collect_slots<D, FLAT, MORE>(a.g, wc, active, tl, a.h, s, a.err, slot_lds);
   }
   // deviations g_i = f_i - w_i rho0 (in the scaled form g_i / w_i)
 #pragma unroll
   for (int i = 0; i < Q; ++i) g[i] = ST::deviation(raw[i], i, rho0);
-  // the slots' list entries, two to a register (entries < 2^16; the list
-  // capacity is at most 512): registers held through the collision
+  // the slots' list entries, two to a register (entries < 2^15): registers held
+  // through the collision
   const unsigned e01 = (unsigned)s.e[0] | ((unsigned)s.e[1] << 16);
   const unsigned e23 = (unsigned)s.e[2] | ((unsigned)s.e[3] << 16);
   auto slot_e = [&](int k) {
@@ -444,7 +447,7 @@ __global__ void __launch_bounds__(BLOCK)
     SlotKin t;
     t.Bs = a.original ? (C)(s.eps[k] * tm / ((1.0 - s.eps[k]) + tm)) : (C)(s.eps[k] * bscale);
     t.Bm = a.original ? Bn_cell : t.Bs;
-    const Entry& P = lds[slot_e(k)];
+    const auto& P = tile_entry<MORE>(tl, slot_e(k));
     // u_s = U + Omega x r in the arithmetic precision: the arm from its FP64
     // nearest image, or in the FP32 forms from the centre's FP32 pair
     C cx, cy, cz;
@@ -499,19 +502,28 @@ __global__ void __launch_bounds__(BLOCK)
       mv[2] = -(t.r[0] * my - t.r[1] * mx);
     }
   };
-  // added to the list entry's FP64 accumulators in LDS
+  // added to the list entry's FP64 accumulators in LDS, or (an entry that LDS
+  // does not hold) to the particle's
   auto accumulate = [&](int e, const C (&mv)[NV]) {
-    double* ac = acc + 6 * e;
-    atomicAdd(ac + 0, (double)mv[0]);
-    atomicAdd(ac + 1, (double)mv[1]);
-    if constexpr (D == 3) {
-      atomicAdd(ac + 2, (double)mv[2]);
-      atomicAdd(ac + 3, (double)mv[3]);
-      atomicAdd(ac + 4, (double)mv[4]);
-      atomicAdd(ac + 5, (double)mv[5]);
-    } else {
-      atomicAdd(ac + 5, (double)mv[2]);
+    auto add = [&](double* ac) {
+      atomicAdd(ac + 0, (double)mv[0]);
+      atomicAdd(ac + 1, (double)mv[1]);
+      if constexpr (D == 3) {
+        atomicAdd(ac + 2, (double)mv[2]);
+        atomicAdd(ac + 3, (double)mv[3]);
+        atomicAdd(ac + 4, (double)mv[4]);
+        atomicAdd(ac + 5, (double)mv[5]);
+      } else {
+        atomicAdd(ac + 5, (double)mv[2]);
+      }
+    };
+    if constexpr (MORE) {
+      if (e >= tl.held) {
+        add(a.facc + 6 * (size_t)tl.id_past(e));
+        return;
+      }
     }
+    add(acc + 6 * e);
   };
   // periodic 3D reduced-precision forms: the particles' equilibrium difference
   // enters the collision through ten per-cell moments (one pass over the
@@ -903,7 +915,7 @@ __global__ void __launch_bounds__(BLOCK)
   // 541 us); the barrier of the mass reduction above orders the LDS
   // accumulation before this read ----
   if (cnt > 0 && a.facc) {
-    for (int t = threadIdx.x; t < 6 * cnt; t += BLOCK) {
+    for (int t = threadIdx.x; t < 6 * tl.held; t += BLOCK) {
       const int e = t / 6, k = t - 6 * e;
       const double v = acc[t];
       if (v != 0.0) atomicAdd(a.facc + 6 * (size_t)lds[e].id + k, v);
@@ -1151,7 +1163,7 @@ __global__ void __launch_bounds__(256) k_rasterize(Geom g, int n, int three_d, d
                                                    const double* x, const double* u,
                                                    const double* w, const double* r,
                                                    PSnap* snap, int* count, int* stale,
-                                                   int* tile_list, int cap, double* f0,
+                                                   TileLists lists, double* f0,
                                                    double* f1, unsigned* err, DemBinOut db) {
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   for (long long k = gid; k < g.ntx * (long long)g.nty * g.ntz;
@@ -1170,7 +1182,7 @@ __global__ void __launch_bounds__(256) k_rasterize(Geom g, int n, int three_d, d
   if (bin) place = dem_bin_place(db, three_d, g, x + 3 * s);
   if (lane < 6) f0[6 * s + lane] = 0.0;
   else if (lane < 12) f1[6 * s + lane - 6] = 0.0;
-  if (ok) bin_tiles<RASTER_LANES>(g, three_d, h, P, s, lane, count, tile_list, cap, err);
+  if (ok) bin_tiles<RASTER_LANES>(g, three_d, h, P, s, lane, count, lists, err);
   if (lane == 0) {
     snap[s] = P;
     if (!ok) atomicOr(err, ERR_RADIUS);
@@ -1179,8 +1191,8 @@ __global__ void __launch_bounds__(256) k_rasterize(Geom g, int n, int three_d, d
 }
 
 template <int D, bool FLAT>
-__global__ void __launch_bounds__(BLOCK) k_solid_fraction(Geom g, double h, int np, int cap,
-                                                        const int* tile_count, const int* tile_list,
+__global__ void __launch_bounds__(BLOCK) k_solid_fraction(Geom g, double h, int np,
+                                                        const int* tile_count, TileLists lists,
                                                         const PSnap* snap, double* eps_total,
                                                         int* ids, double* seps, int kout,
                                                         unsigned* err) {
@@ -1188,14 +1200,14 @@ __global__ void __launch_bounds__(BLOCK) k_solid_fraction(Geom g, double h, int 
   __shared__ SlotLds slot_lds;
   LdsEntry* lds = reinterpret_cast<LdsEntry*>(smem_d);
   const int tile = blockIdx.x;
-  const int cnt = load_tile_list(tile_count, tile_list, cap, snap, tile, lds, nullptr, np);
+  const TileList tl = load_tile_list(tile_count, lists, snap, tile, lds, nullptr, np);
   const WaveCells<FLAT> wc = wave_cells<FLAT>(g, tile);
   const LaneCell cell = lane_cell<FLAT>(g, wc);
   const bool active = (int)(threadIdx.x & 63) <= wc.last;
   const long long n = cell.x + (long long)g.nx * (cell.y + (long long)g.ny * wc.z);
   Slots s;
   s.n = 0;
-  if (cnt > 0) collect_slots<D, FLAT>(g, wc, active, lds, cnt, h, s, err, slot_lds);
+  if (tl.cnt > 0) collect_slots<D, FLAT, FLAT>(g, wc, active, tl, h, s, err, slot_lds);
   if (!active) return;
   double S_ = 0.0;
 #pragma unroll
@@ -1206,7 +1218,7 @@ __global__ void __launch_bounds__(BLOCK) k_solid_fraction(Geom g, double h, int 
 #pragma unroll
   for (int k = 0; k < KSLOTS; ++k) {
     if (k >= kout) break;
-    if (ids) ids[(size_t)n * kout + k] = k < s.n ? lds[s.e[k]].id : -1;
+    if (ids) ids[(size_t)n * kout + k] = k < s.n ? tile_entry<FLAT>(tl, s.e[k]).id : -1;
     if (seps) seps[(size_t)n * kout + k] = k < s.n ? s.eps[k] : 0.0;
   }
   for (int k = KSLOTS; k < kout; ++k) {
@@ -1225,36 +1237,40 @@ static int grid_for(long long n, int block = 256) {
   return (int)b;
 }
 
-template <int Q, int PREC, bool WALLS, bool FLAT>
+template <int Q, int PREC, bool WALLS, bool FLAT, bool MORE>
 static int dispatch_step(psclbm_ctx* c, const StepArgs& a, int par, size_t lds_bytes) {
   const int nb = c->ntiles + a.dem_blocks;
   if (par == 2) {  // ring step: canonical FP64 in and out
     if constexpr (PREC == PSCLBM_FP64) {
       if ((double)c->geom.N * Q * sizeof(double) > 256.0 * 1024 * 1024)
-        k_step<Q, PREC, 2, WALLS, FLAT, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+        k_step<Q, PREC, 2, WALLS, FLAT, MORE, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
       else
-        k_step<Q, PREC, 2, WALLS, FLAT><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+        k_step<Q, PREC, 2, WALLS, FLAT, MORE><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
     } else {
       return PSCLBM_EINVAL;
     }
   } else if (par == 1) {
-    k_step<Q, PREC, 1, WALLS, FLAT><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+    k_step<Q, PREC, 1, WALLS, FLAT, MORE><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
   } else if (c->geom.nt_even) {
-    k_step<Q, PREC, 0, WALLS, FLAT, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+    k_step<Q, PREC, 0, WALLS, FLAT, MORE, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
   } else {
-    k_step<Q, PREC, 0, WALLS, FLAT><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+    k_step<Q, PREC, 0, WALLS, FLAT, MORE><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
   }
   return hip_ok(hipGetLastError());
 }
 
-template <int Q, int PREC>
+template <int Q, int PREC, bool FLAT, bool MORE>
 static int dispatch_step(psclbm_ctx* c, const StepArgs& a, int par, size_t lds) {
   const bool walls = !(c->geom.periodic[0] && c->geom.periodic[1] && c->geom.periodic[2]);
-  if (c->geom.flat)
-    return walls ? dispatch_step<Q, PREC, true, true>(c, a, par, lds)
-                 : dispatch_step<Q, PREC, false, true>(c, a, par, lds);
-  return walls ? dispatch_step<Q, PREC, true, false>(c, a, par, lds)
-               : dispatch_step<Q, PREC, false, false>(c, a, par, lds);
+  return walls ? dispatch_step<Q, PREC, true, FLAT, MORE>(c, a, par, lds)
+               : dispatch_step<Q, PREC, false, FLAT, MORE>(c, a, par, lds);
+}
+
+template <int Q, int PREC>
+static int dispatch_step(psclbm_ctx* c, const StepArgs& a, int par, size_t lds) {
+  if (!c->geom.flat) return dispatch_step<Q, PREC, false, false>(c, a, par, lds);
+  return a.np > 0 && a.lists.more_cap > 0 ? dispatch_step<Q, PREC, true, true>(c, a, par, lds)
+                                          : dispatch_step<Q, PREC, true, false>(c, a, par, lds);
 }
 
 template <int PREC>
@@ -1333,8 +1349,7 @@ int launch_rasterize(psclbm_ctx* c, const psclbm_particles* p, bool dem_bins) {
   if (blocks < 1) blocks = 1;
   k_rasterize<<<(unsigned)blocks, 256, 0, c->stream>>>(
       c->geom, p->n, three_d, c->cfg.shell_h, p->x, p->u, p->omega, p->radius, c->snap,
-      c->tile_count_buf[next], c->tile_count_buf[c->tile_cur], c->tile_list,
-      c->list_cap, c->facc[0], c->facc[1], c->err, db);
+      c->tile_count_buf[next], c->tile_count_buf[c->tile_cur], c->lists, c->facc[0], c->facc[1], c->err, db);
   const int rc = hip_ok(hipGetLastError());
   if (rc) return rc;
   c->tile_cur = next;
@@ -1345,9 +1360,9 @@ int launch_rasterize(psclbm_ctx* c, const psclbm_particles* p, bool dem_bins) {
 
 template <int D, bool FLAT>
 static int solid_fraction(psclbm_ctx* c, double* eps, int* ids, double* seps, int k) {
-  const size_t lds = (sizeof(LdsEntry) + sizeof(double)) * (size_t)c->list_cap;
+  const size_t lds = (sizeof(LdsEntry) + sizeof(double)) * (size_t)c->lists.cap;
   k_solid_fraction<D, FLAT><<<c->ntiles, BLOCK, lds, c->stream>>>(
-      c->geom, c->cfg.shell_h, c->np, c->list_cap, c->tile_count, c->tile_list, c->snap, eps, ids,
+      c->geom, c->cfg.shell_h, c->np, c->tile_count, c->lists, c->snap, eps, ids,
       seps, k, c->err);
   return hip_ok(hipGetLastError());
 }
@@ -1370,9 +1385,8 @@ static StepArgs step_args(psclbm_ctx* c) {
   for (int k = 0; k < 3; ++k) a.force[k] = c->cfg.body_force[k];
   a.h = c->cfg.shell_h;
   a.np = c->np;
-  a.cap = c->list_cap;
   a.tile_count = c->tile_count;
-  a.tile_list = c->tile_list;
+  a.lists = c->lists;
   a.snap = c->snap;
   const int next = c->force_buf ^ 1;
   a.facc = c->facc[next];
@@ -1425,8 +1439,7 @@ static int outlet_velocity(psclbm_ctx* c, const void* f, int prec, int par, cons
 }
 
 static size_t step_lds(const psclbm_ctx* c) {
-  return c->np > 0 ? (sizeof(LdsEntry) + 6 * sizeof(double)) * (size_t)c->list_cap
-                   : 0;
+  return c->np > 0 ? (sizeof(LdsEntry) + 6 * sizeof(double)) * (size_t)c->lists.cap : 0;
 }
 
 int launch_step(psclbm_ctx* c, bool mass) {

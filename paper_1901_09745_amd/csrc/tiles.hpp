@@ -82,6 +82,64 @@ struct LdsEntryT<float> {
 };
 using LdsEntry = LdsEntryT<double>;
 
+template <typename E>
+__device__ __forceinline__ void fill_entry(LdsEntryT<E>& L, const PSnap& P, int id) {
+  L.x = P.x[0];
+  L.y = P.x[1];
+  L.z = P.x[2];
+  L.r = P.r;
+  L.cs = P.cs;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if constexpr (std::is_same<E, float>::value) {
+      L.xh[a] = (float)P.x[a];
+      L.xl[a] = (float)(P.x[a] - (double)L.xh[a]);
+      L.uf[a] = (float)P.u[a];
+      L.wf[a] = (float)P.w[a];
+    } else {
+      L.u[a] = P.u[a];
+      L.w[a] = P.w[a];
+    }
+  }
+  L.id = id;
+}
+
+// A tile's particle list: `cnt` particles, the first `held` of them in LDS.  A
+// row tile's are all held.  A flat tile meets the particles of several row tiles
+// and its list has room for all of theirs, but LDS for half as much again as one
+// of them, which is what the lists of most packings reach; the particles past
+// that are read from their snapshots at each use.  (300x180x190 with 8000 spheres
+// and lists of 64, FP64 / FP32 / FP16: 607 / 350 / 264 us a step, 602 / 344 / 250
+// without the look-ups, 614 / 378 / 328 with up to 206 entries in LDS, 723 / 445 /
+// 340 in row tiles.)
+template <typename E>
+struct TileListT {
+  LdsEntryT<E>* lds;
+  int cnt, held;
+  int over;         // the list is longer than what is held (scalar)
+  const int* rest;  // ids of the entries from `held` on
+  const PSnap* snap;
+  __device__ __forceinline__ int id_past(int e) const { return rest[e - held]; }
+};
+using TileList = TileListT<double>;
+
+// Entry e of the list: the one in LDS, or (MORE: the list may be longer than
+// what is held) one filled here.  GUARD: the waves of shorter lists branch over
+// the lane's test (the adjoint 76 -> 74 us, 100x80x80; the step, which it costs a
+// spilled register, without).
+template <bool MORE, bool GUARD = false, typename E>
+__device__ __forceinline__ typename std::conditional<MORE, LdsEntryT<E>, const LdsEntryT<E>&>::type
+tile_entry(const TileListT<E>& tl, int e) {
+  if constexpr (MORE) {
+    if ((!GUARD || tl.over) && e >= tl.held) {
+      LdsEntryT<E> L;
+      fill_entry(L, tl.snap[tl.id_past(e)], tl.id_past(e));
+      return L;
+    }
+  }
+  return tl.lds[e];
+}
+
 // Slots of one cell: up to KSLOTS particles with eps > 0, ascending particle
 // id (lds[e[k]].id).  The fractions are evaluated in FP64 and held as E (FP64,
 // or FP32 for the FP32 arithmetic forms, whose weights are formed in FP32).
@@ -97,7 +155,7 @@ using Slots = SlotsT<double>;
 template <typename E>
 struct SlotLdsT {
   int n[BLOCK];
-  unsigned short e[KSLOTS][BLOCK];  // list entries (the list holds at most 512)
+  unsigned short e[KSLOTS][BLOCK];  // list entries (a list holds less than 2^15)
   E eps[KSLOTS][BLOCK];
 };
 using SlotLds = SlotLdsT<double>;
@@ -139,9 +197,9 @@ struct WaveCells {
 // ERR_SLOTS).  All 64 lanes must call this.
 static_assert(SEG == 64, "64 cells a wave");
 
-template <int D, bool FLAT, typename E>
-__device__ inline void collect_slots(const Geom& g, const WaveCells<FLAT>& wc, bool active,
-                                     const LdsEntryT<E>* lds, int cnt, double h, SlotsT<E>& s,
+template <int D, bool FLAT, bool MORE, typename E>
+__device__ inline void collect_slots_of(const Geom& g, const WaveCells<FLAT>& wc, bool active,
+                                     const TileListT<E>& tl, double h, SlotsT<E>& s,
                                      unsigned* err, SlotLdsT<E>& sl) {
   const int px = g.periodic[0], py = g.periodic[1], pz = g.periodic[2];
   const int nx = g.nx, ny = g.ny, nz = g.nz;
@@ -151,12 +209,13 @@ __device__ inline void collect_slots(const Geom& g, const WaveCells<FLAT>& wc, b
   const int wbase = tid - lane;
   const int last = wc.last;  // uniform over the wave
   const double Lx = (double)nx;
-  // item t: entry t / rows, row t % rows (the quotient is exact: t < 2^15 and
-  // rows <= 64, so (t + 1/2) / rows stays 2^-7 from a whole number)
+  // item t: entry t / rows, row t % rows (the quotient is exact: rows <= 64, so
+  // (t + 1/2) / rows stays 2^-7 from a whole number, which the product's error,
+  // 2^-22 of its value, does not reach below 2^15 entries: a list's limit)
   const int rows = FLAT ? wc.rows : 1;
   const float per_row = FLAT ? __builtin_amdgcn_rcpf((float)rows) : 1.0f;
   auto entry_of = [&](int t) { return FLAT ? (int)(((float)t + 0.5f) * per_row) : t; };
-  const int items = cnt * rows;
+  const int items = tl.cnt * rows;
   sl.n[tid] = 0;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -172,7 +231,7 @@ __device__ inline void collect_slots(const Geom& g, const WaveCells<FLAT>& wc, b
       const int xr = wc.x0 - row * nx;
       const int la = FLAT && xr < 0 ? -xr : 0;
       const int lb = FLAT && nx - 1 - xr < last ? nx - 1 - xr : last;
-      const LdsEntryT<E>& P = lds[ec];
+      const auto& P = tile_entry<MORE>(tl, ec);
       const double dy = min_image((double)(wc.y0 + row) - P.y, py, ny);
       dyz2 = dy * dy;
       if constexpr (D == 3) {
@@ -224,7 +283,7 @@ __device__ inline void collect_slots(const Geom& g, const WaveCells<FLAT>& wc, b
       const int cl = lob + (j - offb);  // cell lane of the pair
       const bool valid = j < total && (unsigned)cl < 64u;
       const int e = entry_of(base + b);
-      const LdsEntryT<E>& P = lds[valid ? e : 0];
+      const auto& P = tile_entry<MORE>(tl, valid ? e : 0);
       const int xr = FLAT ? wc.x0 - (pkb >> 22) * nx : wc.x0;
       double dx = (double)(xr + cl) - P.x;
       dx = wrapb ? min_image(dx, px, nx) : dx + shb;
@@ -280,7 +339,7 @@ __device__ inline void collect_slots(const Geom& g, const WaveCells<FLAT>& wc, b
   if (__any(n > 1)) {
     int id[KSLOTS];
 #pragma unroll
-    for (int k = 0; k < KSLOTS; ++k) id[k] = k < n ? lds[s.e[k]].id : 0x7fffffff;
+    for (int k = 0; k < KSLOTS; ++k) id[k] = k < n ? tile_entry<MORE>(tl, s.e[k]).id : 0x7fffffff;
     // compare-exchange network on (id, e, eps): (0,1) (2,3) (0,2) (1,3) (1,2)
     auto cx = [&](int i, int k) {
       const bool sw = id[k] < id[i];
@@ -304,64 +363,59 @@ __device__ inline void collect_slots(const Geom& g, const WaveCells<FLAT>& wc, b
   }
 }
 
-
-template <typename E>
-__device__ __forceinline__ void fill_entry(LdsEntryT<E>& L, const PSnap& P, int id) {
-  L.x = P.x[0];
-  L.y = P.x[1];
-  L.z = P.x[2];
-  L.r = P.r;
-  L.cs = P.cs;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    if constexpr (std::is_same<E, float>::value) {
-      L.xh[a] = (float)P.x[a];
-      L.xl[a] = (float)(P.x[a] - (double)L.xh[a]);
-      L.uf[a] = (float)P.u[a];
-      L.wf[a] = (float)P.w[a];
-    } else {
-      L.u[a] = P.u[a];
-      L.w[a] = P.w[a];
+// MORE: the tile's list may be longer than what LDS holds; those that are take a
+// copy of the search of their own.
+template <int D, bool FLAT, bool MORE, typename E>
+__device__ __forceinline__ void collect_slots(const Geom& g, const WaveCells<FLAT>& wc, bool active,
+                                              const TileListT<E>& tl, double h, SlotsT<E>& s,
+                                              unsigned* err, SlotLdsT<E>& sl) {
+  if constexpr (MORE) {
+    if (tl.over) {
+      collect_slots_of<D, FLAT, true>(g, wc, active, tl, h, s, err, sl);
+      return;
     }
   }
-  L.id = id;
+  collect_slots_of<D, FLAT, false>(g, wc, active, tl, h, s, err, sl);
 }
 
 // Loads the tile's particle list into LDS (in list order: the slot search
-// orders each cell's slots by particle id) and clears its force accumulators.
-// Returns the list length (uniform over the block); when it is positive the
-// block has passed a barrier after the fill.  Must be called by the whole
-// block.
+// orders each cell's slots by particle id), as far as LDS holds it, and clears
+// the force accumulators of the entries held.  The list length is uniform over
+// the block; when it is positive the block has passed a barrier after the fill.
+// Must be called by the whole block.
 // `issue` is called once the loads of the count and the first ids are under
 // way: loads a kernel starts there travel beside the list's own chain (count
 // and ids, snapshots, LDS).
 template <typename E, typename Issue>
-__device__ inline int load_tile_list(const int* tile_count, const int* tile_list, int cap,
-                                     const PSnap* snap, int tile, LdsEntryT<E>* lds, double* acc,
-                                     int np, Issue issue) {
+__device__ inline TileListT<E> load_tile_list(const int* tile_count, const TileLists& ls,
+                                              const PSnap* snap, int tile, LdsEntryT<E>* lds,
+                                              double* acc, int np, Issue issue) {
   // each thread's first list entry is read alongside the count (entries past
   // the count are stale ids or zeros inside the list buffer, never used)
-  const int* lst = tile_list + (size_t)tile * cap;
+  const int* lst = ls.ids + (size_t)tile * ls.cap;
   const int e0 = (int)threadIdx.x;
-  const int pre = np > 0 && e0 < cap ? lst[e0] : 0;
+  const int pre = np > 0 && e0 < ls.cap ? lst[e0] : 0;
   int cnt = np > 0 ? tile_count[tile] : 0;
   issue();
-  if (cnt > cap) cnt = cap;
-  if (cnt == 0) return 0;
+  if (cnt > ls.cap + ls.more_cap) cnt = ls.cap + ls.more_cap;
+  const int held = cnt < ls.cap ? cnt : ls.cap;
+  const int over = __builtin_amdgcn_readfirstlane((int)(cnt > held));
+  const TileListT<E> tl{lds, cnt, held, over, ls.more + (size_t)tile * ls.more_cap, snap};
+  if (cnt == 0) return tl;
   // (the first entry apart from the loop: its id is waited for by itself, not
   // with every load issued after it)
-  if (e0 < cnt) fill_entry(lds[e0], snap[pre], pre);
-  for (int e = e0 + BLOCK; e < cnt; e += BLOCK) fill_entry(lds[e], snap[lst[e]], lst[e]);
+  if (e0 < held) fill_entry(lds[e0], snap[pre], pre);
+  for (int e = e0 + BLOCK; e < held; e += BLOCK) fill_entry(lds[e], snap[lst[e]], lst[e]);
   if (acc)
-    for (int k = threadIdx.x; k < 6 * cnt; k += BLOCK) acc[k] = 0.0;
+    for (int k = threadIdx.x; k < 6 * held; k += BLOCK) acc[k] = 0.0;
   __syncthreads();
-  return cnt;
+  return tl;
 }
 template <typename E>
-__device__ inline int load_tile_list(const int* tile_count, const int* tile_list, int cap,
-                                     const PSnap* snap, int tile, LdsEntryT<E>* lds, double* acc,
-                                     int np) {
-  return load_tile_list(tile_count, tile_list, cap, snap, tile, lds, acc, np, [] {});
+__device__ inline TileListT<E> load_tile_list(const int* tile_count, const TileLists& ls,
+                                              const PSnap* snap, int tile, LdsEntryT<E>* lds,
+                                              double* acc, int np) {
+  return load_tile_list(tile_count, ls, snap, tile, lds, acc, np, [] {});
 }
 
 // The calling wave's cells in a tile.
@@ -716,7 +770,7 @@ struct SmallDiv {
 // leaving out the box corners' tiles, a fifth, gained nothing.)
 template <int LPP>
 __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSnap& P, int s,
-                                 int lane, int* count, int* tile_list, int cap, unsigned* err) {
+                                 int lane, int* count, const TileLists& ls, unsigned* err) {
   const double R = P.r + h;
   const int L[3] = {g.nx, g.ny, g.nz};
   // (flat tiles: runs of x cells and of rows)
@@ -753,8 +807,10 @@ __device__ inline void bin_tiles(const Geom& g, int three_d, double h, const PSn
 #pragma unroll
       for (int j = 0; j < U; ++j) {
         if (t[j] < 0) continue;
-        if (slot[j] < cap)
-          tile_list[(size_t)t[j] * cap + slot[j]] = s;
+        if (slot[j] < ls.cap)
+          ls.ids[(size_t)t[j] * ls.cap + slot[j]] = s;
+        else if (slot[j] - ls.cap < ls.more_cap)
+          ls.more[(size_t)t[j] * ls.more_cap + (slot[j] - ls.cap)] = s;
         else
           atomicOr(err, ERR_SLOTS);
       }

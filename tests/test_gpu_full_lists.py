@@ -1,0 +1,194 @@
+"""Tile lists filled to max_tile_particles on lattices in flat tiles.
+
+max_tile_particles is what the lists of row tiles (the widest of 256, 128 and
+64 cells along x that pads the row least, in 2D 64; 256 cells in all) reach
+here, counted on the host; a flat tile, 256 consecutive cells of a plane, meets
+more particles than that, and more than the half as many again that its
+workgroup holds in LDS.  Fractions, steps, recomputed states and sensitivities
+against the oracle (FP64 1e-12, as everywhere), the reduced forms against an
+FP64 step from the very state they held (64 FP32 roundings of the largest
+deviation; FP16 storage adds 2^-11)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from helpers import _print_case, force_scale, relerr
+
+pytestmark = pytest.mark.gpu
+
+# q, nx, ny, nz, radius: short rows, rows of two waves and less, of 64 x 4 row tiles
+SIZES = [(19, 5, 60, 10, 1.2), (19, 10, 40, 12, 1.2), (19, 24, 30, 12, 1.2),
+         (19, 129, 24, 8, 1.6), (19, 190, 14, 9, 1.2), (19, 300, 12, 9, 1.2),
+         (9, 200, 60, 1, 1.2)]
+
+
+def _particles(q, L, r, seed):
+    """Spheres or disks on a jittered cubic lattice, filling the periodic box."""
+    rng = np.random.default_rng(seed)
+    D = 2 if q == 9 else 3
+    cnt = [max(1, int(L[a] / (2 * r + 0.6))) for a in range(D)]
+    idx = np.stack(np.meshgrid(*[np.arange(c) for c in cnt], indexing="ij"), -1).reshape(-1, D)
+    n = len(idx)
+    x, u, w = np.zeros((n, 3)), np.zeros((n, 3)), np.zeros((n, 3))
+    for a in range(D):
+        x[:, a] = (idx[:, a] + 0.5 + rng.uniform(-0.1, 0.1, n)) * L[a] / cnt[a] % L[a]
+        u[:, a] = rng.normal(0, 5e-3, n)
+    w[:, 0 if D == 3 else 2:] = rng.normal(0, 1e-3, (n, 3 if D == 3 else 1))
+    perm = rng.permutation(n)
+    return W.Particles(x[perm], u, w, np.full(n, r))
+
+
+def _longest(lat, p, tile):
+    """Longest list over the tiles (tile(x, y) -> number in the plane) of the
+    particles whose box X +- (r + h) holds a cell of the tile."""
+    counts = {}
+    D = 2 if lat.q == 9 else 3
+    L = (lat.nx, lat.ny, lat.nz)
+    for i in range(p.n):
+        R = p.r[i] + lat.h
+        ax = [np.unique(np.arange(np.ceil(p.x[i, a] - R), np.floor(p.x[i, a] + R) + 1).astype(int)
+                        % L[a]) if a < D else np.array([0]) for a in range(3)]
+        planes = np.unique(tile(ax[0][:, None], ax[1][None, :]))
+        for z in ax[2]:
+            for t in planes:
+                counts[t, z] = counts.get((t, z), 0) + 1
+    return max(counts.values())
+
+
+def _case(size):
+    q, nx, ny, nz, r = size
+    lat = W.LatticeSpec(q=q, nx=nx, ny=ny, nz=nz, tau=0.7, force=(2e-5, -1e-5, 0))
+    p = _particles(q, (nx, ny, nz), r, nx + ny)
+    twx = 64
+    if q == 19:
+        twx = min((256, 128, 64), key=lambda t: -(-nx // t) * t)
+    twy, across = 256 // twx, -(-nx // twx)
+    cap = _longest(lat, p, lambda x, y: x // twx + across * (y // twy))
+    flat = _longest(lat, p, lambda x, y: (x + nx * y) // 256)
+    assert flat > cap + cap // 2  # more than LDS holds
+    return lat, p, cap
+
+
+def _lattice(lat, p, cap, form="fp64"):
+    import paper_1901_09745_amd.psclbm as P
+    return P.Lattice(lat, form, max_particles=p.n, max_radius=float(p.r.max()),
+                     max_tile_particles=cap)
+
+
+@pytest.mark.parametrize("size", SIZES, ids=lambda s: "x".join(map(str, s)))
+def test_full_lists_step(size):
+    import torch
+    import paper_1901_09745_amd.psclbm as P
+    lat, p, cap = _case(size)
+    _print_case(test="full lists", size=size, n=p.n, max_tile_particles=cap)
+    f0 = W.random_state(lat, 9, amp=1e-2)
+    ref = oracle.Lattice(lat, f0)
+    G = _lattice(lat, p, cap)
+    G.set_f(torch.from_numpy(f0).cuda())
+    dp = P.DeviceParticles.from_host(p)
+    G.rasterize(dp)
+    _, ids, seps = G.solid_fraction()
+    _, rid, reps, _ = oracle.rasterize(lat, p.x, p.r)
+    assert np.array_equal(ids.cpu().numpy().reshape(-1, 4), np.asarray(rid)[:, :4])
+    assert np.abs(seps.cpu().numpy().reshape(-1, 4) - np.asarray(reps)[:, :4]).max() < 1e-13
+    for _ in range(3):
+        before = ref.f.copy()
+        F, T = ref.step(p)
+        G.step(1)
+    G.sync()
+    assert relerr(G.get_f().cpu().numpy(), ref.f) < 1e-12
+    Fg, Tg = (t.cpu().numpy() for t in G.forces())
+    tol = 1e-12 * force_scale(lat, before, p) + 1e-300
+    assert np.all(np.abs(Fg - F).max(1) <= tol)
+    assert np.all(np.abs(Tg - T).max(1) <= tol * (p.r + lat.h))
+    ring = torch.empty((2,) + f0.shape, dtype=torch.float64, device="cuda")
+    P.lbm_recompute(G.ctx, torch.from_numpy(f0).cuda(), 2, ring)
+    again = oracle.Lattice(lat, f0)
+    for k in range(2):
+        again.step(p)
+        assert relerr(ring[k].cpu().numpy(), again.f) < 1e-12
+    # the reduced forms, both parities
+    w = np.array([4 / 9] + [1 / 9] * 4 + [1 / 36] * 4 if lat.q == 9 else
+                 [1 / 3] + [1 / 18] * 6 + [1 / 36] * 12).reshape(-1, 1, 1, 1)
+    H = _lattice(lat, p, cap)
+    H.rasterize(dp)
+    for form, store in (("fp32", 0.0), ("fp16", 2.0 ** -11)):
+        R = _lattice(lat, p, cap, form)
+        R.set_f(torch.from_numpy(f0).cuda())
+        R.rasterize(dp)
+        for _ in range(2):
+            held = R.get_f()
+            H.set_f(held)
+            H.step(1)
+            R.step(1)
+            a, b = H.get_f().cpu().numpy(), R.get_f().cpu().numpy()
+            big = max(np.abs(a - w).max(), np.abs(held.cpu().numpy() - w).max())
+            assert np.abs(a - b).max() <= (64 * 2.0 ** -24 + store) * big
+            # a force is a sum of fewer than 256 such cell terms
+            Fr, Fh = R.forces()[0].cpu().numpy(), H.forces()[0].cpu().numpy()
+            assert np.abs(Fr - Fh).max() <= 256 * 64 * 2.0 ** -24 * big
+        R.sync()
+        H.sync()
+
+
+@pytest.mark.parametrize("size", SIZES, ids=lambda s: "x".join(map(str, s)))
+def test_full_lists_adjoint(size):
+    """One adjoint step against the directional derivative of the oracle's step
+    (central differences, h = 1e-6, whose rounding is eps times the sizes of the
+    sums over h), and the adjoint of the fractions against their derivative
+    (x_n - X)/|x_n - X| on the linear band."""
+    import torch
+    import paper_1901_09745_amd.psclbm as P
+    lat, p, cap = _case(size)
+    _print_case(test="full lists adjoint", size=size, n=p.n, max_tile_particles=cap)
+    rng = np.random.default_rng(4)
+    D = 2 if lat.q == 9 else 3
+    f0 = W.random_state(lat, 10, amp=1e-2)
+    lam, gF, gT = rng.normal(size=f0.shape), rng.normal(size=(p.n, 3)), rng.normal(size=(p.n, 3))
+    df, du, dw = rng.normal(size=f0.shape) * 1e-2, rng.normal(size=(p.n, 3)), rng.normal(size=(p.n, 3))
+    if D == 2:
+        gF[:, 2] = du[:, 2] = 0
+        gT[:, :2] = dw[:, :2] = 0
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    zero = lambda: torch.zeros((p.n, 3), dtype=torch.float64, device="cuda")  # noqa: E731
+    G = _lattice(lat, p, cap)
+    G.rasterize(P.DeviceParticles.from_host(p))
+    out = torch.empty(f0.shape, dtype=torch.float64, device="cuda")
+    gx, gu, gw = zero(), zero(), zero()
+    P.lbm_step_adjoint(G.ctx, t(f0), t(lam), out, t(gF), t(gT), gx, gu, gw, None)
+    G.sync()
+
+    def J(h):
+        S = oracle.Lattice(lat, f0 + h * df)
+        F, T = S.step(W.Particles(p.x, p.u + h * du, p.omega + h * dw, p.r))
+        return np.array([(S.f * lam).sum(), (F * gF).sum(), (T * gT).sum()])
+
+    h = 1e-6
+    num = ((J(h) - J(-h)) / (2 * h)).sum()
+    got = float((out.cpu().numpy() * df).sum() + (gu.cpu().numpy() * du).sum() +
+                (gw.cpu().numpy() * dw).sum())
+    size_ = np.abs(f0 * lam).sum() + 100.0
+    assert abs(got - num) <= 4 * 2.0 ** -53 * size_ / h + 1e-9 * abs(num)
+
+    # the fractions alone
+    _, rid, reps, _ = oracle.rasterize(lat, p.x, p.r)
+    ids, eps = np.asarray(rid)[:, :4], np.asarray(reps)[:, :4]
+    gs = rng.normal(size=ids.shape)
+    gX = zero()
+    P.psc_rasterize_adjoint(G.ctx, t(gs), 4, gX)
+    G.sync()
+    cell = np.stack(np.unravel_index(np.arange(lat.ncells), lat.shape)[::-1], -1)
+    want, scale = np.zeros((p.n, 3)), np.zeros(p.n)
+    for k in range(4):
+        c = np.nonzero((ids[:, k] >= 0) & (eps[:, k] > 0) & (eps[:, k] < 1))[0]
+        s = ids[c, k]
+        d = (cell[c] - p.x[s])[:, :D]
+        L = np.array([lat.nx, lat.ny, lat.nz])[:D]
+        d -= L * np.round(d / L)
+        dist = np.sqrt((d ** 2).sum(1))
+        on = np.abs(dist - p.r[s]) < lat.h
+        for a in range(D):
+            np.add.at(want[:, a], s[on], (gs[c, k] * d[:, a] / dist)[on])
+        np.add.at(scale, s[on], np.abs(gs[c, k])[on])
+    assert np.all(np.abs(gX.cpu().numpy() - want).max(1) <= 1e-12 * scale + 1e-300)
