@@ -79,12 +79,15 @@ int validate(const psclbm_config* c) {
 // against 531-556 us with 64-wide tiles).  2D: 64 x 4 tiles, whose four rows
 // share one short particle list (512 x 256 FP64 step 11.7 against 14.6 us
 // with 256-wide tiles, FP32 the same).  PSCLBM_TILE_X in the environment (64,
-// 128 or 256) overrides the choice, for measurements.
+// 128 or 256) overrides the choice, and that of flat tiles, for measurements.
+int tile_width_asked() {
+  const char* e = std::getenv("PSCLBM_TILE_X");
+  const int v = e ? std::atoi(e) : 0;
+  return v == 64 || v == 128 || v == 256 ? v : 0;
+}
+
 int tile_width(int nx, int nz) {
-  if (const char* e = std::getenv("PSCLBM_TILE_X")) {
-    const int v = std::atoi(e);
-    if (v == 64 || v == 128 || v == 256) return v;
-  }
+  if (const int v = tile_width_asked()) return v;
   if (nz == 1) return 64;
   int best = 64;
   long long pad = ((long long)nx + 63) / 64 * 64;
@@ -133,7 +136,7 @@ int nt_even(const psclbm_config* c, bool flat) {
 //   its own lanes, and that launch costs 5 us.
 //   Not with lists longer than 160: a flat tile's is half as long again, in LDS.
 bool flat_tiles(const psclbm_config* c) {
-  if (c->nx % SEG == 0) return false;
+  if (c->nx % SEG == 0 || tile_width_asked()) return false;
   if (c->max_particles > 0 && c->max_tile_particles > 160) return false;
   if (c->lattice == 9 && (c->nx < SEG || c->nx >= 0.85 * ((c->nx + SEG - 1) / SEG * SEG)))
     return false;
