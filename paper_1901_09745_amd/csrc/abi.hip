@@ -118,6 +118,24 @@ int nt_even(const psclbm_config* c, bool flat) {
   return distribution_bytes(c) > 256.0 * 1024 * 1024 ? 1 : 0;
 }
 
+// Entries a flat tile's particle list takes at most: every particle of the row
+// tiles that it overlaps, so that particles whose row lists fit max_tile_particles
+// fit here too.  Its 256 cells lie in at most `rows` rows, these in `bands` rows of
+// row tiles, and in each row they touch a run of row tiles.
+int flat_list(const psclbm_config* c) {
+  const int twx = tile_width(c->nx, c->nz), twy = BLOCK / twx;
+  const int rows = std::min((BLOCK - 2) / c->nx + 2, c->ny);
+  const int across = (c->nx + twx - 1) / twx;
+  const int bands = std::min((rows + twy - 2) / twy + 1, (c->ny + twy - 1) / twy);
+  const long long tiles = std::min(bands * (long long)across, BLOCK / twx + 2LL * rows);
+  return (int)std::min(tiles * c->max_tile_particles, (long long)c->max_particles);
+}
+
+// and those of them that its workgroup holds in LDS
+int flat_list_lds(const psclbm_config* c) {
+  return std::min(c->max_tile_particles + c->max_tile_particles / 2, flat_list(c));
+}
+
 // Flat tiles (256 consecutive cells of a plane) instead of row tiles, which
 // leave lanes of each row's last 64-cell segment without a cell (a wave that
 // costs as many instructions and as much latency as a full one) and, in rows
@@ -131,14 +149,30 @@ int nt_even(const psclbm_config* c, bool flat) {
 //   2D: only rows of 64 or more that are less than 85 % full (70: 1.06-1.12
 //   times faster, 200: 1.02-1.09); fuller ones gain nothing, and with particles
 //   rows of 40-50 lose 10 % (each row of a wave is searched by itself).
+//   With lists that may be longer than LDS holds, not on small lattices whose
+//   rows are well filled, where split lines cost little and the look-ups and the
+//   rows of a wave searched one by one cost more:
+//   3D: distributions within the 256 MB last-level cache and rows 70 % full or
+//   more.  A coupled step takes, row / flat tiles, at one particle in 800 to 20000
+//   cells, 100x50x50 (78 %) 0.84-1.0 (FP32 21.0 against 24.9 us), 190x96x96 (99 %)
+//   0.86-0.94 (FP64 101 against 118), 90x100x100 (70 %) 0.95-1.12, 80x80x80 (62 %)
+//   0.99-1.14, rows of 10 to 20 1.1-1.6; larger lattices 1.04-1.38.
+//   2D: up to 2^18 cells (four workgroups a CU): 70x200 0.81-0.86 (18.5 against
+//   21.6 us), 200x200 0.96, 100x2500 0.92-1.0; 150x2500 0.99-1.02, 70x8000
+//   1.07-1.18, 200x30000 0.94-1.2.
 //   Not with an outlet on an x face unless other outlet faces need their
-//   velocities read before the step anyway: a flat wave cannot take them from
-//   its own lanes, and that launch costs 5 us.
-//   Not with lists longer than 160: a flat tile's is half as long again, in LDS.
+//   velocities read before the step anyway: the cells whose neighbour is in
+//   another flat wave need that launch, 5 us.
+//   Not with max_tile_particles over 160: a flat list holds half as much again in
+//   LDS.
 bool flat_tiles(const psclbm_config* c) {
   if (c->nx % SEG == 0 || tile_width_asked()) return false;
   if (c->max_particles > 0 && c->max_tile_particles > 160) return false;
-  if (c->lattice == 9 && (c->nx < SEG || c->nx >= 0.85 * ((c->nx + SEG - 1) / SEG * SEG)))
+  const double full = (double)c->nx / ((c->nx + SEG - 1) / SEG * SEG);
+  if (c->lattice == 9 && (c->nx < SEG || full >= 0.85)) return false;
+  if (c->max_particles > 0 && flat_list(c) > flat_list_lds(c) &&
+      (c->lattice == 9 ? (double)c->nx * c->ny <= 262144.0
+                       : full >= 0.7 && distribution_bytes(c) <= 256.0 * 1024 * 1024))
     return false;
   bool x_outlet = false, other = false;
   for (int f = 0; f < (c->lattice == 9 ? 4 : 6); ++f)
@@ -185,17 +219,8 @@ Layout plan(const psclbm_config* c, bool may_be_flat = true) {
   l.list_cap = c->max_tile_particles;
   l.more_cap = 0;
   if (l.flat && np > 0) {
-    // A flat tile's list takes every particle of the row tiles that it overlaps
-    // (a list that a row tile had room for never overflows on a flat one): its
-    // 256 cells lie in at most `rows` rows, these in `bands` rows of row tiles,
-    // and in each row they touch a run of row tiles.
-    const int rows = std::min((BLOCK - 2) / c->nx + 2, c->ny);
-    const int across = (c->nx + l.twx - 1) / l.twx;
-    const int bands = std::min((rows + l.twy - 2) / l.twy + 1, (c->ny + l.twy - 1) / l.twy);
-    const long long tiles = std::min(bands * (long long)across, BLOCK / l.twx + 2LL * rows);
-    const int all = (int)std::min(tiles * c->max_tile_particles, (long long)np);
-    l.list_cap = std::min(c->max_tile_particles + c->max_tile_particles / 2, all);
-    l.more_cap = all - l.list_cap;
+    l.list_cap = flat_list_lds(c);
+    l.more_cap = flat_list(c) - l.list_cap;
   }
   const int cap = np > 0 ? l.list_cap + l.more_cap : 1;
   bool outlet = false;

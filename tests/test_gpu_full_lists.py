@@ -1,4 +1,4 @@
-"""Tile lists filled to max_tile_particles on lattices in flat tiles.
+"""Tile lists filled to max_tile_particles on lattices that flat tiles are for.
 
 max_tile_particles is what the lists of row tiles (the widest of 256, 128 and
 64 cells along x that pads the row least, in 2D 64; 256 cells in all) reach
@@ -18,9 +18,10 @@ from helpers import _print_case, force_scale, relerr
 pytestmark = pytest.mark.gpu
 
 # q, nx, ny, nz, radius: short rows, rows of two waves and less, of 64 x 4 row tiles
+# (190, 300 and the smaller 2D lattice stay in row tiles while they are this small)
 SIZES = [(19, 5, 60, 10, 1.2), (19, 10, 40, 12, 1.2), (19, 24, 30, 12, 1.2),
          (19, 129, 24, 8, 1.6), (19, 190, 14, 9, 1.2), (19, 300, 12, 9, 1.2),
-         (9, 200, 60, 1, 1.2)]
+         (9, 200, 60, 1, 1.2), (9, 200, 1320, 1, 1.2)]
 
 
 def _particles(q, L, r, seed):
