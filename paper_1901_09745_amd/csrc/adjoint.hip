@@ -62,7 +62,7 @@ struct AdjArgs {
   double* outlet_g;       // [6][face cells][3], dJ/du of that velocity
   long long face_stride;
   unsigned inlet_mask, outlet_mask, moving_mask;
-  unsigned outlet_wave;   // outlet faces (x only) whose neighbour is in the same wave
+  unsigned outlet_wave;   // outlet faces (x only) served from the neighbour's lane
 };
 
 template <int Q>
@@ -81,7 +81,9 @@ __device__ __forceinline__ double feq_i(int i, double rho, double ux, double uy,
 // loads started first, 180 with the slots' gradients summed over lanes before
 // the LDS atomics, 162 with the hints (5.0 TB/s).  1024^2 with 1600 disks 60
 // -> 52 us (open faces compiled out, three waves); the 512x256 channel 17.0 ->
-// 13.1 (the inlet's gradient summed per tile).
+// 13.1 (the inlet's gradient summed per tile).  The open 200x100x100 box in flat
+// tiles 319 -> 235 (x outlets from the neighbour's lane, as in row tiles; faces'
+// passes with a cell's loads in flight together).
 // WIDE: arrays of 4 GiB or more a direction (the reduced forms hold up to 2^31
 // cells, and the sensitivities are FP64 in every form), addressed in 64 bits.
 template <int Q, bool WALLS, bool FLAT, bool NT, bool WIDE = false>
@@ -195,6 +197,7 @@ __global__ void __launch_bounds__(BLOCK)
 
     // inlet / outlet reset (as in the forward: outlets first, an inlet wins)
     int reset = 0, rface = 0;
+    bool by_lane = false;  // of an outlet: its neighbour is in this wave
     double ub0 = 0.0, ub1 = 0.0, ub2 = 0.0;
     double rho = rho_in, jx = j0, jy = j1, jz = j2;
     if (WALLS && active && (a.inlet_mask | a.outlet_mask)) {
@@ -203,7 +206,8 @@ __global__ void __launch_bounds__(BLOCK)
         const bool on = fc == 0 ? x == 0 : fc == 1 ? x == d.nx - 1 : fc == 2 ? y == 0
                       : fc == 3 ? y == d.ny - 1 : fc == 4 ? z == 0 : z == d.nz - 1;
         if (((a.outlet_mask >> fc) & 1u) && on) {
-          if ((a.outlet_wave >> fc) & 1u) {
+          by_lane = ((a.outlet_wave >> fc) & 1u) && !(FLAT && lane == (fc == 0 ? SEG - 1 : 0));
+          if (by_lane) {
             ub0 = wu0; ub1 = wu1; ub2 = wu2;
           } else {
             const unsigned k = fc < 2 ? (unsigned)y + (unsigned)d.ny * z
@@ -495,7 +499,7 @@ __global__ void __launch_bounds__(BLOCK)
           atomicAdd(face_acc + 3 * rface + 1, g1);
           atomicAdd(face_acc + 3 * rface + 2, g2);
         }
-      } else if (!((a.outlet_wave >> rface) & 1u)) {
+      } else if (!by_lane) {
         const unsigned k = rface < 2 ? (unsigned)y + (unsigned)d.ny * z
                                      : (rface < 4 ? (unsigned)x + (unsigned)d.nx * z
                                                   : (unsigned)x + (unsigned)d.nx * y);
@@ -512,7 +516,7 @@ __global__ void __launch_bounds__(BLOCK)
 #pragma unroll
       for (int fc = 0; fc < 2; ++fc) {
         if (!((a.outlet_wave >> fc) & 1u)) continue;
-        const bool mine = reset == 2 && rface == fc;
+        const bool mine = reset == 2 && rface == fc && by_lane;
         const int nbx = fc == 0 ? 1 : d.nx - 2;
         const int src = x == nbx ? (fc == 0 ? lane - 1 : lane + 1) : lane;
         const double v0 = __shfl(mine ? g0 : 0.0, src);
@@ -558,70 +562,46 @@ __global__ void __launch_bounds__(BLOCK)
   }
 }
 
-// Velocity (Eq. 5) of each outlet cell's interior neighbour, from a canonical
-// FP64 state.
-__global__ void k_outlet_velocity_canon(Geom g, int face, const double* f, double fx, double fy,
-                                        double fz, double* out, long long stride) {
-  const int ax = face / 2;
-  const int u1 = ax == 0 ? 1 : 0, u2 = ax == 2 ? 1 : 2;
-  const int Ld[3] = {g.nx, g.ny, g.nz};
-  const long long cells = (long long)Ld[u1] * Ld[u2];
-  const int q = g.q;
-  for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < cells;
-       k += (long long)gridDim.x * blockDim.x) {
-    int p[3];
-    p[u1] = (int)(k % Ld[u1]);
-    p[u2] = (int)(k / Ld[u1]);
-    p[ax] = (face % 2 == 0) ? 1 : Ld[ax] - 2;
-    const long long m = p[0] + (long long)g.nx * (p[1] + (long long)g.ny * p[2]);
-    double rho = 0.0, j0 = 0.0, j1 = 0.0, j2 = 0.0;
-    for (int i = 0; i < q; ++i) {
-      const double fi = f[(size_t)i * g.N + m];
-      const int ex = q == 9 ? Lattice<9>::ex(i) : Lattice<19>::ex(i);
-      const int ey = q == 9 ? Lattice<9>::ey(i) : Lattice<19>::ey(i);
-      const int ez = q == 9 ? Lattice<9>::ez(i) : Lattice<19>::ez(i);
-      rho += fi;
-      j0 += ex * fi;
-      j1 += ey * fi;
-      j2 += ez * fi;
-    }
-    double* o = out + ((size_t)face * stride + k) * 3;
-    o[0] = (j0 + 0.5 * fx) / rho;
-    o[1] = (j1 + 0.5 * fy) / rho;
-    o[2] = (j2 + 0.5 * fz) / rho;
-  }
-}
-
 // Outlet cells: the sensitivity of the reset velocity goes to the interior
 // neighbour's state through u = (sum f e + F/2)/rho: lam_j += g . (e_j - u)/rho.
+// One face a launch, since two faces may have a neighbour in common; all Q loads
+// of a cell in flight together.  edge: only the cells at the waves' edges.
 template <int Q>
-__global__ void k_outlet_adjoint(Geom g, int face, const double* f, const double* gu,
-                                 double* lam, double fx, double fy, double fz, long long stride) {
+__global__ void __launch_bounds__(256) k_outlet_adjoint(Geom g, int face, int edge, const double* f,
+                                                        const double* gu, double* lam, double fx,
+                                                        double fy, double fz, long long stride) {
   using L = Lattice<Q>;
+  const Dims d = dims_of(g);
   const int ax = face / 2;
-  const int u1 = ax == 0 ? 1 : 0, u2 = ax == 2 ? 1 : 2;
-  const int Ld[3] = {g.nx, g.ny, g.nz};
-  const long long cells = (long long)Ld[u1] * Ld[u2];
-  for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < cells;
-       k += (long long)gridDim.x * blockDim.x) {
-    int p[3];
-    p[u1] = (int)(k % Ld[u1]);
-    p[u2] = (int)(k / Ld[u1]);
-    p[ax] = (face % 2 == 0) ? 1 : Ld[ax] - 2;
-    const long long m = p[0] + (long long)g.nx * (p[1] + (long long)g.ny * p[2]);
+  const unsigned w1 = (unsigned)(ax == 0 ? d.ny : d.nx);
+  const unsigned cells = w1 * (unsigned)(ax == 2 ? d.ny : d.nz);
+  const int inner = (face % 2 == 0) ? 1 : (ax == 0 ? d.nx : ax == 1 ? d.ny : d.nz) - 2;
+  const unsigned N = (unsigned)g.N;
+  for (unsigned k = blockIdx.x * 256u + threadIdx.x; k < cells; k += gridDim.x * 256u) {
+    const int b = (int)(k / w1), a = (int)(k - (unsigned)b * w1);
+    const int x = ax == 0 ? inner : a;
+    const int y = ax == 0 ? a : ax == 1 ? inner : b;
+    const int z = ax == 2 ? inner : b;
+    if (edge && !at_wave_edge(d, face, y)) continue;
+    const unsigned n = (unsigned)x + d.sy * (unsigned)y + d.sz * (unsigned)z;
+    double v[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) v[i] = f[(size_t)i * N + n];
     double rho = 0.0, j0 = 0.0, j1 = 0.0, j2 = 0.0;
+#pragma unroll
     for (int i = 0; i < Q; ++i) {
-      const double fi = f[(size_t)i * g.N + m];
-      rho += fi;
-      j0 += L::ex(i) * fi;
-      j1 += L::ey(i) * fi;
-      j2 += L::ez(i) * fi;
+      rho += v[i];
+      eacc(L::ex(i), j0, v[i]);
+      eacc(L::ey(i), j1, v[i]);
+      eacc(L::ez(i), j2, v[i]);
     }
     const double ux = (j0 + 0.5 * fx) / rho, uy = (j1 + 0.5 * fy) / rho, uz = (j2 + 0.5 * fz) / rho;
     const double* gv = gu + ((size_t)face * stride + k) * 3;
+    const double g0 = gv[0], g1 = gv[1], g2 = gv[2];
+#pragma unroll
     for (int j = 0; j < Q; ++j)
-      lam[(size_t)j * g.N + m] +=
-          (gv[0] * (L::ex(j) - ux) + gv[1] * (L::ey(j) - uy) + gv[2] * (L::ez(j) - uz)) / rho;
+      lam[(size_t)j * N + n] +=
+          (g0 * (L::ex(j) - ux) + g1 * (L::ey(j) - uy) + g2 * (L::ez(j) - uz)) / rho;
   }
 }
 
@@ -673,9 +653,13 @@ static void launch_step_adjoint(psclbm_ctx* c, const AdjArgs& a, size_t lds) {
     return;
   }
   // (rows of whole lines only: see the even steps' choice)
-  const bool nt = !FLAT && (double)c->geom.N * Q * sizeof(double) > 256.0 * 1024 * 1024;
-  if (nt) k_adjoint<Q, WALLS, FLAT, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
-  else k_adjoint<Q, WALLS, FLAT, false><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+  if constexpr (!FLAT) {
+    if ((double)c->geom.N * Q * sizeof(double) > 256.0 * 1024 * 1024) {
+      k_adjoint<Q, WALLS, FLAT, true><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
+      return;
+    }
+  }
+  k_adjoint<Q, WALLS, FLAT, false><<<c->ntiles, BLOCK, lds, c->stream>>>(a);
 }
 template <int Q>
 static void launch_step_adjoint(psclbm_ctx* c, const AdjArgs& a, bool walls, size_t lds) {
@@ -719,28 +703,27 @@ int launch_adjoint(psclbm_ctx* c, const double* f, const double* lam_in, double*
     if (c->geom.face[fc] == PSCLBM_OUTLET_EQ) a.outlet_mask |= 1u << fc;
     if (c->geom.face[fc] == PSCLBM_MOVING_WALL) a.moving_mask |= 1u << fc;
   }
-  a.outlet_wave = c->geom.flat ? 0u : outlet_wave_mask(c->geom, a.outlet_mask);
-  const unsigned separate = a.outlet_mask & ~a.outlet_wave;
+  a.outlet_wave = outlet_wave_mask(c->geom, a.outlet_mask);
+  const unsigned edges = outlet_edges(c->geom, a.outlet_wave);
+  const unsigned separate = (a.outlet_mask & ~a.outlet_wave) | edges;
   const double* F = c->cfg.body_force;
   const int fgrid = (int)((c->face_stride + 255) / 256 < 4096 ? (c->face_stride + 255) / 256 : 4096);
-  for (int fc = 0; fc < 6; ++fc) {
-    if (!((separate >> fc) & 1u)) continue;
-    k_outlet_velocity_canon<<<fgrid, 256, 0, c->stream>>>(c->geom, fc, f, F[0], F[1], F[2],
-                                                          c->outlet_u, c->face_stride);
-  }
+  int rc = launch_outlet_velocity(c, f, PSCLBM_FP64, 0, separate, edges);
+  if (rc) return rc;
   const size_t lds = c->np > 0 ? (sizeof(LdsEntry) + 9 * sizeof(double)) * (size_t)c->lists.cap : 0;
   const bool walls = !(c->geom.periodic[0] && c->geom.periodic[1] && c->geom.periodic[2]);
   if (c->geom.q == 9) launch_step_adjoint<9>(c, a, walls, lds);
   else launch_step_adjoint<19>(c, a, walls, lds);
-  int rc = hip_ok(hipGetLastError());
+  rc = hip_ok(hipGetLastError());
   if (rc) return rc;
   for (int fc = 0; fc < 6; ++fc) {
     if (!((separate >> fc) & 1u)) continue;
+    const int edge = (int)((edges >> fc) & 1u);
     if (c->geom.q == 9)
-      k_outlet_adjoint<9><<<fgrid, 256, 0, c->stream>>>(c->geom, fc, f, c->outlet_g, lam_out,
+      k_outlet_adjoint<9><<<fgrid, 256, 0, c->stream>>>(c->geom, fc, edge, f, c->outlet_g, lam_out,
                                                         F[0], F[1], F[2], c->face_stride);
     else
-      k_outlet_adjoint<19><<<fgrid, 256, 0, c->stream>>>(c->geom, fc, f, c->outlet_g, lam_out,
+      k_outlet_adjoint<19><<<fgrid, 256, 0, c->stream>>>(c->geom, fc, edge, f, c->outlet_g, lam_out,
                                                          F[0], F[1], F[2], c->face_stride);
   }
   return hip_ok(hipGetLastError());

@@ -210,6 +210,11 @@ inline unsigned outlet_wave_mask(const Geom& g, unsigned outlet_mask) {
   return m;
 }
 
+// The faces of outlet_wave with such cells.
+inline unsigned outlet_edges(const Geom& g, unsigned outlet_wave) {
+  return g.flat ? outlet_wave : 0u;
+}
+
 }  // namespace psclbm
 
 struct psclbm_ctx {
@@ -409,6 +414,11 @@ int launch_coupled(psclbm_ctx* c, const psclbm_dem_params* prm, double* x, doubl
 int launch_solid_fraction(psclbm_ctx* c, double* eps, int* ids, double* seps, int k);
 int launch_step(psclbm_ctx* c, bool mass);
 int launch_recompute(psclbm_ctx* c, const double* f0, int nsteps, double* ring);
+// Velocities (Eq. 5) of the interior neighbours of the outlet cells of `faces`, and
+// of those of `edges` only at the waves' edges, into outlet_u, from a state in
+// storage form `prec` at streaming parity `par`.
+int launch_outlet_velocity(psclbm_ctx* c, const void* f, int prec, int par, unsigned faces,
+                           unsigned edges);
 int launch_mass(psclbm_ctx* c, double* h_mass);
 int launch_zero(psclbm_ctx* c, void* p, size_t bytes);
 int launch_dem_step(psclbm_ctx* c, const psclbm_dem_params* prm, double* x, double* u,

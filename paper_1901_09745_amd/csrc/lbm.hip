@@ -975,9 +975,7 @@ __global__ void __launch_bounds__(256) k_outlet_velocity(Geom g, const void* f, 
     const int z = ax == 2 ? inner : b;
     // edges: x faces whose cells take the velocity from the neighbour's lane but
     // for those whose neighbour is in the next flat wave
-    if (((edges >> face) & 1u) &&
-        (((unsigned)(face ? d.nx - 1 : 0) + d.sy * (unsigned)y) % SEG) != (face ? 0u : SEG - 1u))
-      continue;
+    if (((edges >> face) & 1u) && !at_wave_edge(d, face, y)) continue;
     const unsigned n = (unsigned)x + d.sy * (unsigned)y + d.sz * (unsigned)z;
     S v[Q];
 #pragma unroll
@@ -1419,12 +1417,9 @@ static StepArgs step_args(psclbm_ctx* c) {
   return a;
 }
 
-// Velocities of the outlets that the step does not take from its own lanes,
-// from a state in storage form `prec` at streaming parity `par`.
-static int outlet_velocity(psclbm_ctx* c, const void* f, int prec, int par, const StepArgs& a) {
+int launch_outlet_velocity(psclbm_ctx* c, const void* f, int prec, int par, unsigned faces,
+                           unsigned edges) {
   const double* F = c->cfg.body_force;
-  const unsigned edges = c->geom.flat ? a.outlet_wave : 0u;
-  const unsigned faces = (a.outlet_mask & ~a.outlet_wave) | edges;
   if (!faces) return PSCLBM_OK;
   const dim3 grid((unsigned)grid_for(c->face_stride), (unsigned)__builtin_popcount(faces));
   if (par)
@@ -1468,7 +1463,9 @@ int launch_step_contacts(psclbm_ctx* c, bool mass, const DemArgs* dem, const dou
     a.fc = c->fcontact;
   }
   // outlets whose neighbour is in another wave: velocities before the step
-  int rc = outlet_velocity(c, c->f, c->prec, par, a);
+  const unsigned edges = outlet_edges(a.g, a.outlet_wave);
+  int rc = launch_outlet_velocity(c, c->f, c->prec, par, (a.outlet_mask & ~a.outlet_wave) | edges,
+                                  edges);
   if (rc) return rc;
   const size_t lds = step_lds(c);
   if (c->prec == PSCLBM_FP64)
@@ -1491,9 +1488,11 @@ int launch_recompute(psclbm_ctx* c, const double* f0, int nsteps, double* ring) 
   a.mass_part = nullptr;
   const size_t lds = step_lds(c);
   const size_t QN = (size_t)c->geom.q * (size_t)c->geom.N;
+  const unsigned edges = outlet_edges(a.g, a.outlet_wave);
   for (int k = 0; k < nsteps; ++k) {
     const double* src = k == 0 ? f0 : ring + (size_t)(k - 1) * QN;
-    int rc = outlet_velocity(c, src, PSCLBM_FP64, 0, a);
+    int rc = launch_outlet_velocity(c, src, PSCLBM_FP64, 0,
+                                    (a.outlet_mask & ~a.outlet_wave) | edges, edges);
     if (rc) return rc;
     a.src = src;
     a.f = ring + (size_t)k * QN;

@@ -504,6 +504,12 @@ __device__ __forceinline__ Dims dims_of(const Geom& g) {
   return d;
 }
 
+// The neighbour of row y's cell at the x face `face` is in another flat wave.
+__device__ __forceinline__ bool at_wave_edge(const Dims& d, int face, int y) {
+  const unsigned p = (unsigned)(face ? d.nx - 1 : 0) + d.sy * (unsigned)y;
+  return p % SEG == (face ? 0u : SEG - 1u);
+}
+
 // Element `e` of a per-direction array through a 32-bit byte offset, in the
 // global address space, so the access is the scalar base plus one 32-bit
 // vector offset.
