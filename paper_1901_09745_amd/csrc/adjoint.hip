@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(BLOCK)
   // before the tile's list is waited for and used after the slot search.
   double ls[Q], fv[Q];
   auto issue = [&] {
-    // (lanes without a cell read the wave's first: no branch, so that the
+    // (lanes without a cell read the last one's: no branch, so that the
     // number of loads under way is known when the list's ids are waited for)
     if (lk.inner) {
 #pragma unroll

@@ -751,12 +751,13 @@ __device__ inline AxisRuns axis_runs(int lo, int hi, int L, int sh, int periodic
   return r;
 }
 
-// k / n and k % n for 0 <= k < 2^20 and 1 <= n < 2^20 in FP32: (k + 1/2) / n
-// stays 1 / (2 n) from a whole number, the product is off by less than 2^-22 of
-// its value, so the quotient is exact while k < 2^20 (larger: by division).
-// Lanes a particle where only its rasterisation needs several (measured below).
+// Lanes a particle where only its rasterisation needs several (measured at the
+// DEM kernel).
 constexpr int RASTER_LANES = 32;
 
+// k / n for 0 <= k < 2^20 and n >= 1 in FP32: (k + 1/2) / n stays 1 / (2 n) from a
+// whole number, the product is off by less than 2^-22 of its value, so the
+// quotient is exact while k < 2^20 (larger: by division).
 struct SmallDiv {
   int n;
   float r;
@@ -877,9 +878,9 @@ __device__ inline int dem_bin_coord(double x, int L, int periodic, int nbin, dou
   return b;
 }
 
-// A place for a particle at position x in its DEM bin of the target set: the
-// record's index, or -1 when the bin is full (called by one lane per particle,
-// early: the atomic's return is waited for at the record's store).
+// A place for a particle at position x in its DEM bin of the target set: the bin
+// and the slot in it, bin_cap or more when the bin is full (called by one lane per
+// particle, early: the atomic's return is waited for at the record's store).
 struct DemPlace {
   int bin, slot;
 };
