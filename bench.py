@@ -47,6 +47,7 @@ from __future__ import annotations
 import argparse
 import hashlib
 import json
+import math
 import os
 import sys
 import time
@@ -641,6 +642,29 @@ def _traffic(kernel_key):
     return ent.get("bytes_per_launch")
 
 
+def _rounded(v, digits=7):
+    """v with every float at `digits` significant digits."""
+    if isinstance(v, float) and math.isfinite(v):
+        return float(f"{v:.{digits}g}")
+    if isinstance(v, dict):
+        return {k: _rounded(x, digits) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [_rounded(x, digits) for x in v]
+    return v
+
+
+# the runs of the paper's own tests: tables of their own, not figures of the metric
+DETAILS = ("ergun", "packing", "drag")
+
+
+def split_line(out):
+    """(details, line): the tables of DETAILS as one JSON object, and the
+    metric's line without them (with them it had grown to 20 KB, which a reader
+    of a log's last kilobytes does not get whole)."""
+    details = json.dumps(_rounded({k: out[k] for k in DETAILS if k in out}))
+    return details, json.dumps(_rounded({k: v for k, v in out.items() if k not in DETAILS}))
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -881,7 +905,9 @@ def main():
     if not args.no_cpu:
         _log("bench: CPU oracle baseline")
         out["cpu_baseline"] = cpu_baseline(args.cpu_budget)
-    print(json.dumps(out), flush=True)
+    details, line = split_line(out)
+    _log("bench: details " + details)
+    print(line, flush=True)
 
 
 if __name__ == "__main__":
