@@ -141,11 +141,12 @@ int flat_list_lds(const psclbm_config* c) {
 // costs as many instructions and as much latency as a full one) and, in rows
 // that are no multiple of a cache line, split the lines between neighbouring
 // workgroups at every segment.
-//   3D: wherever nx is no multiple of 64.  A step takes, row -> flat tiles
-//   (with particles): 80^3 FP64 44 -> 35 us; 300x180x190 FP32 404-466 -> 315;
-//   300x180x190 FP16 288-355 -> 251; 250x200x200 FP64 659 -> 560; rows of 120
-//   (94 % full) FP32 23.8 -> 22.2.  Full rows are the better ones as row tiles
-//   (the flat kernel's y varies over the wave, 5 % of the instructions).
+//   3D: wherever nx is no multiple of 64.  A step without particles takes, row ->
+//   flat tiles, 10x100x100 FP32 11.7 -> 6.6 us, 80^3 FP64 27.3 -> 26.0 and FP16
+//   15.0 -> 11.2, 190x96x96 (99 % full) 1.01-1.07 times longer in rows, 250x200x200
+//   FP64 674 -> 587, 300x180x190 FP32 391 -> 308 and FP16 236 -> 168; one sphere
+//   and open faces the same.  Full rows are the better ones as row tiles (the flat
+//   kernel's y varies over the wave, 5 % of the instructions).
 //   2D: only rows of 64 or more that are less than 85 % full (70: 1.06-1.12
 //   times faster, 200: 1.02-1.09); fuller ones gain nothing, and with particles
 //   rows of 40-50 lose 10 % (each row of a wave is searched by itself).
