@@ -1240,10 +1240,20 @@ static int dispatch_step(psclbm_ctx* c, const StepArgs& a, int par, size_t lds_b
   const int nb = c->ntiles + a.dem_blocks;
   if (par == 2) {  // ring step: canonical FP64 in and out
     if constexpr (PREC == PSCLBM_FP64) {
-      if ((double)c->geom.N * Q * sizeof(double) > 256.0 * 1024 * 1024)
-        k_step<Q, PREC, 2, WALLS, FLAT, MORE, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
-      else
-        k_step<Q, PREC, 2, WALLS, FLAT, MORE><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+      // The state read is streamed where it is a little larger than the 256 MB
+      // last-level cache, which then holds more of the state written, the next
+      // step's source: 192x96x96 (256 MB) 113 -> 99 us, 2048^2 (288 MB) 127 ->
+      // 111, 128^3 (304 MB) 130 -> 121; above that the hints cost: 192x128x128
+      // (456 MB) 201 -> 203, 384x192x192 891 -> 942 (256^3 0.99-1.05 times), and
+      // flat tiles, whose waves share lines, 1.06-1.14 times at any size.
+      const double mb = (double)c->geom.N * Q * sizeof(double) / (1024 * 1024);
+      if constexpr (!FLAT) {
+        if (mb > 256.0 && mb <= 352.0) {
+          k_step<Q, PREC, 2, WALLS, FLAT, MORE, true><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
+          return hip_ok(hipGetLastError());
+        }
+      }
+      k_step<Q, PREC, 2, WALLS, FLAT, MORE><<<nb, BLOCK, lds_bytes, c->stream>>>(a);
     } else {
       return PSCLBM_EINVAL;
     }
